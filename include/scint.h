@@ -100,7 +100,7 @@ int ps_supported_size_at(int dtype, int i);
  *   phi_out           device [n_real][N][N] real (dtype)
  * A warning (ps_last_warning) is set when delta >= r_diff/2, the sampling
  * criterion of Sect. 3.2.2.
- * In FP32 from N = 2048 a batch is split into up to four jobs of consecutive
+ * In FP32 from N = 5000 a batch is split into up to four jobs of consecutive
  * realisations whose noise passes carry the previous job's transpose as
  * extra workgroups (SCINT_SCREEN_JOBS=<n> in the environment sets the
  * number, 1 turns the split off); every value is the same bit for bit.
@@ -124,7 +124,7 @@ int ps_generate(int N, double delta, double r_diff, double beta, uint64_t seed,
  *
  *   phi       device [n][N][N] real (input, not modified)
  *   I_out     device [n][N][N] real; must not overlap phi (PS_E_ALIAS)
- * In FP32 from N = 2048 up with n >= 2 the screens run as the pipelined jobs
+ * In FP32 from N = 5000 up with n >= 2 the screens run as the pipelined jobs
  * of illumination_polychromatic (one wavelength), with the same result.
  */
 int fresnel_propagate(int N, double delta, double lambda, double z, const void *phi,
@@ -198,13 +198,15 @@ int ps_screen_fresnel(int N, double delta, double r_diff, double beta, uint64_t 
  *   phi_ref   device [n_real][N][N] real;  I_out device [n_real][N][N] real
  * Work is split into jobs of up to 64 wavelengths and as many realisations as
  * the workspace budget allows (ps_set_workspace_budget).  In FP32 from
- * N = 2048 up the jobs are pipelined (work that fits one job is split into
- * two, by realisations or else by wavelengths): the transpose between the
- * two 1-D passes of one job runs inside the launches of the neighbouring
- * jobs' passes, which takes twice the workspace of the plain loop and gives
- * the same result bit for bit for the same job split (environment
- * SCINT_PIPELINE=0 turns it off).  The pipelined first passes give each row
- * two workgroups, each taking half of the job's wavelengths (same result;
+ * N = 2048 up the jobs are those of a pipeline (work that fits one job is
+ * split into two, by realisations or else by wavelengths).  From N = 5000 the
+ * transpose between the two 1-D passes of one job runs inside the launches of
+ * the neighbouring jobs' passes, which takes twice the workspace of the plain
+ * loop and gives the same result bit for bit for the same job split
+ * (environment SCINT_PIPELINE=0 turns it off); up to 4096 the first pass
+ * stores its field by columns, no transpose runs, and the jobs follow each
+ * other in one field buffer.  The first passes may give each row several
+ * workgroups, each taking a part of the job's wavelengths (same result;
  * SCINT_ITER_SPLIT=1 keeps one).
  */
 int illumination_polychromatic(int N, double delta, double z, const void *phi_ref,
@@ -420,12 +422,13 @@ int ps_set_workspace_budget(size_t bytes);
  * of these sizes under a workspace budget of budget_bytes (host arithmetic
  * only: no device call, callable without a GPU).  Any output pointer may be
  * NULL.
- *   pipelined        1 if the jobs are pipelined (transposes inside the
- *                    passes), 0 for the plain loop
+ *   pipelined        1 if the jobs are those of the pipeline (from N = 5000
+ *                    with the transposes inside the passes), 0 for the plain
+ *                    loop
  *   n_jobs           number of jobs (pipelined) or chunks (plain loop)
  *   lambdas_per_job  wavelengths per job (<= 64)
  *   real_per_job     realisations per job
- *   workspace_bytes  workspace the call asks for
+ *   workspace_bytes  upper bound of the workspace the call asks for
  * Errors as for illumination_polychromatic's sizes; budget_bytes must be > 0.
  */
 int ps_plan_polychromatic(int N, int n_real, int n_lambda, int dtype, size_t budget_bytes, int *pipelined,

@@ -27,7 +27,7 @@ LIBDIR = os.path.join(PKG, "lib")
 LIB = os.path.join(LIBDIR, "libscint.so")
 HIPCC = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
 
-PROGRAMS = ["ProgNoise", "ProgNoiseSwap", "ProgScreen", "ProgScreenProp", "ProgPhaseProp", "ProgPropIntensity",
+PROGRAMS = ["ProgNoise", "ProgNoiseSwap", "ProgScreen", "ProgScreenProp", "ProgPhaseProp", "ProgPhasePropX", "ProgPropIntensity",
             "ProgRealFwd", "ProgFwdRe", "ProgSmearMid", "ProgInvRe", "ProgVjpY", "ProgVjpX",
             "ProgPropField", "ProgVjpYField", "ProgApertureX", "ProgAbs2"]
 # programs built for float only (their side transposes are complex64)

@@ -67,21 +67,21 @@ template <int N> constexpr int conflict_degree(const int (&addr)[N], int n, int 
     return worst;
 }
 
-template <int L, int V> constexpr int exch_conflicts(const ExchLayout &lay, int s, int elem_bytes) {
+template <int L, int V> constexpr int exch_conflicts(const ExchLayout &lay, int s, int elem_bytes, int rows = 1) {
     using P = Plan<L, V>;
     const int T = P::T, R = P::R[s], Ns = stage_ns<L, V>(s), sh = lds_pad_shift<L>();
-    const int n = T < 64 ? T : 64;
+    const int n = T * rows < 64 ? T * rows : 64;  // lane l: thread l / rows of row l % rows
     int worst = 0;
     int a[64] = {};
     for (int r = 0; r < 2 && r < R; ++r) {  // writes of butterflies j = t, outputs r
-        for (int t = 0; t < n; ++t) {
-            const int k = t % Ns;
-            a[t] = layout_at(lay, sh, (t - k) * R + k + r * Ns);
+        for (int l = 0; l < n; ++l) {
+            const int t = l / rows, k = t % Ns;
+            a[l] = layout_at(lay, sh, (t - k) * R + k + r * Ns) * rows + l % rows;
         }
         const int c = conflict_degree(a, n, elem_bytes);
         if (c > worst) worst = c;
     }
-    for (int t = 0; t < n; ++t) a[t] = layout_at(lay, sh, t);  // reads, m = 0
+    for (int l = 0; l < n; ++l) a[l] = layout_at(lay, sh, l / rows) * rows + l % rows;  // reads, m = 0
     const int c = conflict_degree(a, n, elem_bytes);
     return c > worst ? c : worst;
 }
@@ -93,19 +93,21 @@ template <int L, int V> constexpr bool linear_ok(int s, int Pd) {
     return (Ns % Pd == 0 || Pd % (Ns * R) == 0) && T % Pd == 0;
 }
 
-// The layout of exchange s (0 <= s < NS - 1) for elements of elem_bytes.
-template <int L, int V> constexpr ExchLayout exch_layout(int s, int elem_bytes) {
+// The layout of exchange s (0 <= s < NS - 1) for elements of elem_bytes, with
+// `rows` rows interleaved (element p of row b at f(p) rows + b; 1: a row on
+// its own).
+template <int L, int V> constexpr ExchLayout exch_layout(int s, int elem_bytes, int rows = 1) {
     using P = Plan<L, V>;
     const int T = P::T, sh = lds_pad_shift<L>(), limit = fixed_layout_length<L>();
     ExchLayout best{false, 0, limit};
-    int best_c = exch_conflicts<L, V>(best, s, elem_bytes);
+    int best_c = exch_conflicts<L, V>(best, s, elem_bytes, rows);
     bool have_linear = false;
     auto consider = [&](int Pd) {
         if (!linear_ok<L, V>(s, Pd)) return;
         const int len = Pd > 0 ? L + L / Pd : L;
         if (len > limit) return;
         const ExchLayout cand{true, Pd, len};
-        const int c = exch_conflicts<L, V>(cand, s, elem_bytes);
+        const int c = exch_conflicts<L, V>(cand, s, elem_bytes, rows);
         if (c < best_c || (c == best_c && !have_linear)) {
             best = cand;
             best_c = c;
@@ -120,13 +122,71 @@ template <int L, int V> constexpr ExchLayout exch_layout(int s, int elem_bytes) 
 }
 
 // Elements a row's exchange buffer takes: the largest exchange layout.
-template <int L, int V> constexpr int exch_buffer_length(int elem_bytes) {
+template <int L, int V> constexpr int exch_buffer_length(int elem_bytes, int rows = 1) {
     int len = L;
     for (int s = 0; s + 1 < Plan<L, V>::NS; ++s) {
-        const int l = exch_layout<L, V>(s, elem_bytes).length;
+        const int l = exch_layout<L, V>(s, elem_bytes, rows).length;
         if (l > len) len = l;
     }
     return len;
+}
+
+// ---------------------------------------------------------------- columns
+// Passes that hand their result to a pass along the other axis store it by
+// columns up to 4096, so that no transpose runs between the two: the workgroup
+// interleaves a few rows in its lanes (lane l is thread l / rows of row
+// l % rows), and each element's store is a run of rows x elem_bytes.  Runs of
+// 32 bytes meet in the L2 when the workgroups that share their lines run next
+// to each other on one XCD; that needs rows small enough for four of them in
+// the LDS.  Longer rows fit two at most, and runs of 16 bytes leave the L2
+// before their line is whole (8192: 1.4 TB/s in the first propagation pass,
+// 3.08 ms for 8 wavelengths against 2.5 ms with the transposes beside it), so
+// from 5000 on the transposes stay.
+constexpr int kColumnsMaxL = 4096;
+constexpr bool stores_columns(int L) { return L <= kColumnsMaxL; }
+
+// Real arrays are read and written by columns too while they stay in cache;
+// above, runs half as long cost more than their transpose (2048: 140 us more
+// in a pass over 16 patterns, transpose 84-104 us).
+constexpr int kRealColumnsMaxL = 1024;
+constexpr bool real_columns(int L) { return L <= kRealColumnsMaxL; }
+
+// Rows that such a workgroup interleaves: runs of 32 bytes in FP32 (16 x
+// 2048^2 forward + adjoint: 1.97 ms; 16 bytes 2.26, 64 bytes 2.24 ms, whose
+// 1024-thread workgroups fill a CU alone), 64 in FP64, fewer where the LDS
+// would hold one workgroup only, and fewer at the small sizes, whose rows
+// would not occupy the chip.
+template <int L, int V> constexpr int column_rows(int elem_bytes) {
+    const int T = Plan<L, V>::T;
+    int rows = 1;
+    while (2 * rows <= 4 && 2 * rows * 120 <= L) rows *= 2;
+    while (T * rows < 32) rows *= 2;
+    while (rows > 1 && (T * rows > 1024 || rows * exch_buffer_length<L, V>(elem_bytes, rows) * elem_bytes >
+                                               (rows * elem_bytes > 32 ? 80 : 160) * 1024))
+        rows /= 2;
+    return rows;
+}
+
+// Row group and part (of `parts` workgroups that share a group's loop
+// iterations) of workgroup w.  Workgroup w runs on XCD w % 8: the `line` row
+// groups that share cache lines of what they store go to one XCD, next to each
+// other in time, so that the parts of a line meet in its L2.
+struct ColumnSlot {
+    int group, part;
+};
+constexpr ColumnSlot column_slot(int w, int line, int parts) {
+    const int q = w >> 3, set = q / line / parts;
+    return ColumnSlot{(set * 8 + (w & 7)) * line + q % line, q / line % parts};
+}
+
+// Elements from one row of such a field to the next.  Stores by columns step
+// by whole rows: whole lines of 128 bytes, and 13 lines more from 2000 on,
+// which spreads them over the channels of the L2 (runs of 32 bytes written
+// alone: 4096 2.3 -> 4.5 TB/s, 2048 3.5 -> 3.9, 2000 2.3 -> 2.9, 2560
+// 4.0 -> 4.4; one line more is the worst choice at 2048, 1.8).
+constexpr int field_pitch(int L, int elem_bytes) {
+    const int line = 128 / elem_bytes;
+    return stores_columns(L) ? (L + line - 1) / line * line + (L >= 2000 ? 13 * line : 0) : L;
 }
 
 }  // namespace scint

@@ -4,6 +4,8 @@
 #include "row_kernel.hpp"
 #include "row_launch.h"
 
+#include <algorithm>
+
 #ifndef SCINT_REAL
 #error "SCINT_REAL (float or double) must be defined"
 #endif
@@ -18,8 +20,25 @@ namespace scint {
 
 template <int L, int V>
 static hipError_t launch_one(const RowProgram &prog, const void *tw, hipStream_t stream) {
-    using Cfg = RowCfg<SCINT_REAL, L, V>;
+    using Cfg = RowCfg<SCINT_REAL, L, V, program_rows<SCINT_REAL, L, V, SCINT_PROG>()>;
+    // sizes that store by columns need no transposes beside their passes, and
+    // only those of real_columns take phase screens by columns
+    constexpr bool wanted = !(stores_columns(L) && has_side<SCINT_PROG>()) &&
+                            (real_columns(L) || !std::is_same<SCINT_PROG, ProgPhasePropX>::value);
+    if constexpr (!wanted) {
+        return hipErrorInvalidValue;
+    } else {
     RowProgram p = prog;
+    if constexpr (Cfg::IL) {
+        // whole sets of 8 XCDs x LINE_GROUPS row groups (row_kernel)
+        const int64_t set = 8 * Cfg::LINE_GROUPS, groups = (prog.total_rows + Cfg::B - 1) / Cfg::B;
+        p.iter_split = iter_splittable<SCINT_PROG>() ? std::min(std::max(prog.iter_split, 1), prog.n_iter) : 1;
+        const int64_t grid = (groups + set - 1) / set * set * p.iter_split;
+        if (grid > (1ll << 31) - 1) return hipErrorInvalidValue;
+        hipLaunchKernelGGL((row_kernel<SCINT_REAL, L, V, SCINT_PROG>), dim3((unsigned)grid), dim3(Cfg::THREADS), 0,
+                           stream, p, static_cast<const cpx<SCINT_REAL> *>(tw));
+        return hipGetLastError();
+    }
     // two workgroups per row only where the program allows it, the loop has
     // two or more iterations and the row workgroups come in whole eights
     const int row_wgs = (prog.total_rows + Cfg::B - 1) / Cfg::B;
@@ -47,6 +66,7 @@ static hipError_t launch_one(const RowProgram &prog, const void *tw, hipStream_t
                            stream, p, static_cast<const cpx<SCINT_REAL> *>(tw));
     }
     return hipGetLastError();
+    }
 }
 
 template <>

@@ -89,16 +89,22 @@ template <int R, long long C, long long M> struct TwConst {
     }
 };
 
-template <typename Real, int L, int V = 0> struct RowCfg {
+template <typename Real, int L, int V = 0, int W = 0> struct RowCfg {
     using P = Plan<L, V>;
     static constexpr int T = P::T;
     static constexpr int ELEM = 2 * (int)sizeof(Real);
+    // W > 0: the workgroup's W rows are interleaved, lane l being thread l / W
+    // of row l % W, and element p of row b lies at f(p) W + b in LDS
+    static constexpr bool IL = W > 0;
+    static constexpr int LS = IL ? W : 1;
     // elements of a row's exchange buffer (the largest exchange layout)
-    static constexpr int LDS_STRIDE = exch_buffer_length<L, V>(ELEM);
+    static constexpr int LDS_STRIDE = exch_buffer_length<L, V>(ELEM, LS);
     static constexpr int B_THREADS = T >= 256 ? 1 : 256 / T;
     static constexpr int B_LDS = (P::NS > 1) ? ((65536 / (LDS_STRIDE * ELEM)) > 0 ? 65536 / (LDS_STRIDE * ELEM) : 1)
                                              : B_THREADS;
-    static constexpr int B = B_THREADS < B_LDS ? B_THREADS : B_LDS;  // rows per workgroup
+    static constexpr int B = IL ? W : B_THREADS < B_LDS ? B_THREADS : B_LDS;  // rows per workgroup
+    // interleaved row groups whose stores by columns share 128-byte lines
+    static constexpr int LINE_GROUPS = 128 / (B * ELEM) > 1 ? 128 / (B * ELEM) : 1;
     static constexpr int THREADS = T * B;
     // LDS: the FFT exchange buffers, then the twiddle cache when it fits (two
     // workgroups per CU kept where the rows allowed two), or at least one
@@ -121,6 +127,7 @@ template <typename Real, int L, int V = 0> struct RowCfg {
 #endif
     static constexpr int WAVES_WG = (THREADS + 63) / 64;
     static constexpr int WAVES_PER_EU =
+        IL ? (sizeof(Real) == 4 && WAVES_WG >= 8 && 2 * LDS_BYTES <= 160 * 1024 ? 4 : SCINT_WAVES_PER_EU) :
         (L >= 10000 && WAVES_WG == 8 && 2 * LDS_BYTES <= 160 * 1024 && SCINT_WAVES_PER_EU < 4) ? 4
                                                                                                  : SCINT_WAVES_PER_EU;
     // Mixed-radix rows of 10000 and more: each FFT stage (and each loop
@@ -201,12 +208,12 @@ template <typename Real, int R> __device__ __forceinline__ void load_bases(cpx<R
     for (int b = 0; b < tw_nbase<R>(); ++b) bv[b] = w[tw_base_power<R>(b)];
 }
 
-template <typename Real, int L, int V, int s, int i = 0>
+template <typename Real, int L, int V, int W, int s, int i = 0>
 __device__ __forceinline__ void stage_butterflies(cpx<Real> (&v)[(Plan<L, V>::E)], cpx<Real> *lds, int t,
                                                   const cpx<Real> *__restrict__ tw, const cpx<Real> *twc,
                                                   TwGroup<Real, Plan<L, V>::R[s]> &tg);
 
-template <typename Real, int L, int V, int s>
+template <typename Real, int L, int V, int W, int s>
 __device__ __forceinline__ void fft_stage(cpx<Real> (&v)[(Plan<L, V>::E)], cpx<Real> *lds, int t,
                                           const cpx<Real> *__restrict__ tw, const cpx<Real> *twc) {
     using P = Plan<L, V>;
@@ -216,9 +223,9 @@ __device__ __forceinline__ void fft_stage(cpx<Real> (&v)[(Plan<L, V>::E)], cpx<R
     constexpr bool last = (s == P::NS - 1);
     // t as seen by this stage's butterflies (see RowCfg::REMAT_T)
     int ts = t;
-    if constexpr (RowCfg<Real, L, V>::REMAT_T) asm volatile("" : "+v"(ts));
+    if constexpr (RowCfg<Real, L, V, W>::REMAT_T) asm volatile("" : "+v"(ts));
     TwGroup<Real, R> tg;
-    if constexpr (mode != 0 && RowCfg<Real, L, V>::TWC_ON) {
+    if constexpr (mode != 0 && RowCfg<Real, L, V, W>::TWC_ON) {
         // the thread's base twiddles, once for all its butterflies of the stage
         cpx<Real> bv[tw_nbase<R>()];
         const cpx<Real> *src = twc + tw_cache_offset<L, V>(s) + (mode == 1 ? ts % Ns : ts) * tw_nbase<R>();
@@ -226,26 +233,27 @@ __device__ __forceinline__ void fft_stage(cpx<Real> (&v)[(Plan<L, V>::E)], cpx<R
         for (int b = 0; b < tw_nbase<R>(); ++b) bv[b] = src[b];
         tg.build(bv);
     }
-    stage_butterflies<Real, L, V, s, 0>(v, lds, ts, tw, twc, tg);
+    stage_butterflies<Real, L, V, W, s, 0>(v, lds, ts, tw, twc, tg);
     if constexpr (!last) {
         __syncthreads();
-        constexpr ExchLayout lay = exch_layout<L, V>(s, 2 * (int)sizeof(Real));
+        constexpr int LS = RowCfg<Real, L, V, W>::LS;
+        constexpr ExchLayout lay = exch_layout<L, V>(s, 2 * (int)sizeof(Real), LS);
         if constexpr (lay.linear) {
             // f(t + m T) = f(t) + m (T + T / P): one address, then offsets
             constexpr int step = T + (lay.P > 0 ? T / lay.P : 0);
             const int q = lay.P > 0 ? ts + (int)((unsigned)ts / (unsigned)lay.P) : ts;
 #pragma unroll
-            for (int m = 0; m < E; ++m) v[m] = lds[q + m * step];
+            for (int m = 0; m < E; ++m) v[m] = lds[q * LS + m * (step * LS)];
         } else {
 #pragma unroll
-            for (int m = 0; m < E; ++m) v[m] = lds[lds_index<L>(ts + m * T)];
+            for (int m = 0; m < E; ++m) v[m] = lds[lds_index<L>(ts + m * T) * LS];
         }
         __syncthreads();
-        fft_stage<Real, L, V, s + 1>(v, lds, t, tw, twc);
+        fft_stage<Real, L, V, W, s + 1>(v, lds, t, tw, twc);
     }
 }
 
-template <typename Real, int L, int V, int s, int i>
+template <typename Real, int L, int V, int W, int s, int i>
 __device__ __forceinline__ void stage_butterflies(cpx<Real> (&v)[(Plan<L, V>::E)], cpx<Real> *lds, int t,
                                                   const cpx<Real> *__restrict__ tw, const cpx<Real> *twc,
                                                   TwGroup<Real, Plan<L, V>::R[s]> &tg) {
@@ -261,7 +269,7 @@ __device__ __forceinline__ void stage_butterflies(cpx<Real> (&v)[(Plan<L, V>::E)
 #pragma unroll
         for (int r = 0; r < R; ++r) a[r] = v[i + r * Q];
         if constexpr (Ns > 1) {
-            if constexpr (mode != 0 && RowCfg<Real, L, V>::TWC_ON) {
+            if constexpr (mode != 0 && RowCfg<Real, L, V, W>::TWC_ON) {
                 constexpr long long C = (mode == 2) ? (long long)(i % (Ns / T)) * T : 0;
                 apply_twiddles<Real, R, C, (long long)Ns * R>(a, tg);
             } else {
@@ -280,20 +288,21 @@ __device__ __forceinline__ void stage_butterflies(cpx<Real> (&v)[(Plan<L, V>::E)
             for (int r = 0; r < R; ++r) v[i + r * Q] = a[r];
         } else {
             const int base = (j - k) * R + k;
-            constexpr ExchLayout lay = exch_layout<L, V>(s, 2 * (int)sizeof(Real));
+            constexpr int LS = RowCfg<Real, L, V, W>::LS;
+            constexpr ExchLayout lay = exch_layout<L, V>(s, 2 * (int)sizeof(Real), LS);
             if constexpr (lay.linear) {
                 // f(base + r Ns) = f(base) + r (Ns + Ns / P) if P divides Ns,
                 // f(base) + r Ns if the butterfly's outputs share one period
                 constexpr int step = Ns + ((lay.P > 0 && Ns % lay.P == 0) ? Ns / lay.P : 0);
                 const int q = lay.P > 0 ? base + (int)((unsigned)base / (unsigned)lay.P) : base;
 #pragma unroll
-                for (int r = 0; r < R; ++r) lds[q + r * step] = a[r];
+                for (int r = 0; r < R; ++r) lds[q * LS + r * (step * LS)] = a[r];
             } else {
 #pragma unroll
-                for (int r = 0; r < R; ++r) lds[lds_index<L>(base + r * Ns)] = a[r];
+                for (int r = 0; r < R; ++r) lds[lds_index<L>(base + r * Ns) * LS] = a[r];
             }
         }
-        stage_butterflies<Real, L, V, s, i + 1>(v, lds, t, tw, twc, tg);
+        stage_butterflies<Real, L, V, W, s, i + 1>(v, lds, t, tw, twc, tg);
     }
 }
 
@@ -317,10 +326,10 @@ __device__ __forceinline__ void fill_tw_cache(cpx<Real> *twc, const cpx<Real> *_
 }
 
 // Forward DFT of the register row (natural order in, natural order out).
-template <typename Real, int L, int V>
+template <typename Real, int L, int V, int W>
 __device__ __forceinline__ void fft_forward(cpx<Real> (&v)[(Plan<L, V>::E)], cpx<Real> *lds, int t,
                                             const cpx<Real> *__restrict__ tw, const cpx<Real> *twc) {
-    fft_stage<Real, L, V, 0>(v, lds, t, tw, twc);
+    fft_stage<Real, L, V, W, 0>(v, lds, t, tw, twc);
 }
 
 // ---------------------------------------------------------------- pointwise
@@ -414,7 +423,7 @@ template <class Ops> constexpr int find_endloop(int i) {
 // two-lane vector of Real, the unit of the streaming complex loads and stores
 template <typename Real> using Real2 = Real __attribute__((ext_vector_type(2)));
 
-template <typename Real, int L, int V> struct RowState {
+template <typename Real, int L, int V, int W> struct RowState {
     static constexpr int E = Plan<L, V>::E;
     cpx<Real> v[E];
     Real acc[E];
@@ -447,7 +456,7 @@ template <typename Real, int L, int V> struct RowState {
 // kept as the pair v = (hi, lo), hi = phi rounded to FP32 and lo the FP32
 // remainder, so that the stored screen is phi correctly rounded and the phase
 // factor can take phi to FP64 accuracy (RF_HILO).
-template <int L, int V, int E = Plan<L, V>::E>
+template <int L, int V, int W, int E = Plan<L, V>::E>
 __device__ __forceinline__ void add_low_modes(cpx<float> *v, const void *low_tab, int grow, int t) {
     constexpr int K = low_modes_k_of(L);
     static_assert(E % 2 == 0, "elements per thread must be even");
@@ -455,7 +464,7 @@ __device__ __forceinline__ void add_low_modes(cpx<float> *v, const void *low_tab
     // the constant address space, so that a workgroup of one row keeps them
     // in scalar registers (the table is written by an earlier launch)
     using ConstRow = const __attribute__((address_space(4))) double *;
-    if constexpr (RowCfg<float, L, V>::B == 1) grow = __builtin_amdgcn_readfirstlane(grow);
+    if constexpr (RowCfg<float, L, V, W>::B == 1) grow = __builtin_amdgcn_readfirstlane(grow);
     const ConstRow Gc = (ConstRow)(static_cast<const double *>(low_tab) + (int64_t)grow * (2 * (K + 1)));
     const double sw = sinpi(2.0 * (double)t / (double)L), cw = cospi(2.0 * (double)t / (double)L);
     double dr[K + 1], di[K + 1];
@@ -508,16 +517,21 @@ __device__ __forceinline__ void add_low_modes(cpx<float> *v, const void *low_tab
     }
 }
 
-template <typename Real, int L, int V, int CODE>
-__device__ __forceinline__ void exec_op(RowState<Real, L, V> &st, const RowOp &op) {
-    constexpr int E = Plan<L, V>::E, T = Plan<L, V>::T;
+template <typename Real, int L, int V, int W, int CODEX>
+__device__ __forceinline__ void exec_op(RowState<Real, L, V, W> &st, const RowOp &op) {
+    constexpr int E = Plan<L, V>::E;
+    // an operand that lies the other way round: its elements are a row apart
+    constexpr bool X = lies_across(CODEX, L);
+    constexpr int CODE = rop_plain(CODEX);
+    constexpr int PITCH = CODE == ROP_STORE_C ? field_pitch(L, 2 * (int)sizeof(Real)) : L;
+    constexpr int T = X ? Plan<L, V>::T * PITCH : Plan<L, V>::T;  // between a thread's elements of the operand
     auto &v = st.v;
     // Rows past the end of the batch (st.valid false) are given batch 0,
     // row 0, so their loads stay inside the operands and need no predicate
     // (a per-element guard serialises the loads); only stores are guarded.
     const bool valid = st.valid;
     const int64_t off = (int64_t)st.batch * op.batch_stride + (int64_t)st.it * op.iter_stride +
-                        (int64_t)st.row * op.row_stride + st.t;
+                        (X ? (int64_t)st.t * PITCH + st.row : (int64_t)st.row * op.row_stride + st.t);
     const double s = (op.flags & RF_ITER_SCALE) ? st.prog->scale[st.it] : op.param;
     if constexpr (CODE == ROP_LOAD_C) {
         // complex rows are read once per pass: streaming (nontemporal) loads
@@ -541,7 +555,7 @@ __device__ __forceinline__ void exec_op(RowState<Real, L, V> &st, const RowOp &o
         const Real *src = static_cast<const Real *>(op.ptr) + off;
         const double sturn = s * (0.5 / kPi);
 #pragma unroll
-        for (int m = 0; m < E; ++m) v[m] = expi_turns<Real>(sturn * (double)src[m * T]);
+        for (int m = 0; m < E; ++m) v[m] = expi_turns<Real>(sturn * (double)src[(int64_t)m * T]);
     } else if constexpr (CODE == ROP_NOISE) {
         const uint32_t r = (uint32_t)st.prog->r0 + (uint32_t)st.batch;
 #pragma unroll
@@ -559,12 +573,12 @@ __device__ __forceinline__ void exec_op(RowState<Real, L, V> &st, const RowOp &o
 #pragma unroll
         for (int m = 0; m < E; ++m) v[m] = expi_turns<Real>(sturn * (double)st.keep[m]);
     } else if constexpr (CODE == ROP_FFT_FWD) {
-        fft_forward<Real, L, V>(v, st.lds, st.t, st.tw, st.twc);
+        fft_forward<Real, L, V, W>(v, st.lds, st.t, st.tw, st.twc);
     } else if constexpr (CODE == ROP_FFT_INV) {
         // IDFT(v) = conj(DFT(conj(v)))
 #pragma unroll
         for (int m = 0; m < E; ++m) v[m].im = -v[m].im;
-        fft_forward<Real, L, V>(v, st.lds, st.t, st.tw, st.twc);
+        fft_forward<Real, L, V, W>(v, st.lds, st.t, st.tw, st.twc);
 #pragma unroll
         for (int m = 0; m < E; ++m) v[m].im = -v[m].im;
     } else if constexpr (CODE == ROP_MUL_TAB) {
@@ -590,12 +604,12 @@ __device__ __forceinline__ void exec_op(RowState<Real, L, V> &st, const RowOp &o
         const Real *src = static_cast<const Real *>(op.ptr) + off;
         const Real sc = (Real)op.param;
 #pragma unroll
-        for (int m = 0; m < E; ++m) v[m] = cscale(v[m], sc * src[m * T]);
+        for (int m = 0; m < E; ++m) v[m] = cscale(v[m], sc * src[(int64_t)m * T]);
     } else if constexpr (CODE == ROP_SQRT2RE) {
         // FP32 screens always take their lowest modes from the FP64 table
         // (the host builds it for every FP32 screen pass)
         if constexpr (std::is_same<Real, float>::value) {
-            add_low_modes<L, V>(v, st.prog->low_tab, st.batch * L + st.row, st.t);  // < 2^30 rows
+            add_low_modes<L, V, W>(v, st.prog->low_tab, st.batch * L + st.row, st.t);  // < 2^30 rows
         } else {
 #pragma unroll
             for (int m = 0; m < E; ++m) v[m] = {sqrt2_of<Real>() * v[m].re, (Real)0};
@@ -620,10 +634,14 @@ __device__ __forceinline__ void exec_op(RowState<Real, L, V> &st, const RowOp &o
             cpx<Real> *dst = static_cast<cpx<Real> *>(const_cast<void *>(op.ptr)) + off;
 #pragma unroll
             for (int m = 0; m < E; ++m) {
-                Real2<Real> x;
-                x.x = v[m].re;
-                x.y = v[m].im;
-                __builtin_nontemporal_store(x, reinterpret_cast<Real2<Real> *>(dst + m * T));
+                if constexpr (X) {  // part of a line: left to the L2 to complete
+                    dst[(int64_t)m * T] = v[m];
+                } else {
+                    Real2<Real> x;
+                    x.x = v[m].re;
+                    x.y = v[m].im;
+                    __builtin_nontemporal_store(x, reinterpret_cast<Real2<Real> *>(dst + m * T));
+                }
             }
         }
     } else if constexpr (CODE == ROP_STORE_R) {
@@ -650,10 +668,10 @@ __device__ __forceinline__ void exec_op(RowState<Real, L, V> &st, const RowOp &o
             Real *dst = static_cast<Real *>(const_cast<void *>(op.ptr)) + off;
             if (op.flags & RF_ADD) {
 #pragma unroll
-                for (int m = 0; m < E; ++m) dst[m * T] += st.acc[m];
+                for (int m = 0; m < E; ++m) dst[(int64_t)m * T] += st.acc[m];
             } else {
 #pragma unroll
-                for (int m = 0; m < E; ++m) dst[m * T] = st.acc[m];
+                for (int m = 0; m < E; ++m) dst[(int64_t)m * T] = st.acc[m];
             }
         }
     } else if constexpr (CODE == ROP_SAVE) {
@@ -682,8 +700,9 @@ __device__ __forceinline__ void exec_op(RowState<Real, L, V> &st, const RowOp &o
         __syncthreads();
         red[st.tid] = part;
         __syncthreads();
+        constexpr int LS = RowCfg<Real, L, V, W>::LS;
         for (int width = 1; width < T; width *= 2) {
-            if ((st.t % (2 * width)) == 0 && st.t + width < T) red[st.tid] += red[st.tid + width];
+            if ((st.t % (2 * width)) == 0 && st.t + width < T) red[st.tid] += red[st.tid + width * LS];
             __syncthreads();
         }
         if (st.t == 0 && valid) static_cast<double *>(op.ptr2)[st.g] = red[st.tid];
@@ -695,8 +714,8 @@ __device__ __forceinline__ void exec_op(RowState<Real, L, V> &st, const RowOp &o
     }
 }
 
-template <typename Real, int L, int V, class Ops, int I, int End>
-__device__ __forceinline__ void run_ops(RowState<Real, L, V> &st) {
+template <typename Real, int L, int V, int W, class Ops, int I, int End>
+__device__ __forceinline__ void run_ops(RowState<Real, L, V, W> &st) {
     if constexpr (I < End) {
         constexpr int c = Ops::code[I];
         if constexpr (c == ROP_LOOP) {
@@ -704,14 +723,14 @@ __device__ __forceinline__ void run_ops(RowState<Real, L, V> &st) {
 #pragma clang loop unroll(disable)
             for (st.it = st.it0; st.it < st.it1; ++st.it) {
                 // (RowCfg::REMAT_T: addresses formed again per iteration)
-                if constexpr (RowCfg<Real, L, V>::REMAT_T) asm volatile("" : "+v"(st.t));
-                run_ops<Real, L, V, Ops, I + 1, e>(st);
+                if constexpr (RowCfg<Real, L, V, W>::REMAT_T) asm volatile("" : "+v"(st.t));
+                run_ops<Real, L, V, W, Ops, I + 1, e>(st);
             }
             st.it = 0;
-            run_ops<Real, L, V, Ops, e + 1, End>(st);
+            run_ops<Real, L, V, W, Ops, e + 1, End>(st);
         } else {
-            exec_op<Real, L, V, c>(st, st.prog->op[I]);
-            run_ops<Real, L, V, Ops, I + 1, End>(st);
+            exec_op<Real, L, V, W, c>(st, st.prog->op[I]);
+            run_ops<Real, L, V, W, Ops, I + 1, End>(st);
         }
     }
 }
@@ -726,17 +745,25 @@ template <class Ops> constexpr bool iter_splittable() {
     if (i >= Ops::n || Ops::code[i] != ROP_LOOP) return false;
     for (++i; i < Ops::n && Ops::code[i] != ROP_ENDLOOP; ++i) {
         const int c = Ops::code[i];
-        if (c != ROP_LOAD_PHASE && c != ROP_LOAD_C && c != ROP_FFT_FWD && c != ROP_FFT_INV && c != ROP_MUL_TAB &&
-            c != ROP_STORE_C)
+        if (c != ROP_LOAD_PHASE && c != ROP_LOAD_PHASEX && c != ROP_LOAD_C && c != ROP_FFT_FWD && c != ROP_FFT_INV && c != ROP_MUL_TAB &&
+            c != ROP_STORE_C && c != ROP_STORE_CX)
             return false;
     }
     return i == Ops::n - 1;
 }
 
+// Rows interleaved in the lanes (0: none): the programs with an operand that
+// lies the other way round at this size.
+template <typename Real, int L, int V, class Ops> constexpr int program_rows() {
+    for (int i = 0; i < Ops::n; ++i)
+        if (lies_across(Ops::code[i], L)) return column_rows<L, V>(2 * (int)sizeof(Real));
+    return 0;
+}
+
 // LDS of a row kernel: the row pass's, or the transpose tile's if larger
 // (programs with side transposes)
 template <typename Real, int L, int V, class Ops> constexpr int row_kernel_lds() {
-    constexpr int a = RowCfg<Real, L, V>::LDS_BYTES, b = (int)sizeof(TransposeTile<cpx<float>>);
+    constexpr int a = RowCfg<Real, L, V, program_rows<Real, L, V, Ops>()>::LDS_BYTES, b = (int)sizeof(TransposeTile<cpx<float>>);
     return has_side<Ops>() && a < b ? b : a;
 }
 
@@ -762,11 +789,11 @@ __device__ __forceinline__ void side_transposes(const RowSide &sd, int N, int sb
     }
 }
 
-template <typename Real, int L, int V, class Ops>
-__global__ __launch_bounds__((RowCfg<Real, L, V>::THREADS))
-__attribute__((amdgpu_waves_per_eu(RowCfg<Real, L, V>::WAVES_PER_EU))) void row_kernel(const RowProgram prog,
+template <typename Real, int L, int V, class Ops, int W = program_rows<Real, L, V, Ops>()>
+__global__ __launch_bounds__((RowCfg<Real, L, V, W>::THREADS))
+__attribute__((amdgpu_waves_per_eu(RowCfg<Real, L, V, W>::WAVES_PER_EU))) void row_kernel(const RowProgram prog,
                                                                            const cpx<Real> *__restrict__ tw) {
-    using Cfg = RowCfg<Real, L, V>;
+    using Cfg = RowCfg<Real, L, V, W>;
     constexpr int E = Plan<L, V>::E, T = Plan<L, V>::T, B = Cfg::B;
     __shared__ __align__(16) unsigned char lds_raw[row_kernel_lds<Real, L, V, Ops>()];
     int rb = blockIdx.x;  // row workgroup number
@@ -786,7 +813,17 @@ __attribute__((amdgpu_waves_per_eu(RowCfg<Real, L, V>::WAVES_PER_EU))) void row_
         rb = grp * sd.fft_blocks + r;
     }
     int it0 = 0, it1 = prog.n_iter;
-    if constexpr (iter_splittable<Ops>()) {
+    if constexpr (Cfg::IL) {
+        // (uniform per workgroup, so the early return comes before any barrier)
+        const int groups = (prog.total_rows + B - 1) / B;
+        const int parts = iter_splittable<Ops>() ? prog.iter_split : 1;
+        const ColumnSlot slot = column_slot(rb, Cfg::LINE_GROUPS, parts);
+        rb = slot.group;
+        if (rb >= groups) return;
+        const int h = (prog.n_iter + parts - 1) / parts;
+        it0 = min(slot.part * h, prog.n_iter);
+        it1 = min(it0 + h, prog.n_iter);
+    } else if constexpr (iter_splittable<Ops>()) {
         if (prog.iter_split == 2) {
             // row workgroups q and q + 8 of each 16 share row workgroup
             // 8 (q / 16) + q % 8
@@ -800,16 +837,16 @@ __attribute__((amdgpu_waves_per_eu(RowCfg<Real, L, V>::WAVES_PER_EU))) void row_
     if constexpr (has_side<Ops>()) {
         if ((int64_t)rb * B >= prog.total_rows) return;
     }
-    RowState<Real, L, V> st;
+    RowState<Real, L, V, W> st;
     st.prog = &prog;
     st.tid = threadIdx.x;
-    const int bsub = st.tid / T;
-    st.t = st.tid - bsub * T;
+    const int bsub = Cfg::IL ? st.tid % B : st.tid / T;
+    st.t = Cfg::IL ? st.tid / B : st.tid - bsub * T;
     st.g = rb * B + bsub;  // global row over the batch
     st.valid = st.g < prog.total_rows;
     st.batch = st.valid ? st.g / L : 0;
     st.row = st.valid ? st.g - st.batch * L : 0;
-    st.lds = reinterpret_cast<cpx<Real> *>(lds_raw) + bsub * Cfg::LDS_STRIDE;
+    st.lds = reinterpret_cast<cpx<Real> *>(lds_raw) + (Cfg::IL ? bsub : bsub * Cfg::LDS_STRIDE);
     st.red = reinterpret_cast<double *>(lds_raw);
     st.tw = tw;
     st.twc = nullptr;
@@ -827,55 +864,59 @@ __attribute__((amdgpu_waves_per_eu(RowCfg<Real, L, V>::WAVES_PER_EU))) void row_
         st.v[m] = {(Real)0, (Real)0};
         st.acc[m] = (Real)0;
     }
-    run_ops<Real, L, V, Ops, 0, Ops::n>(st);
+    run_ops<Real, L, V, W, Ops, 0, Ops::n>(st);
 }
 
 // The row programs used by the library.  Each name lists its op codes; the
 // host fills the operands of op[i] for code i.
-using ProgNoise = OpList<ROP_NOISE, ROP_FFT_INV, ROP_STORE_C>;
+using ProgNoise = OpList<ROP_NOISE, ROP_FFT_INV, ROP_STORE_CX>;
 // the noise pass carrying the transpose of an earlier batch's output (RowSide)
-using ProgNoiseT = OpList<ROP_SIDE_T, ROP_NOISE, ROP_FFT_INV, ROP_STORE_C>;
+using ProgNoiseT = OpList<ROP_SIDE_T, ROP_NOISE, ROP_FFT_INV, ROP_STORE_CX>;
 // the same along kx (rows ky), for screens made transposed
-using ProgNoiseSwap = OpList<ROP_NOISE_SWAP, ROP_FFT_INV, ROP_STORE_C>;
-using ProgNoiseSwapT = OpList<ROP_SIDE_T, ROP_NOISE_SWAP, ROP_FFT_INV, ROP_STORE_C>;
+using ProgNoiseSwap = OpList<ROP_NOISE_SWAP, ROP_FFT_INV, ROP_STORE_CX>;
+using ProgNoiseSwapT = OpList<ROP_SIDE_T, ROP_NOISE_SWAP, ROP_FFT_INV, ROP_STORE_CX>;
 using ProgScreen = OpList<ROP_LOAD_C, ROP_FFT_INV, ROP_SQRT2RE, ROP_STORE_R>;
 using ProgScreenProp = OpList<ROP_LOAD_C, ROP_FFT_INV, ROP_SQRT2RE, ROP_STORE_R, ROP_EXP_RE, ROP_FFT_FWD,
-                              ROP_MUL_TAB, ROP_FFT_INV, ROP_STORE_C>;
+                              ROP_MUL_TAB, ROP_FFT_INV, ROP_STORE_CX>;
 // (the phase is re-read for every wavelength: keeping it in registers
 // costs more in occupancy than the cached re-read)
-using ProgPhaseProp = OpList<ROP_LOOP, ROP_LOAD_PHASE, ROP_FFT_FWD, ROP_MUL_TAB, ROP_FFT_INV, ROP_STORE_C,
+using ProgPhaseProp = OpList<ROP_LOOP, ROP_LOAD_PHASE, ROP_FFT_FWD, ROP_MUL_TAB, ROP_FFT_INV, ROP_STORE_CX,
                              ROP_ENDLOOP>;
+// the same on phase screens read by columns (the sizes of real_columns), so
+// that the second pass runs along x and writes the pattern in natural order
+using ProgPhasePropX = OpList<ROP_LOOP, ROP_LOAD_PHASEX, ROP_FFT_FWD, ROP_MUL_TAB, ROP_FFT_INV, ROP_STORE_CX,
+                              ROP_ENDLOOP>;
 // (the weights of a co-addition ride in the chirp tables, so the sum of
 // |.|^2 takes no product by them)
 using ProgPropIntensity = OpList<ROP_LOOP, ROP_LOAD_C, ROP_FFT_FWD, ROP_MUL_TAB, ROP_FFT_INV, ROP_ACC_ABS2U,
                                  ROP_ENDLOOP, ROP_STORE_ACC>;
 // the two propagation passes carrying transposes of other data (RowSide)
 using ProgPhasePropT = OpList<ROP_SIDE_T, ROP_LOOP, ROP_LOAD_PHASE, ROP_FFT_FWD, ROP_MUL_TAB, ROP_FFT_INV,
-                              ROP_STORE_C, ROP_ENDLOOP>;
+                              ROP_STORE_CX, ROP_ENDLOOP>;
 using ProgPropIntensityT = OpList<ROP_SIDE_T, ROP_LOOP, ROP_LOAD_C, ROP_FFT_FWD, ROP_MUL_TAB, ROP_FFT_INV,
                                   ROP_ACC_ABS2U, ROP_ENDLOOP, ROP_STORE_ACC>;
-using ProgRealFwd = OpList<ROP_LOAD_R, ROP_FFT_FWD, ROP_STORE_C>;
+using ProgRealFwd = OpList<ROP_LOAD_R, ROP_FFT_FWD, ROP_STORE_CX>;
 using ProgFwdRe = OpList<ROP_LOAD_C, ROP_FFT_FWD, ROP_STORE_R>;
 using ProgSmearMid = OpList<ROP_LOAD_C, ROP_FFT_FWD, ROP_SAVE, ROP_LOOP, ROP_RESTORE, ROP_MUL_RTAB2D,
-                            ROP_FFT_INV, ROP_STORE_C, ROP_ENDLOOP>;
+                            ROP_FFT_INV, ROP_STORE_CX, ROP_ENDLOOP>;
 using ProgInvRe = OpList<ROP_LOAD_C, ROP_FFT_INV, ROP_STORE_R>;
 // the three smear passes carrying transposes of other data (RowSide)
-using ProgRealFwdT = OpList<ROP_SIDE_T, ROP_LOAD_R, ROP_FFT_FWD, ROP_STORE_C>;
+using ProgRealFwdT = OpList<ROP_SIDE_T, ROP_LOAD_R, ROP_FFT_FWD, ROP_STORE_CX>;
 using ProgSmearMidT = OpList<ROP_SIDE_T, ROP_LOAD_C, ROP_FFT_FWD, ROP_SAVE, ROP_LOOP, ROP_RESTORE, ROP_MUL_RTAB2D,
-                             ROP_FFT_INV, ROP_STORE_C, ROP_ENDLOOP>;
+                             ROP_FFT_INV, ROP_STORE_CX, ROP_ENDLOOP>;
 using ProgInvReT = OpList<ROP_SIDE_T, ROP_LOAD_C, ROP_FFT_INV, ROP_STORE_R>;
-using ProgVjpY = OpList<ROP_LOAD_C, ROP_FFT_FWD, ROP_MUL_TAB, ROP_FFT_INV, ROP_MUL_RLOAD, ROP_FFT_FWD,
-                        ROP_MUL_TAB, ROP_FFT_INV, ROP_STORE_C>;
+using ProgVjpY = OpList<ROP_LOAD_C, ROP_FFT_FWD, ROP_MUL_TAB, ROP_FFT_INV, ROP_MUL_RLOADX, ROP_FFT_FWD,
+                        ROP_MUL_TAB, ROP_FFT_INV, ROP_STORE_CX>;
 using ProgVjpX = OpList<ROP_LOAD_C, ROP_FFT_FWD, ROP_MUL_TAB, ROP_FFT_INV, ROP_GRAD_PHI, ROP_STORE_R,
                         ROP_DOT_R>;
 // the second propagation pass keeping the field A as the adjoint's
 // checkpoint beside |A|^2, and the adjoint's first pass starting from it
 using ProgPropField = OpList<ROP_LOAD_C, ROP_FFT_FWD, ROP_MUL_TAB, ROP_FFT_INV, ROP_STORE_C, ROP_ACC_ABS2U,
-                             ROP_STORE_ACC>;
-using ProgVjpYField = OpList<ROP_LOAD_C, ROP_MUL_RLOAD, ROP_FFT_FWD, ROP_MUL_TAB, ROP_FFT_INV, ROP_STORE_C>;
+                             ROP_STORE_ACCX>;
+using ProgVjpYField = OpList<ROP_LOAD_C, ROP_MUL_RLOADX, ROP_FFT_FWD, ROP_MUL_TAB, ROP_FFT_INV, ROP_STORE_CX>;
 // aperture mode: windowed, chirped exp(i s phi) -> DFT along the row; then
 // DFT along the other axis and |.|^2
-using ProgApertureX = OpList<ROP_LOAD_PHASE, ROP_MUL_TAB, ROP_MUL_ROWTAB, ROP_FFT_FWD, ROP_STORE_C>;
+using ProgApertureX = OpList<ROP_LOAD_PHASEX, ROP_MUL_TAB, ROP_MUL_ROWTAB, ROP_FFT_FWD, ROP_STORE_CX>;
 using ProgAbs2 = OpList<ROP_LOAD_C, ROP_FFT_FWD, ROP_ACC_ABS2, ROP_STORE_ACC>;
 
 }  // namespace scint

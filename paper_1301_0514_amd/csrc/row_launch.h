@@ -13,6 +13,7 @@ struct ProgNoiseSwapTag;
 struct ProgScreenTag;
 struct ProgScreenPropTag;
 struct ProgPhasePropTag;
+struct ProgPhasePropXTag;  // sizes of real_columns only
 struct ProgPropIntensityTag;
 struct ProgRealFwdTag;
 struct ProgFwdReTag;

@@ -13,6 +13,8 @@
 
 #include <stdint.h>
 
+#include "lds_layout.hpp"
+
 namespace scint {
 
 enum RowOpCode : int32_t {
@@ -46,7 +48,25 @@ enum RowOpCode : int32_t {
     ROP_SIDE_T,      // first op only: the launch also runs the transposes of RowProgram::side
     ROP_ACC_ABS2U,   // acc[e] += |v|^2, no weight (two fused multiply-adds per element)
     ROP_NOISE_SWAP,  // ROP_NOISE with row = ky, element = kx (screens made transposed)
+    // The same operations on an array that lies the other way round, at the
+    // sizes of stores_columns (complex) and real_columns (real): row and
+    // element change places (address ptr + b batch_stride + it iter_stride +
+    // e pitch + row; pitch N, or field_pitch for complex fields).  At other
+    // sizes the host transposes and these are the plain ones.
+    ROP_STORE_CX,     // ROP_STORE_C
+    ROP_LOAD_PHASEX,  // ROP_LOAD_PHASE
+    ROP_MUL_RLOADX,   // ROP_MUL_RLOAD
+    ROP_STORE_ACCX,   // ROP_STORE_ACC
 };
+
+// the operation an ...X code does, and whether it is one at size L
+constexpr int32_t rop_plain(int32_t c) {
+    return c == ROP_STORE_CX ? ROP_STORE_C : c == ROP_LOAD_PHASEX ? ROP_LOAD_PHASE
+         : c == ROP_MUL_RLOADX ? ROP_MUL_RLOAD : c == ROP_STORE_ACCX ? ROP_STORE_ACC : c;
+}
+constexpr bool lies_across(int32_t c, int L) {
+    return c != rop_plain(c) && (c == ROP_STORE_CX ? stores_columns(L) : real_columns(L));
+}
 
 // Flag bits
 enum : int32_t {

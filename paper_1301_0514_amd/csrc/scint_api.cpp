@@ -354,10 +354,11 @@ double row_bytes(const RowProgram &p, int n_ops, int dtype, bool algorithmic) {
     for (int i = 0; i < n_ops; ++i) {
         const RowOp &o = p.op[i];
         double b = 0.0;
-        switch (o.code) {
+        switch (rop_plain(o.code)) {
         case ROP_LOOP: in_loop = true; break;
         case ROP_ENDLOOP: in_loop = false; break;
-        case ROP_LOAD_C: case ROP_STORE_C: b = 2 * rb; break;
+        case ROP_LOAD_C: b = 2 * rb; break;
+        case ROP_STORE_C: b = o.ptr ? 2 * rb : 0.0; break;
         case ROP_LOAD_R: case ROP_LOAD_PHASE: case ROP_KEEP_R: case ROP_MUL_RLOAD: case ROP_MUL_RTAB2D:
         case ROP_GRAD_PHI: case ROP_DOT_R: b = rb; break;
         case ROP_STORE_R: b = o.ptr ? rb : 0.0; break;
@@ -380,7 +381,7 @@ double row_flops(const RowProgram &p, int n_ops) {
     bool in_loop = false;
     for (int i = 0; i < n_ops; ++i) {
         double f = 0.0;
-        switch (p.op[i].code) {
+        switch (rop_plain(p.op[i].code)) {
         case ROP_LOOP: in_loop = true; break;
         case ROP_ENDLOOP: in_loop = false; break;
         case ROP_FFT_FWD: case ROP_FFT_INV: f = 5.0 * log2n; break;
@@ -405,6 +406,7 @@ SCINT_PROG_NAME(ProgNoiseSwap)
 SCINT_PROG_NAME(ProgScreen)
 SCINT_PROG_NAME(ProgScreenProp)
 SCINT_PROG_NAME(ProgPhaseProp)
+SCINT_PROG_NAME(ProgPhasePropX)
 SCINT_PROG_NAME(ProgPropIntensity)
 SCINT_PROG_NAME(ProgRealFwd)
 SCINT_PROG_NAME(ProgFwdRe)
@@ -596,6 +598,22 @@ int transpose(const void *in, void *out, int N, int64_t nbatch, int elem_bytes, 
     return PS_OK;
 }
 
+// Complex fields between two passes along different axes (the buffers W1, W2
+// and the like below): N rows of field_row() elements, field_elems() in all.
+int64_t field_row(int N, int dtype) { return field_pitch(N, 2 * (int)real_bytes(dtype)); }
+int64_t field_elems(int N, int dtype) { return (int64_t)N * field_row(N, dtype); }
+size_t field_bytes(int N, int dtype) { return (size_t)field_elems(N, dtype) * 2 * real_bytes(dtype); }
+
+// The field `from` of a pass as the pass along the other axis takes it in
+// *next: `from` itself at the sizes that store it by columns, else its
+// transpose in `to`.
+int exchange(void *from, void *to, int N, int64_t nbatch, int dtype, void **next, hipStream_t stream) {
+    *next = from;
+    if (stores_columns(N)) return PS_OK;
+    *next = to;
+    return transpose(from, to, N, nbatch, 2 * (int)real_bytes(dtype), stream);
+}
+
 // Chirp tables H1(k)/N for n wavelengths with Fresnel radii rho[j] pixels.
 // amp (optional, one per wavelength) multiplies each table.
 int chirp_tables(void *tab, int N, const std::vector<double> &rho, int dtype, bool normalise, hipStream_t stream,
@@ -752,11 +770,12 @@ static SideCfg side_cfg() {
 // so the results do not depend on the split.  With swap the first pass runs
 // along kx instead (rows ky), so that the second pass makes the screens
 // transposed, [b][x][y].
+// *next is the buffer (W1 or W2) that the second pass reads (exchange()).
 int screen_passes(int N, double R, double beta, uint64_t seed, uint32_t r0, int nb, int dtype, void *W1, void *W2,
-                  hipStream_t stream, bool swap) {
+                  void **next, hipStream_t stream, bool swap) {
     const SideCfg sc = side_cfg();
-    const int J = (dtype == PS_F32 && N >= 2048 && sc.on) ? std::min(nb, sc.screen_jobs) : 1;
-    const size_t cbytes = (size_t)nn(N) * 2 * real_bytes(dtype);
+    const int J = (dtype == PS_F32 && N >= 2048 && sc.on && !stores_columns(N)) ? std::min(nb, sc.screen_jobs) : 1;
+    const size_t cbytes = field_bytes(N, dtype);
     const int64_t upm = (int64_t)transpose_units_x(N) * transpose_units_y(N);
     int prev0 = 0, prev_n = 0;  // realisations of the previous job
     for (int k = 0; k < J; ++k) {
@@ -766,7 +785,7 @@ int screen_passes(int N, double R, double beta, uint64_t seed, uint32_t r0, int 
         if (k > 0) a.op(ROP_SIDE_T);
         a.op(swap ? ROP_NOISE_SWAP : ROP_NOISE)
             .op(ROP_FFT_INV)
-            .op(ROP_STORE_C, static_cast<char *>(W1) + j0 * cbytes, nn(N), N);
+            .op(ROP_STORE_C, static_cast<char *>(W1) + j0 * cbytes, field_elems(N, dtype), field_row(N, dtype));
         if (k == 0) {
             const int rc = swap ? run_row<ProgNoiseSwapTag>(dtype, N, a.p, a.n, stream)
                                 : run_row<ProgNoiseTag>(dtype, N, a.p, a.n, stream);
@@ -786,36 +805,49 @@ int screen_passes(int N, double R, double beta, uint64_t seed, uint32_t r0, int 
         prev0 = j0;
         prev_n = jn;
     }
-    return transpose(static_cast<char *>(W1) + prev0 * cbytes, static_cast<char *>(W2) + prev0 * cbytes, N, prev_n,
-                     2 * (int)real_bytes(dtype), stream);
+    if (int rc = exchange(static_cast<char *>(W1) + prev0 * cbytes, static_cast<char *>(W2) + prev0 * cbytes, N, prev_n,
+                          dtype, next, stream))
+        return rc;
+    *next = static_cast<char *>(*next) - prev0 * cbytes;
+    return PS_OK;
 }
 
-// Second propagation pass of nb screens (rows x of the transposed field W2:
-// DFT along y, chirp, inverse DFT, |.|^2 into Iacc, transposed layout; for
-// screens made transposed, the same along x on rows y, natural layout).  With
-// F non-NULL the field A itself is kept there too, [b][x][y] complex, as the
-// adjoint's checkpoint.
-int prop_y_pass(int N, int dtype, int nb, const void *W2, const void *H, void *Iacc, void *F, hipStream_t stream) {
+// Second propagation pass of nb screens on the exchanged field W: DFT,
+// chirp, inverse DFT, |.|^2 into I, in the layout of the pass's own rows.
+int prop_pass(int N, int dtype, int nb, const void *W, const void *H, void *I, hipStream_t stream) {
     ProgBuilder d(N, (int64_t)nb * N);
-    if (F) {
-        d.op(ROP_LOAD_C, W2, nn(N), N)
-            .op(ROP_FFT_FWD)
-            .op(ROP_MUL_TAB, H)
-            .op(ROP_FFT_INV)
-            .op(ROP_STORE_C, F, nn(N), N)
-            .op(ROP_ACC_ABS2U)
-            .op(ROP_STORE_ACC, Iacc, nn(N), N);
-        return run_row<ProgPropFieldTag>(dtype, N, d.p, d.n, stream);
-    }
     d.op(ROP_LOOP)
-        .op(ROP_LOAD_C, W2, nn(N), N)
+        .op(ROP_LOAD_C, W, field_elems(N, dtype), field_row(N, dtype))
         .op(ROP_FFT_FWD)
         .op(ROP_MUL_TAB, H)
         .op(ROP_FFT_INV)
         .op(ROP_ACC_ABS2U)
         .op(ROP_ENDLOOP)
-        .op(ROP_STORE_ACC, Iacc, nn(N), N);
+        .op(ROP_STORE_ACC, I, nn(N), N);
     return run_row<ProgPropIntensityTag>(dtype, N, d.p, d.n, stream);
+}
+
+// The same along y on rows x, with the pattern in natural layout [b][y][x] in
+// I: written so at the sizes of real_columns, else transposed from T (scratch).
+// With F non-NULL the field A itself is kept there, [b][x][y] complex, as the
+// adjoint's checkpoint.
+int prop_y_pass(int N, int dtype, int nb, const void *W, const void *H, void *T, void *I, void *F,
+                hipStream_t stream) {
+    const bool natural = real_columns(N);
+    if (F || natural) {
+        ProgBuilder d(N, (int64_t)nb * N);
+        d.op(ROP_LOAD_C, W, field_elems(N, dtype), field_row(N, dtype))
+            .op(ROP_FFT_FWD)
+            .op(ROP_MUL_TAB, H)
+            .op(ROP_FFT_INV)
+            .op(ROP_STORE_C, F, nn(N), N)
+            .op(ROP_ACC_ABS2U)
+            .op(ROP_STORE_ACCX, natural ? I : T, nn(N), N);
+        if (int rc = run_row<ProgPropFieldTag>(dtype, N, d.p, d.n, stream)) return rc;
+    } else if (int rc = prop_pass(N, dtype, nb, W, H, T, stream)) {
+        return rc;
+    }
+    return natural ? PS_OK : transpose(T, I, N, nb, (int)real_bytes(dtype), stream);
 }
 
 // ------------------------------------------------------------ no-allocation path
@@ -998,7 +1030,7 @@ int ps_generate(int N, double delta, double r_diff, double beta, uint64_t seed, 
     if (!(std::isfinite(beta) && beta > 2.0 && beta < 4.0)) return fail(PS_E_PARAM, "beta must lie in (2, 4)");
     if (delta >= r_diff / 2.0) g_last_warning = "pixel side >= R_diff/2: the phase variations are undersampled";
     hipStream_t stream = static_cast<hipStream_t>(hip_stream);
-    const size_t cbytes = (size_t)nn(N) * 2 * real_bytes(dtype);
+    const size_t cbytes = field_bytes(N, dtype);
     const int nb_max = (int)std::max<size_t>(1, workspace_budget() / (2 * cbytes));
     for (int b0 = 0; b0 < n_real; b0 += nb_max) {
         const int nb = std::min(nb_max, n_real - b0);
@@ -1010,11 +1042,12 @@ int ps_generate(int N, double delta, double r_diff, double beta, uint64_t seed, 
         void *W1 = base + c.take(cbytes * nb);
         void *W2 = base + c.take(cbytes * nb);
         void *LT = base + c.take(low_mode_bytes(N, nb, dtype));
-        if (int rc = screen_passes(N, r_diff / delta, beta, seed, r0, nb, dtype, W1, W2, stream, false)) return rc;
+        void *S = nullptr;
+        if (int rc = screen_passes(N, r_diff / delta, beta, seed, r0, nb, dtype, W1, W2, &S, stream, false)) return rc;
         ProgBuilder b(N, (int64_t)nb * N);
         if (int rc = low_mode_pass(b.p, N, r_diff / delta, beta, seed, r0, nb, dtype, LT, stream, false)) return rc;
         char *phi = static_cast<char *>(phi_out) + (size_t)b0 * nn(N) * real_bytes(dtype);
-        b.op(ROP_LOAD_C, W2, nn(N), N).op(ROP_FFT_INV).op(ROP_SQRT2RE).op(ROP_STORE_R, phi, nn(N), N, 0, 0, 1.0);
+        b.op(ROP_LOAD_C, S, field_elems(N, dtype), field_row(N, dtype)).op(ROP_FFT_INV).op(ROP_SQRT2RE).op(ROP_STORE_R, phi, nn(N), N, 0, 0, 1.0);
         if (int rc = run_row<ProgScreenTag>(dtype, N, b.p, b.n, stream)) return rc;
     }
     return PS_OK;
@@ -1039,7 +1072,7 @@ int ps_screen_fresnel(int N, double delta, double r_diff, double beta, uint64_t 
     if (delta >= r_diff / 2.0) g_last_warning = "pixel side >= R_diff/2: the phase variations are undersampled";
     hipStream_t stream = static_cast<hipStream_t>(hip_stream);
     const double rho = std::sqrt(lambda * z / (2.0 * kPiD)) / delta;
-    const size_t cbytes = (size_t)nn(N) * 2 * real_bytes(dtype);
+    const size_t cbytes = field_bytes(N, dtype);
     const size_t tbytes = (size_t)N * 2 * real_bytes(dtype);
     const int nb_max = (int)std::max<size_t>(1, workspace_budget() / (2 * cbytes));
     for (int b0 = 0; b0 < n_real; b0 += nb_max) {
@@ -1062,11 +1095,13 @@ int ps_screen_fresnel(int N, double delta, double r_diff, double beta, uint64_t 
         // transpose.  With either returned, the natural order (screen rows y,
         // the field's checkpoint layout [b][x][y]).
         const bool swap = !phi_out && !field_out;
-        if (int rc = screen_passes(N, r_diff / delta, beta, seed, r0, nb, dtype, W1, W2, stream, swap)) return rc;
+        void *S = nullptr, *A = nullptr;
+        if (int rc = screen_passes(N, r_diff / delta, beta, seed, r0, nb, dtype, W1, W2, &S, stream, swap)) return rc;
+        void *X = S == W1 ? W2 : W1;  // the buffer that is free again
         char *phi = phi_out ? static_cast<char *>(phi_out) + (size_t)b0 * nn(N) * real_bytes(dtype) : nullptr;
         ProgBuilder b(N, (int64_t)nb * N);
         if (int rc = low_mode_pass(b.p, N, r_diff / delta, beta, seed, r0, nb, dtype, LT, stream, swap)) return rc;
-        b.op(ROP_LOAD_C, W2, nn(N), N)
+        b.op(ROP_LOAD_C, S, field_elems(N, dtype), field_row(N, dtype))
             .op(ROP_FFT_INV)
             .op(ROP_SQRT2RE)
             .op(ROP_STORE_R, phi, nn(N), N, 0, 0, 1.0)
@@ -1074,46 +1109,49 @@ int ps_screen_fresnel(int N, double delta, double r_diff, double beta, uint64_t 
             .op(ROP_FFT_FWD)
             .op(ROP_MUL_TAB, H)
             .op(ROP_FFT_INV)
-            .op(ROP_STORE_C, W1, nn(N), N);
+            .op(ROP_STORE_C, X, field_elems(N, dtype), field_row(N, dtype));
         if (int rc = run_row<ProgScreenPropTag>(dtype, N, b.p, b.n, stream)) return rc;
-        if (int rc = transpose(W1, W2, N, nb, 2 * (int)real_bytes(dtype), stream)) return rc;
-        char *F = field_out ? static_cast<char *>(field_out) + (size_t)b0 * cbytes : nullptr;
+        if (int rc = exchange(X, S, N, nb, dtype, &A, stream)) return rc;
+        char *F = field_out ? static_cast<char *>(field_out) + (size_t)b0 * nn(N) * 2 * real_bytes(dtype) : nullptr;
         char *I = static_cast<char *>(I_out) + (size_t)b0 * nn(N) * real_bytes(dtype);
-        if (swap) {
-            if (int rc = prop_y_pass(N, dtype, nb, W2, H, I, nullptr, stream)) return rc;
-            continue;
-        }
-        if (int rc = prop_y_pass(N, dtype, nb, W2, H, W1, F, stream)) return rc;
-        if (int rc = transpose(W1, I, N, nb, (int)real_bytes(dtype), stream)) return rc;
+        const int rc = swap ? prop_pass(N, dtype, nb, A, H, I, stream)
+                            : prop_y_pass(N, dtype, nb, A, H, A == X ? S : X, I, F, stream);
+        if (rc) return rc;
     }
     return PS_OK;
 }
 
 // Propagation of nb screens for a chunk of wavelengths: intensities summed
 // with the given weights into Iacc (transposed layout [b][x][y]); add != 0
-// accumulates onto Iacc.
+// accumulates onto Iacc.  One wavelength at the sizes of real_columns
+// (natural): the screens are read by columns, so that the second pass runs
+// along x and writes the pattern as it lies.
 static int poly_chunk(int N, const void *phi, int nb, const std::vector<double> &rho,
                       const std::vector<double> &scale, const std::vector<double> &weight, int dtype, void *W1,
-                      void *W2, void *H, void *Iacc, bool add, hipStream_t stream) {
+                      void *W2, void *H, void *Iacc, bool natural, bool add, int iter_split, hipStream_t stream) {
     const int C = (int)rho.size();
     const std::vector<double> amp = weight_amps(weight, 0, C);
     if (int rc = chirp_tables(H, N, rho, dtype, true, stream, &amp)) return rc;
     ProgBuilder a(N, (int64_t)nb * N);
     a.p.n_iter = C;
+    a.p.iter_split = iter_split;
     for (int j = 0; j < C; ++j) a.p.scale[j] = scale[j];
     a.op(ROP_LOOP)
-        .op(ROP_LOAD_PHASE, phi, nn(N), N, 0, RF_ITER_SCALE)
+        .op(natural ? ROP_LOAD_PHASEX : ROP_LOAD_PHASE, phi, nn(N), N, 0, RF_ITER_SCALE)
         .op(ROP_FFT_FWD)
         .op(ROP_MUL_TAB, H, 0, 0, N)
         .op(ROP_FFT_INV)
-        .op(ROP_STORE_C, W1, nn(N), N, (int64_t)nb * nn(N))
+        .op(ROP_STORE_C, W1, field_elems(N, dtype), field_row(N, dtype), (int64_t)nb * field_elems(N, dtype))
         .op(ROP_ENDLOOP);
-    if (int rc = run_row<ProgPhasePropTag>(dtype, N, a.p, a.n, stream)) return rc;
-    if (int rc = transpose(W1, W2, N, (int64_t)nb * C, 2 * (int)real_bytes(dtype), stream)) return rc;
+    if (int rc = natural ? run_row<ProgPhasePropXTag>(dtype, N, a.p, a.n, stream)
+                         : run_row<ProgPhasePropTag>(dtype, N, a.p, a.n, stream))
+        return rc;
+    void *A = nullptr;
+    if (int rc = exchange(W1, W2, N, (int64_t)nb * C, dtype, &A, stream)) return rc;
     ProgBuilder b(N, (int64_t)nb * N);
     b.p.n_iter = C;
     b.op(ROP_LOOP)
-        .op(ROP_LOAD_C, W2, nn(N), N, (int64_t)nb * nn(N))
+        .op(ROP_LOAD_C, A, field_elems(N, dtype), field_row(N, dtype), (int64_t)nb * field_elems(N, dtype))
         .op(ROP_FFT_FWD)
         .op(ROP_MUL_TAB, H, 0, 0, N)
         .op(ROP_FFT_INV)
@@ -1121,6 +1159,12 @@ static int poly_chunk(int N, const void *phi, int nb, const std::vector<double> 
         .op(ROP_ENDLOOP)
         .op(ROP_STORE_ACC, Iacc, nn(N), N, 0, add ? RF_ADD : 0);
     return run_row<ProgPropIntensityTag>(dtype, N, b.p, b.n, stream);
+}
+
+// Workgroups per row group of a first pass over C wavelengths at the smaller
+// sizes: more where the rows alone leave the chip idle.
+static int rows_iter_split(int64_t rows, int C) {
+    return (int)std::max<int64_t>(1, std::min<int64_t>(C, 4096 / std::max<int64_t>(rows, 1)));
 }
 
 // One job of the polychromatic propagation: nb realisations from b0, m
@@ -1276,14 +1320,15 @@ int fresnel_propagate(int N, double delta, double lambda, double z, const void *
     // FP32 from 2048 up with two or more realisations: the pipelined form
     // (one wavelength of phase scale s and weight 1)
     const SideCfg sc = side_cfg();
-    if (dtype == PS_F32 && N >= 2048 && n >= 2 && sc.on) {
+    const bool cols = stores_columns(N), natural = real_columns(N);
+    if (dtype == PS_F32 && N >= 2048 && n >= 2 && sc.on && !cols) {
         std::vector<PolyJob> jobs;
         int Cp = 0, nbp = 0;
         if (plan_poly_jobs(N, n, 1, workspace_budget(), &jobs, &Cp, &nbp))
             return poly_pipelined(N, static_cast<const char *>(phi), jobs, Cp, nbp, 1, {rho}, {phase_scale}, {1.0},
                                   I_out, sc, stream);
     }
-    const size_t cbytes = (size_t)nn(N) * 2 * real_bytes(dtype);
+    const size_t cbytes = field_bytes(N, dtype);
     const size_t tbytes = (size_t)N * 2 * real_bytes(dtype);
     const int nb_max = (int)std::max<size_t>(1, workspace_budget() / (2 * cbytes));
     for (int b0 = 0; b0 < n; b0 += nb_max) {
@@ -1296,12 +1341,15 @@ int fresnel_propagate(int N, double delta, double lambda, double z, const void *
         void *W2 = base + c.take(cbytes * nb);
         void *H = base + c.take(tbytes);
         const char *ph = static_cast<const char *>(phi) + (size_t)b0 * nn(N) * real_bytes(dtype);
-        // W1 (complex) is free again once transposed into W2, so it holds the
-        // transposed intensity
-        if (int rc = poly_chunk(N, ph, nb, {rho}, {phase_scale}, {1.0}, dtype, W1, W2, H, W1, false, stream))
-            return rc;
         char *I = static_cast<char *>(I_out) + (size_t)b0 * nn(N) * real_bytes(dtype);
-        if (int rc = transpose(W1, I, N, nb, (int)real_bytes(dtype), stream)) return rc;
+        // the transposed intensity goes to the buffer that is free then: W1
+        // once it is transposed into W2, or W2 where nothing is
+        void *It = cols ? W2 : W1;
+        if (int rc = poly_chunk(N, ph, nb, {rho}, {phase_scale}, {1.0}, dtype, W1, W2, H, natural ? (void *)I : It, natural,
+                                false, 1, stream))
+            return rc;
+        if (!natural)
+            if (int rc = transpose(It, I, N, nb, (int)real_bytes(dtype), stream)) return rc;
     }
     return PS_OK;
 }
@@ -1341,28 +1389,35 @@ int fresnel_propagate_noalloc(int N, double delta, double lambda, double z, cons
     const double a = kPiD * rho * rho / ((double)N * (double)N);
     HIP_TRY(launch_chirp_tables(H, N, &a, 1, 1.0 / N, f64, stream));
     // x pass: exp(i s phi), DFT, chirp, inverse DFT; transpose; y pass:
-    // DFT, chirp, inverse DFT, |.|^2 (into W1, transposed); transpose to I_out
+    // DFT, chirp, inverse DFT, |.|^2 (transposed); transpose to I_out.  Sizes
+    // that store by columns need no transpose of the field, and those of
+    // real_columns none of the pattern.
+    const bool cols = stores_columns(N), natural = real_columns(N);
+    if (cols) W2 = W1 + (field_bytes(N, dtype) * n + 255) / 256 * 256;  // (within the two fields counted above)
+    char *It = natural ? static_cast<char *>(I_out) : cols ? W2 : W1;
     ProgBuilder x(N, (int64_t)n * N);
     x.op(ROP_LOOP)
-        .op(ROP_LOAD_PHASE, phi, nn(N), N, 0, 0, phase_scale)
+        .op(natural ? ROP_LOAD_PHASEX : ROP_LOAD_PHASE, phi, nn(N), N, 0, 0, phase_scale)
         .op(ROP_FFT_FWD)
         .op(ROP_MUL_TAB, H)
         .op(ROP_FFT_INV)
-        .op(ROP_STORE_C, W1, nn(N), N)
+        .op(ROP_STORE_C, W1, field_elems(N, dtype), field_row(N, dtype))
         .op(ROP_ENDLOOP);
-    if (int rc = launch_row_plan0<ProgPhasePropTag>(dtype, N, x.p, TW, stream)) return rc;
-    HIP_TRY(launch_transpose(W1, W2, N, n, (int)cb, stream));
+    if (int rc = natural ? launch_row_plan0<ProgPhasePropXTag>(dtype, N, x.p, TW, stream)
+                         : launch_row_plan0<ProgPhasePropTag>(dtype, N, x.p, TW, stream))
+        return rc;
+    if (!cols) HIP_TRY(launch_transpose(W1, W2, N, n, (int)cb, stream));
     ProgBuilder y(N, (int64_t)n * N);
     y.op(ROP_LOOP)
-        .op(ROP_LOAD_C, W2, nn(N), N)
+        .op(ROP_LOAD_C, cols ? W1 : W2, field_elems(N, dtype), field_row(N, dtype))
         .op(ROP_FFT_FWD)
         .op(ROP_MUL_TAB, H)
         .op(ROP_FFT_INV)
         .op(ROP_ACC_ABS2U)
         .op(ROP_ENDLOOP)
-        .op(ROP_STORE_ACC, W1, nn(N), N);
+        .op(ROP_STORE_ACC, It, nn(N), N);
     if (int rc = launch_row_plan0<ProgPropIntensityTag>(dtype, N, y.p, TW, stream)) return rc;
-    HIP_TRY(launch_transpose(W1, I_out, N, n, (int)rb, stream));
+    if (!natural) HIP_TRY(launch_transpose(It, I_out, N, n, (int)rb, stream));
     return PS_OK;
 }
 
@@ -1382,7 +1437,7 @@ int fresnel_propagate_field(int N, double delta, double lambda, double z, const 
         return fail(PS_E_ALIAS, "field_out overlaps phi or I_out");
     hipStream_t stream = static_cast<hipStream_t>(hip_stream);
     const double rho = std::sqrt(lambda * z / (2.0 * kPiD)) / delta;
-    const size_t cbytes = (size_t)nn(N) * 2 * real_bytes(dtype);
+    const size_t cbytes = field_bytes(N, dtype);
     const size_t tbytes = (size_t)N * 2 * real_bytes(dtype);
     const int nb_max = (int)std::max<size_t>(1, workspace_budget() / (2 * cbytes));
     for (int b0 = 0; b0 < n; b0 += nb_max) {
@@ -1402,14 +1457,14 @@ int fresnel_propagate_field(int N, double delta, double lambda, double z, const 
             .op(ROP_FFT_FWD)
             .op(ROP_MUL_TAB, H)
             .op(ROP_FFT_INV)
-            .op(ROP_STORE_C, W1, nn(N), N)
+            .op(ROP_STORE_C, W1, field_elems(N, dtype), field_row(N, dtype))
             .op(ROP_ENDLOOP);
         if (int rc = run_row<ProgPhasePropTag>(dtype, N, a.p, a.n, stream)) return rc;
-        if (int rc = transpose(W1, W2, N, nb, 2 * (int)real_bytes(dtype), stream)) return rc;
-        char *F = static_cast<char *>(field_out) + (size_t)b0 * cbytes;
-        if (int rc = prop_y_pass(N, dtype, nb, W2, H, W1, F, stream)) return rc;
+        void *A = nullptr;
+        if (int rc = exchange(W1, W2, N, nb, dtype, &A, stream)) return rc;
+        char *F = static_cast<char *>(field_out) + (size_t)b0 * nn(N) * 2 * real_bytes(dtype);
         char *I = static_cast<char *>(I_out) + (size_t)b0 * nn(N) * real_bytes(dtype);
-        if (int rc = transpose(W1, I, N, nb, (int)real_bytes(dtype), stream)) return rc;
+        if (int rc = prop_y_pass(N, dtype, nb, A, H, A == W1 ? W2 : W1, I, F, stream)) return rc;
     }
     return PS_OK;
 }
@@ -1434,7 +1489,7 @@ int fresnel_aperture(int N, double delta, double lambda, double z, const void *p
     const size_t rbytes = (size_t)nn(N) * real_bytes(dtype) * n;
     if (overlaps(phi, rbytes, I_out, rbytes)) return fail(PS_E_ALIAS, "I_out overlaps phi");
     hipStream_t stream = static_cast<hipStream_t>(hip_stream);
-    const size_t cbytes = (size_t)nn(N) * 2 * real_bytes(dtype);
+    const size_t cbytes = field_bytes(N, dtype);
     const size_t tbytes = (size_t)N * 2 * real_bytes(dtype);
     const int nb_max = (int)std::max<size_t>(1, workspace_budget() / (2 * cbytes));
     const double norm = 1.0 / (two_pi_rho2 * two_pi_rho2);
@@ -1449,24 +1504,31 @@ int fresnel_aperture(int N, double delta, double lambda, double z, const void *p
         void *A = base + c.take(tbytes);
         HIP_TRY(launch_aperture_table(A, N, 1.0 / (4.0 * kPiD * rho * rho), Lm, dtype == PS_F64, stream));
         const char *ph = static_cast<const char *>(phi) + (size_t)b0 * nn(N) * real_bytes(dtype);
-        // rows y: G = A[x] A[y] exp(i s phi), DFT along x
+        // rows y: G = A[x] A[y] exp(i s phi), DFT along x (sizes of
+        // real_columns: the columns x of phi, DFT along y; the second pass
+        // then runs along x and writes the pattern as it lies)
         ProgBuilder a(N, (int64_t)nb * N);
-        a.op(ROP_LOAD_PHASE, ph, nn(N), N, 0, 0, phase_scale)
+        a.op(ROP_LOAD_PHASEX, ph, nn(N), N, 0, 0, phase_scale)
             .op(ROP_MUL_TAB, A)
             .op(ROP_MUL_ROWTAB, A)
             .op(ROP_FFT_FWD)
-            .op(ROP_STORE_C, W1, nn(N), N);
+            .op(ROP_STORE_C, W1, field_elems(N, dtype), field_row(N, dtype));
         if (int rc = run_row<ProgApertureXTag>(dtype, N, a.p, a.n, stream)) return rc;
-        if (int rc = transpose(W1, W2, N, nb, 2 * (int)real_bytes(dtype), stream)) return rc;
-        // rows kx: DFT along y, |.|^2 / (2 pi rho^2)^2 (transposed intensity in W1)
+        void *G = nullptr;
+        if (int rc = exchange(W1, W2, N, nb, dtype, &G, stream)) return rc;
+        // rows kx: DFT along y, |.|^2 / (2 pi rho^2)^2 (transposed intensity in
+        // the buffer that is free)
+        char *I = static_cast<char *>(I_out) + (size_t)b0 * nn(N) * real_bytes(dtype);
+        const bool natural = real_columns(N);
+        void *It = natural ? (void *)I : G == W1 ? W2 : W1;
         ProgBuilder d(N, (int64_t)nb * N);
-        d.op(ROP_LOAD_C, W2, nn(N), N)
+        d.op(ROP_LOAD_C, G, field_elems(N, dtype), field_row(N, dtype))
             .op(ROP_FFT_FWD)
             .op(ROP_ACC_ABS2, nullptr, 0, 0, 0, 0, norm)
-            .op(ROP_STORE_ACC, W1, nn(N), N);
+            .op(ROP_STORE_ACC, It, nn(N), N);
         if (int rc = run_row<ProgAbs2Tag>(dtype, N, d.p, d.n, stream)) return rc;
-        char *I = static_cast<char *>(I_out) + (size_t)b0 * nn(N) * real_bytes(dtype);
-        if (int rc = transpose(W1, I, N, nb, (int)real_bytes(dtype), stream)) return rc;
+        if (!natural)
+            if (int rc = transpose(It, I, N, nb, (int)real_bytes(dtype), stream)) return rc;
     }
     return PS_OK;
 }
@@ -1550,23 +1612,28 @@ int illumination_polychromatic(int N, double delta, double z, const void *phi_re
         scale[j] = lambda_ref / lambdas[j];
         weight[j] = (weights ? weights[j] : 1.0) / wsum;
     }
-    const size_t cbytes = (size_t)nn(N) * 2 * real_bytes(dtype);
+    const size_t cbytes = field_bytes(N, dtype);
     const size_t rb1 = (size_t)nn(N) * real_bytes(dtype);
     const SideCfg sc = side_cfg();
     const PolyPlan pl = plan_polychromatic(N, n_real, n_lambda, dtype, workspace_budget(), sc);
-    if (pl.pipelined)
+    const bool cols = stores_columns(N), natural = real_columns(N) && n_lambda == 1;
+    if (pl.pipelined && !cols)
         return poly_pipelined(N, static_cast<const char *>(phi_ref), pl.jobs, pl.C, pl.nb, n_lambda, rho, scale, weight,
                               I_out, sc, stream);
+    // (sizes that store by columns: the same jobs, one after the other, with no
+    // transposes to carry and one field buffer)
     const int C = pl.C, nb_max = pl.nb;
     for (int b0 = 0; b0 < n_real; b0 += nb_max) {
         const int nb = std::min(nb_max, n_real - b0);
+        char *I = static_cast<char *>(I_out) + (size_t)b0 * rb1;
         void *ws = nullptr;
         const size_t tbytes = (size_t)C * N * 2 * real_bytes(dtype);
-        if (int rc = get_workspace(stream, 2 * cbytes * (size_t)C * nb + rb1 * nb + tbytes + 2048, &ws)) return rc;
+        const size_t wbytes = cbytes * (size_t)C * nb;
+        if (int rc = get_workspace(stream, (cols ? 1 : 2) * wbytes + rb1 * nb + tbytes + 2048, &ws)) return rc;
         Carver c;
         char *base = static_cast<char *>(ws);
-        void *W1 = base + c.take(cbytes * (size_t)C * nb);
-        void *W2 = base + c.take(cbytes * (size_t)C * nb);
+        void *W1 = base + c.take(wbytes);
+        void *W2 = cols ? nullptr : base + c.take(wbytes);
         void *Iacc = base + c.take(rb1 * nb);
         void *H = base + c.take(tbytes);
         const char *ph = static_cast<const char *>(phi_ref) + (size_t)b0 * rb1;
@@ -1575,10 +1642,13 @@ int illumination_polychromatic(int N, double delta, double z, const void *phi_re
             std::vector<double> r(rho.begin() + j0, rho.begin() + j0 + m);
             std::vector<double> s(scale.begin() + j0, scale.begin() + j0 + m);
             std::vector<double> w(weight.begin() + j0, weight.begin() + j0 + m);
-            if (int rc = poly_chunk(N, ph, nb, r, s, w, dtype, W1, W2, H, Iacc, j0 > 0, stream)) return rc;
+            const int split = cols && sc.iter_split > 1 ? rows_iter_split((int64_t)nb * N, m) : 1;
+            if (int rc = poly_chunk(N, ph, nb, r, s, w, dtype, W1, W2, H, natural ? (void *)I : Iacc, natural, j0 > 0, split,
+                                    stream))
+                return rc;
         }
-        char *I = static_cast<char *>(I_out) + (size_t)b0 * rb1;
-        if (int rc = transpose(Iacc, I, N, nb, (int)real_bytes(dtype), stream)) return rc;
+        if (!natural)
+            if (int rc = transpose(Iacc, I, N, nb, (int)real_bytes(dtype), stream)) return rc;
     }
     return PS_OK;
 }
@@ -1627,7 +1697,7 @@ static int get_disk_spectra(int N, const std::vector<double> &Rpx, int dtype, hi
     }
     if (int rc = refuse_in_capture(stream, "building the disk spectra of these radii")) return rc;
     const size_t rb = (size_t)nn(N) * real_bytes(dtype);
-    const size_t cb = 2 * rb;
+    const size_t cb = field_bytes(N, dtype);
     const size_t qb = disk_quarter_elems(N) * real_bytes(dtype);
     void *block = nullptr;
     if (hipMalloc(&block, qb * Rpx.size()) != hipSuccess) return fail(PS_E_ALLOC, "hipMalloc of disk spectra failed");
@@ -1654,13 +1724,14 @@ static int get_disk_spectra(int N, const std::vector<double> &Rpx, int dtype, hi
         if (e != hipSuccess) rc = fail(PS_E_DEVICE, std::string("disk image: ") + hipGetErrorString(e));
         if (!rc) {
             ProgBuilder a(N, N);
-            a.op(ROP_LOAD_R, tab, 0, N).op(ROP_FFT_FWD).op(ROP_STORE_C, W1, 0, N);
+            a.op(ROP_LOAD_R, tab, 0, N).op(ROP_FFT_FWD).op(ROP_STORE_C, W1, 0, field_row(N, dtype));
             rc = run_row<ProgRealFwdTag>(dtype, N, a.p, a.n, stream);
         }
-        if (!rc) rc = transpose(W1, W2, N, 1, 2 * (int)real_bytes(dtype), stream);
+        void *F = nullptr;
+        if (!rc) rc = exchange(W1, W2, N, 1, dtype, &F, stream);
         if (!rc) {
             ProgBuilder b(N, N);
-            b.op(ROP_LOAD_C, W2, 0, N).op(ROP_FFT_FWD).op(ROP_STORE_R, tab, 0, N, 0, 0, 1.0 / (double)nn(N));
+            b.op(ROP_LOAD_C, F, 0, field_row(N, dtype)).op(ROP_FFT_FWD).op(ROP_STORE_R, tab, 0, N, 0, 0, 1.0 / (double)nn(N));
             rc = run_row<ProgFwdReTag>(dtype, N, b.p, b.n, stream);
         }
         if (!rc) {
@@ -1693,6 +1764,7 @@ static int get_disk_spectra(int N, const std::vector<double> &Rpx, int dtype, hi
 // the middle pass (y forward, times each disk spectrum, y inverse), and per
 // radius the inverse x pass to real patterns.
 struct SmearJob {
+    int64_t fe, fr;  // elements of a complex field and of its rows
     const char *Iin;
     char *Iout;
     int np, step;
@@ -1712,31 +1784,31 @@ static ProgBuilder smear_rf_prog(int N, const SmearJob &j, size_t rb1, bool side
     a.op(ROP_LOAD_R, j.Iin, (int64_t)j.step * nn(N), N, 0, pair ? RF_PAIR : 0, 0.0,
          pair ? const_cast<char *>(j.Iin) + rb1 : nullptr)
         .op(ROP_FFT_FWD)
-        .op(ROP_STORE_C, j.W1, nn(N), N);
+        .op(ROP_STORE_C, j.W1, j.fe, j.fr);
     return a;
 }
 static ProgBuilder smear_mid_prog(int N, const SmearJob &j, const void *D, int n_r, bool side) {
     ProgBuilder b(N, (int64_t)j.np * N);
     b.p.n_iter = n_r;
     if (side) b.op(ROP_SIDE_T);
-    b.op(ROP_LOAD_C, j.W2, nn(N), N)
+    b.op(ROP_LOAD_C, j.W2, j.fe, j.fr)
         .op(ROP_FFT_FWD)
         .op(ROP_SAVE)
         .op(ROP_LOOP)
         .op(ROP_RESTORE)
         .op(ROP_MUL_RTAB2D, D, 0, N / 2 + 1, disk_quarter_elems(N))
         .op(ROP_FFT_INV)
-        .op(ROP_STORE_C, j.V1, (int64_t)n_r * nn(N), N, nn(N))
+        .op(ROP_STORE_C, j.V1, (int64_t)n_r * j.fe, j.fr, j.fe)
         .op(ROP_ENDLOOP);
     return b;
 }
 static ProgBuilder smear_ir_prog(int N, const SmearJob &j, int r, int n_r, size_t rb1, bool side) {
     const bool pair = j.step == 2;
-    const size_t cbytes = 2 * rb1;
+    const size_t cbytes = (size_t)j.fe * 2 * (rb1 / nn(N));
     ProgBuilder d(N, (int64_t)j.np * N);
     char *dst = j.Iout + (size_t)r * rb1;
     if (side) d.op(ROP_SIDE_T);
-    d.op(ROP_LOAD_C, j.V2 + (size_t)r * cbytes, (int64_t)n_r * nn(N), N)
+    d.op(ROP_LOAD_C, j.V2 + (size_t)r * cbytes, (int64_t)n_r * j.fe, j.fr)
         .op(ROP_FFT_INV)
         .op(ROP_STORE_R, dst, (int64_t)j.step * n_r * nn(N), N, 0, pair ? RF_PAIR : 0, 1.0,
             pair ? dst + (size_t)n_r * rb1 : nullptr);
@@ -1804,7 +1876,8 @@ int source_smear(int N, double delta, const void *I_in, const double *radii, int
     for (int j = 0; j < n_r; ++j) rpx[j] = radii[j] / delta;
     const void *D = nullptr;
     if (int rc = get_disk_spectra(N, rpx, dtype, stream, &D)) return rc;
-    const size_t cbytes = 2 * rb1;
+    const size_t cbytes = field_bytes(N, dtype);
+    const int64_t fe = field_elems(N, dtype), fr = field_row(N, dtype);
     const size_t budget = workspace_budget();
     const int nb_max = (int)std::max<size_t>(1, budget / (cbytes * (2 + 2 * (size_t)n_r)));
     // The disk kernel is real, so two real patterns a and b ride in one
@@ -1828,13 +1901,14 @@ int source_smear(int N, double delta, const void *I_in, const double *radii, int
             const char *Iin = static_cast<const char *>(I_in) + (size_t)(b0 + pb) * rb1;
             // I_out[b][r]: transform q holds realisations b0 + pb + step q (and + 1)
             char *Iout = static_cast<char *>(I_out) + (size_t)(b0 + pb) * n_r * rb1;
-            SmearJob all{Iin, Iout, np, step, W1, W2, V1, V2};
-            if (dtype == PS_F32 && N >= 2048 && np >= 2 && sc.on) {
+            const bool cols = stores_columns(N);
+            SmearJob all{fe, fr, Iin, Iout, np, step, W1, cols ? W1 : W2, V1, cols ? V1 : V2};
+            if (dtype == PS_F32 && N >= 2048 && np >= 2 && sc.on && !cols) {
                 // two jobs, the transposes of each riding on the other's passes
                 const int q0 = (np + 1) / 2;
-                const SmearJob j0{Iin, Iout, q0, step, W1, W2, V1, V2};
+                const SmearJob j0{fe, fr, Iin, Iout, q0, step, W1, W2, V1, V2};
                 const size_t o = (size_t)q0 * cbytes;  // offset of job 1 in the complex buffers
-                const SmearJob j1{Iin + (size_t)q0 * step * rb1, Iout + (size_t)q0 * step * n_r * rb1, np - q0, step,
+                const SmearJob j1{fe, fr, Iin + (size_t)q0 * step * rb1, Iout + (size_t)q0 * step * n_r * rb1, np - q0, step,
                                   W1 + o, W2 + o, V1 + o * n_r, V2 + o * n_r};
                 const int64_t upm = (int64_t)transpose_units_x(N) * transpose_units_y(N);
                 const SmearSide t1_0{j0.W1, j0.W2, 0, upm * j0.np}, t1_1{j1.W1, j1.W2, 0, upm * j1.np};
@@ -1852,9 +1926,11 @@ int source_smear(int N, double delta, const void *I_in, const double *radii, int
                     if (int rc = smear_ir(N, j1, r, n_r, nullptr, sc, stream)) return rc;
             } else {
                 if (int rc = smear_rf_any(N, dtype, all, stream)) return rc;
-                if (int rc = transpose(W1, W2, N, np, (int)(cbytes / nn(N)), stream)) return rc;
+                if (!cols)
+                    if (int rc = transpose(W1, W2, N, np, 2 * (int)real_bytes(dtype), stream)) return rc;
                 if (int rc = smear_mid_any(N, dtype, all, D, n_r, stream)) return rc;
-                if (int rc = transpose(V1, V2, N, (int64_t)np * n_r, (int)(cbytes / nn(N)), stream)) return rc;
+                if (!cols)
+                    if (int rc = transpose(V1, V2, N, (int64_t)np * n_r, 2 * (int)real_bytes(dtype), stream)) return rc;
                 for (int r = 0; r < n_r; ++r)
                     if (int rc = smear_ir_any(N, dtype, all, r, n_r, stream)) return rc;
             }
@@ -1883,7 +1959,7 @@ int fresnel_propagate_vjp(int N, double delta, double lambda, double z, const vo
     if (phi_dot_grad_out)
         if (int rc = refuse_in_capture(stream, "returning phi_dot_grad_out to the host")) return rc;
     const double rho = std::sqrt(lambda * z / (2.0 * kPiD)) / delta;
-    const size_t cbytes = 2 * rb1;
+    const size_t cbytes = field_bytes(N, dtype);
     const size_t tbytes = (size_t)N * 2 * real_bytes(dtype);
     const int nb_max = (int)std::max<size_t>(1, workspace_budget() / (2 * cbytes + rb1 + N * 8));
     std::vector<double> dots(n, 0.0);
@@ -1904,16 +1980,20 @@ int fresnel_propagate_vjp(int N, double delta, double lambda, double z, const vo
         if (int rc = chirp_tables(H, N, {rho}, dtype, true, stream)) return rc;
         const char *ph = static_cast<const char *>(phi) + (size_t)b0 * rb1;
         const char *gI = static_cast<const char *>(grad_I) + (size_t)b0 * rb1;
-        if (int rc = transpose(gI, Gt, N, nb, (int)real_bytes(dtype), stream)) return rc;
+        const bool across = real_columns(N);  // grad_I read by columns
+        const void *gt = across ? gI : Gt;
+        if (!across)
+            if (int rc = transpose(gI, Gt, N, nb, (int)real_bytes(dtype), stream)) return rc;
+        void *A = nullptr, *X = W1;  // X: the adjoint field after its first pass
         if (field) {
             // from the checkpoint: g_A = 2 grad_I A, adjoint y-propagation
             ProgBuilder b(N, (int64_t)nb * N);
-            b.op(ROP_LOAD_C, static_cast<const char *>(field) + (size_t)b0 * cbytes, nn(N), N)
-                .op(ROP_MUL_RLOAD, Gt, nn(N), N, 0, 0, 2.0)
+            b.op(ROP_LOAD_C, static_cast<const char *>(field) + (size_t)b0 * 2 * rb1, nn(N), N)
+                .op(ROP_MUL_RLOADX, gt, nn(N), N, 0, 0, 2.0)
                 .op(ROP_FFT_FWD)
                 .op(ROP_MUL_TAB, H, 0, 0, 0, RF_CONJ)
                 .op(ROP_FFT_INV)
-                .op(ROP_STORE_C, W1, nn(N), N);
+                .op(ROP_STORE_C, X, field_elems(N, dtype), field_row(N, dtype));
             if (int rc = run_row<ProgVjpYFieldTag>(dtype, N, b.p, b.n, stream)) return rc;
         } else {
             // forward x-propagation (recomputed from phi)
@@ -1923,28 +2003,30 @@ int fresnel_propagate_vjp(int N, double delta, double lambda, double z, const vo
                 .op(ROP_FFT_FWD)
                 .op(ROP_MUL_TAB, H)
                 .op(ROP_FFT_INV)
-                .op(ROP_STORE_C, W1, nn(N), N)
+                .op(ROP_STORE_C, W1, field_elems(N, dtype), field_row(N, dtype))
                 .op(ROP_ENDLOOP);
             if (int rc = run_row<ProgPhasePropTag>(dtype, N, a.p, a.n, stream)) return rc;
-            if (int rc = transpose(W1, W2, N, nb, (int)(cbytes / nn(N)), stream)) return rc;
+            if (int rc = exchange(W1, W2, N, nb, dtype, &A, stream)) return rc;
+            X = A == W1 ? W2 : W1;
             // y-propagation to A (transposed), g_A = 2 grad_I A, adjoint y-propagation
             ProgBuilder b(N, (int64_t)nb * N);
-            b.op(ROP_LOAD_C, W2, nn(N), N)
+            b.op(ROP_LOAD_C, A, field_elems(N, dtype), field_row(N, dtype))
                 .op(ROP_FFT_FWD)
                 .op(ROP_MUL_TAB, H)
                 .op(ROP_FFT_INV)
-                .op(ROP_MUL_RLOAD, Gt, nn(N), N, 0, 0, 2.0)
+                .op(ROP_MUL_RLOADX, gt, nn(N), N, 0, 0, 2.0)
                 .op(ROP_FFT_FWD)
                 .op(ROP_MUL_TAB, H, 0, 0, 0, RF_CONJ)
                 .op(ROP_FFT_INV)
-                .op(ROP_STORE_C, W1, nn(N), N);
+                .op(ROP_STORE_C, X, field_elems(N, dtype), field_row(N, dtype));
             if (int rc = run_row<ProgVjpYTag>(dtype, N, b.p, b.n, stream)) return rc;
         }
-        if (int rc = transpose(W1, W2, N, nb, (int)(cbytes / nn(N)), stream)) return rc;
+        void *Y = nullptr;
+        if (int rc = exchange(X, X == W1 ? W2 : W1, N, nb, dtype, &Y, stream)) return rc;
         // adjoint x-propagation, dL/dphi = s Im(g_U conj U), and sum phi dL/dphi per row
         char *gphi = static_cast<char *>(grad_phi_out) + (size_t)b0 * rb1;
         ProgBuilder d(N, (int64_t)nb * N);
-        d.op(ROP_LOAD_C, W2, nn(N), N)
+        d.op(ROP_LOAD_C, Y, field_elems(N, dtype), field_row(N, dtype))
             .op(ROP_FFT_FWD)
             .op(ROP_MUL_TAB, H, 0, 0, 0, RF_CONJ)
             .op(ROP_FFT_INV)
@@ -2101,7 +2183,7 @@ int ps_structure_function(int N, double delta, const void *phi, int n, const dou
     hipStream_t stream = static_cast<hipStream_t>(hip_stream);
     if (int rc = refuse_in_capture(stream, "ps_structure_function")) return rc;
     const int nbins = N / 2 + 1;
-    const size_t cbytes = (size_t)nn(N) * 2 * real_bytes(dtype);
+    const size_t cbytes = field_bytes(N, dtype);
     const int nb_max = (int)std::max<size_t>(1, workspace_budget() / (2 * cbytes));
     std::vector<double> rpx(n_r);
     for (int j = 0; j < n_r; ++j) rpx[j] = radii[j] / delta;
@@ -2120,16 +2202,18 @@ int ps_structure_function(int N, double delta, const void *phi, int n, const dou
         const char *ph = static_cast<const char *>(phi) + (size_t)b0 * nn(N) * real_bytes(dtype);
         // |DFT phi|^2 / N^2: DFT along x, transpose, DFT along y and |.|^2
         ProgBuilder a(N, (int64_t)nb * N);
-        a.op(ROP_LOAD_R, ph, nn(N), N).op(ROP_FFT_FWD).op(ROP_STORE_C, W1, nn(N), N);
+        a.op(ROP_LOAD_R, ph, nn(N), N).op(ROP_FFT_FWD).op(ROP_STORE_C, W1, field_elems(N, dtype), field_row(N, dtype));
         if (int rc = run_row<ProgRealFwdTag>(dtype, N, a.p, a.n, stream)) return rc;
-        if (int rc = transpose(W1, W2, N, nb, 2 * (int)real_bytes(dtype), stream)) return rc;
+        void *F = nullptr;
+        if (int rc = exchange(W1, W2, N, nb, dtype, &F, stream)) return rc;
+        void *P = F == W1 ? W2 : W1;
         ProgBuilder d(N, (int64_t)nb * N);
-        d.op(ROP_LOAD_C, W2, nn(N), N)
+        d.op(ROP_LOAD_C, F, field_elems(N, dtype), field_row(N, dtype))
             .op(ROP_FFT_FWD)
             .op(ROP_ACC_ABS2, nullptr, 0, 0, 0, 0, 1.0 / ((double)N * (double)N))
-            .op(ROP_STORE_ACC, W1, nn(N), N);
+            .op(ROP_STORE_ACC, P, nn(N), N);
         if (int rc = run_row<ProgAbs2Tag>(dtype, N, d.p, d.n, stream)) return rc;
-        HIP_TRY(launch_ring_sums(W1, N, nb, dtype == PS_F64, S, nullptr, stream));
+        HIP_TRY(launch_ring_sums(P, N, nb, dtype == PS_F64, S, nullptr, stream));
         if (n_r > 0 || rdiff_out)
             HIP_TRY(launch_hankel(S, N, nb, rpx.data(), n_r, D, rdiff_out ? R : nullptr, stream));
         std::vector<double> hS(S_out ? (size_t)nb * nbins : 0), hD((size_t)nb * n_r), hR(rdiff_out ? nb : 0);

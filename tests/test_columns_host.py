@@ -1,0 +1,22 @@
+"""The sizes that store their fields by columns (host logic, no GPU): builds
+tests/columns_check.cpp with the host compiler."""
+import os
+import shutil
+import subprocess
+
+import pytest
+
+HERE = os.path.dirname(os.path.abspath(__file__))
+CSRC = os.path.join(HERE, "..", "paper_1301_0514_amd", "csrc")
+
+
+def test_column_layouts(tmp_path):
+    cxx = shutil.which("g++") or shutil.which("c++")
+    if cxx is None:
+        pytest.skip("no host C++ compiler")
+    exe = str(tmp_path / "columns_check")
+    subprocess.run([cxx, "-std=c++17", "-O1", "-I", CSRC, os.path.join(HERE, "columns_check.cpp"), "-o", exe],
+                   check=True, capture_output=True, text=True)
+    r = subprocess.run([exe], capture_output=True, text=True)
+    assert r.returncode == 0, r.stdout[-3000:]
+    assert "ok L=4096 V=1 eb=8 rows=4" in r.stdout and r.stdout.strip().endswith("0 failures")
