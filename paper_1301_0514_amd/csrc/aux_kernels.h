@@ -65,13 +65,15 @@ hipError_t launch_ring_sums(const void *P, int N, int nbatch, bool f64, double *
 // D(r) = 2 (xi(0) - xi(r)) from ring spectra S [nbatch][N/2 + 1] (pixel units,
 // the J0 sum of Eq. crec) at n_r radii (pixels; by value, kRadiiPerLaunch at a
 // time) into D [nbatch][n_r], and R_diff^rec (D = 1) into rdiff [nbatch] if
-// rdiff != NULL (NaN if not bracketed in [1e-3, N/2]).
+// rdiff != NULL (NaN if not bracketed in [1e-3, N/2]); scratch:
+// hankel_scratch_bytes(nbatch), 8-byte aligned (needed with rdiff only).
 constexpr int kRadiiPerLaunch = 64;
 struct RadiusSet {
     double r[kRadiiPerLaunch];
 };
+size_t hankel_scratch_bytes(int nbatch);
 hipError_t launch_hankel(const double *S, int N, int nbatch, const double *radii, int n_r, double *D, double *rdiff,
-                         hipStream_t stream);
+                         void *scratch, hipStream_t stream);
 
 // The lowest Fourier modes of FP32 screens, synthesised in FP64 (Sect. 3.1):
 // for realisations r0 + b, b < nbatch, with W = 2K + 1,

@@ -3,6 +3,8 @@
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
+#include <cmath>
+
 #include "aux_kernels.h"
 #include "device_common.hpp"
 #include "transpose_tile.hpp"
@@ -494,33 +496,45 @@ hipError_t launch_ring_sums(const void *P, int N, int nbatch, bool f64, double *
 // J0 = sqrt(2 / (pi x)) (P cos(x - pi/4) - Q sin(x - pi/4)),
 // P = sum_k (-1)^k a_2k / x^2k, Q = sum_k (-1)^k a_(2k+1) / x^(2k+1),
 // a_k = prod_{j <= k} (2j - 1)^2 / (k! 8^k), summed while the terms shrink.
+// The ratios of successive terms come from tables, so that a term takes two
+// products and no division.
+constexpr int kJ0Series = 80, kJ0Hankel = 60;
+struct J0Ratios {
+    double series[kJ0Series], hankel[kJ0Hankel];  // 1 / k^2, (2k - 1)^2 / (8k)
+    constexpr J0Ratios() : series(), hankel() {
+        for (int k = 1; k < kJ0Series; ++k) series[k] = 1.0 / ((double)k * (double)k);
+        for (int k = 1; k < kJ0Hankel; ++k) hankel[k] = (double)((2 * k - 1) * (2 * k - 1)) / (8.0 * k);
+    }
+};
+__constant__ J0Ratios kJ0 = J0Ratios();
+
 __device__ double bessel_j0(double x) {
     x = fabs(x);
     if (x < 14.0) {
         const double y = 0.25 * x * x;
         double t = 1.0, sum = 1.0;
-        for (int k = 1; k < 80; ++k) {
-            t *= -y / ((double)k * (double)k);
+        for (int k = 1; k < kJ0Series; ++k) {
+            t *= -y * kJ0.series[k];
             sum += t;
             if (fabs(t) < 1e-17 * fabs(sum) && (double)k * k > y) break;
         }
         return sum;
     }
-    double P = 1.0, Q = 0.0, a = 1.0, xp = 1.0, last = 1.0;
-    for (int k = 1; k < 60; ++k) {
-        a *= (double)((2 * k - 1) * (2 * k - 1)) / (8.0 * k);
-        xp *= x;
-        const double term = a / xp;
-        if (term > last) break;  // the asymptotic series starts to diverge
-        last = term;
+    const double ix = 1.0 / x;
+    double P = 1.0, Q = 0.0, term = 1.0;
+    for (int k = 1; k < kJ0Hankel; ++k) {
+        const double next = term * (kJ0.hankel[k] * ix);
+        if (next > term) break;  // the asymptotic series starts to diverge
+        term = next;
         if (k & 1)
             Q += ((k / 2) & 1) ? term : -term;  // k = 1: -a1/x, k = 3: +a3/x^3, ...
         else
             P += ((k / 2) & 1) ? -term : term;  // k = 2: -a2/x^2, k = 4: +a4/x^4, ...
         if (term < 1e-17) break;
     }
-    const double ph = x - 0.25 * 3.14159265358979323846;
-    return sqrt(2.0 / (3.14159265358979323846 * x)) * (P * cos(ph) - Q * sin(ph));
+    double sn, cs;
+    sincos(x - 0.25 * kPi, &sn, &cs);
+    return sqrt(2.0 / (kPi * x)) * (P * cs - Q * sn);
 }
 
 // D(r) = 2 sum_{b=1}^{N/2} 2 pi (b/N) S_b (1 - J0(2 pi b r / N)) / N for the
@@ -529,58 +543,119 @@ __device__ double structure_at(const double *S, int N, double r, double *red) {
     double acc = 0.0;
     for (int b = 1 + (int)threadIdx.x; b <= N / 2; b += 256) {
         const double q = (double)b / N;
-        acc += q * S[b] * (1.0 - bessel_j0(2.0 * 3.14159265358979323846 * q * r));
+        acc += q * S[b] * (1.0 - bessel_j0(2.0 * kPi * q * r));
     }
     __syncthreads();
     const double tot = block_tree_sum(acc, red);
-    return 4.0 * 3.14159265358979323846 * tot / N;
+    return 4.0 * kPi * tot / N;
 }
 
-// One workgroup per screen: D at the given radii (pixels) and, if rdiff !=
-// NULL, R_diff^rec solving D = 1 by bisection on [1e-3, N/2] (NaN when the
-// root is not bracketed).
-__global__ __launch_bounds__(256) void hankel_kernel(const double *S, int N, RadiusSet rs, int n_r, double *D,
-                                                     int ld_D, int r0, double *rdiff) {
+// D at one radius per workgroup: D[screen ld_D + r0 + j] for radius j (pixels).
+__global__ __launch_bounds__(256) void hankel_kernel(const double *S, int N, RadiusSet rs, double *D, int ld_D, int r0) {
     __shared__ double red[256];
-    const int bat = blockIdx.x;
-    const double *Sb = S + (int64_t)bat * (N / 2 + 1);
-    for (int j = 0; j < n_r; ++j) {
-        const double d = structure_at(Sb, N, rs.r[j], red);
-        if (threadIdx.x == 0) D[(int64_t)bat * ld_D + r0 + j] = d;
+    const int j = blockIdx.x, bat = blockIdx.y;
+    const double d = structure_at(S + (int64_t)bat * (N / 2 + 1), N, rs.r[j], red);
+    if (threadIdx.x == 0) D[(int64_t)bat * ld_D + r0 + j] = d;
+}
+
+// R_diff^rec solves D = 1 by bisection on [1e-3, N/2] to a relative 1e-12 (NaN
+// when the root is not bracketed), kRootLevels levels of it per launch: one
+// workgroup for each of the 2^levels - 1 midpoints that these levels can come
+// to evaluates D there, and the next launch walks down the tree.  On one
+// workgroup the 40-60 evaluations, one after the other, took 1.5 ms for two
+// 4000^2 screens; the launches take 0.1 ms.  RootState of a screen: the
+// bracket before the launch's levels and D at their midpoints (node 1 the
+// first, nodes 2n and 2n + 1 below and above it); two alternate.
+constexpr int kRootLevels = 8, kRootNodes = 1 << kRootLevels;
+constexpr double kRootLo = 1e-3;
+struct RootState {
+    double lo, hi;
+    double D[kRootNodes];
+};
+
+__device__ __forceinline__ bool root_found(double lo, double hi) { return !(hi - lo > 1e-12 * hi); }
+
+__device__ __forceinline__ void root_walk(const RootState &s, double &lo, double &hi) {
+    lo = s.lo;
+    hi = s.hi;
+    for (int node = 1; node < kRootNodes && !root_found(lo, hi);) {
+        const double mid = 0.5 * (lo + hi);
+        const bool below = s.D[node] < 1.0;
+        (below ? lo : hi) = mid;
+        node = 2 * node + below;
     }
-    if (!rdiff) return;
-    double lo = 1e-3, hi = 0.5 * N;
-    const double dlo = structure_at(Sb, N, lo, red), dhi = structure_at(Sb, N, hi, red);
-    if (!(dlo < 1.0 && dhi >= 1.0)) {
-        if (threadIdx.x == 0) rdiff[bat] = __longlong_as_double(0x7ff8000000000000LL);
+}
+
+// ends: D at the two ends of the first bracket, [screen][2]; first: the
+// bracket is the whole range
+__global__ __launch_bounds__(256) void root_kernel(const double *S, int N, const double *ends, const RootState *from,
+                                                   RootState *to, int first) {
+    __shared__ double red[256];
+    const int node = blockIdx.x + 1, bat = blockIdx.y;
+    if (!(ends[2 * bat] < 1.0 && ends[2 * bat + 1] >= 1.0)) return;
+    double lo = kRootLo, hi = 0.5 * N;
+    if (!first) root_walk(from[bat], lo, hi);
+    if (node == 1 && threadIdx.x == 0) {
+        to[bat].lo = lo;
+        to[bat].hi = hi;
+    }
+    // the node's midpoint, down the path that its bits spell
+    for (int bit = 30 - __clz(node); bit >= 0; --bit) {
+        if (root_found(lo, hi)) return;
+        const double mid = 0.5 * (lo + hi);
+        ((node >> bit) & 1 ? lo : hi) = mid;
+    }
+    if (root_found(lo, hi)) return;  // (the walk stops above this node)
+    const double d = structure_at(S + (int64_t)bat * (N / 2 + 1), N, 0.5 * (lo + hi), red);
+    if (threadIdx.x == 0) to[bat].D[node] = d;
+}
+
+__global__ __launch_bounds__(64) void root_finish_kernel(int n, const double *ends, const RootState *from, double *rdiff) {
+    const int bat = blockIdx.x * 64 + threadIdx.x;
+    if (bat >= n) return;
+    if (!(ends[2 * bat] < 1.0 && ends[2 * bat + 1] >= 1.0)) {
+        rdiff[bat] = __longlong_as_double(0x7ff8000000000000LL);
         return;
     }
-    for (int it = 0; it < 200 && hi - lo > 1e-12 * hi; ++it) {  // every thread sees the same lo, hi
-        const double mid = 0.5 * (lo + hi);
-        if (structure_at(Sb, N, mid, red) < 1.0)
-            lo = mid;
-        else
-            hi = mid;
-    }
-    if (threadIdx.x == 0) rdiff[bat] = 0.5 * (lo + hi);
+    double lo, hi;
+    root_walk(from[bat], lo, hi);
+    rdiff[bat] = 0.5 * (lo + hi);
 }
 
+size_t hankel_scratch_bytes(int nbatch) { return (size_t)nbatch * (2 * sizeof(RootState) + 2 * sizeof(double)); }
+
 hipError_t launch_hankel(const double *S, int N, int nbatch, const double *radii, int n_r, double *D, double *rdiff,
-                         hipStream_t stream) {
-    if (n_r == 0) {
+                         void *scratch, hipStream_t stream) {
+    for (int b0 = 0; b0 < nbatch; b0 += 65535) {
+        const int nb = nbatch - b0 < 65535 ? nbatch - b0 : 65535;
+        const double *Sb = S + (int64_t)b0 * (N / 2 + 1);
+        for (int j0 = 0; j0 < n_r; j0 += kRadiiPerLaunch) {
+            const int nr = n_r - j0 < kRadiiPerLaunch ? n_r - j0 : kRadiiPerLaunch;
+            RadiusSet rs{};
+            for (int j = 0; j < nr; ++j) rs.r[j] = radii[j0 + j];
+            hipLaunchKernelGGL(hankel_kernel, dim3(nr, nb), dim3(256), 0, stream, Sb, N, rs, D + (int64_t)b0 * n_r, n_r, j0);
+            if (hipError_t e = hipGetLastError()) return e;
+        }
+        if (!rdiff) continue;
+        RootState *state = static_cast<RootState *>(scratch);
+        double *ends = reinterpret_cast<double *>(state + 2 * (size_t)nbatch);
         RadiusSet rs{};
-        hipLaunchKernelGGL(hankel_kernel, dim3(nbatch), dim3(256), 0, stream, S, N, rs, 0, D, 0, 0, rdiff);
-        return hipGetLastError();
-    }
-    for (int j0 = 0; j0 < n_r; j0 += kRadiiPerLaunch) {
-        const int nr = n_r - j0 < kRadiiPerLaunch ? n_r - j0 : kRadiiPerLaunch;
-        RadiusSet rs{};
-        for (int j = 0; j < nr; ++j) rs.r[j] = radii[j0 + j];
-        // the root is found once, with the first chunk of radii
-        hipLaunchKernelGGL(hankel_kernel, dim3(nbatch), dim3(256), 0, stream, S, N, rs, nr, D, n_r, j0,
-                           j0 == 0 ? rdiff : nullptr);
-        hipError_t e = hipGetLastError();
-        if (e != hipSuccess) return e;
+        rs.r[0] = kRootLo;
+        rs.r[1] = 0.5 * N;
+        hipLaunchKernelGGL(hankel_kernel, dim3(2, nb), dim3(256), 0, stream, Sb, N, rs, ends, 2, 0);
+        if (hipError_t e = hipGetLastError()) return e;
+        // the bracket shrinks from N/2 to 1e-12 of a root that is at least
+        // 1e-3 pixels: at most log2(N/2 / 1e-15) halvings
+        const int levels = (int)std::ceil(std::log2(0.5 * N / (1e-12 * kRootLo)));
+        const int rounds = (levels + kRootLevels - 1) / kRootLevels;
+        for (int k = 0; k < rounds; ++k) {
+            hipLaunchKernelGGL(root_kernel, dim3(kRootNodes - 1, nb), dim3(256), 0, stream, Sb, N, ends,
+                               state + (size_t)((k + 1) % 2) * nb, state + (size_t)(k % 2) * nb, k == 0 ? 1 : 0);
+            if (hipError_t e = hipGetLastError()) return e;
+        }
+        hipLaunchKernelGGL(root_finish_kernel, dim3((nb + 63) / 64), dim3(64), 0, stream, nb, ends,
+                           state + (size_t)((rounds - 1) % 2) * nb, rdiff + b0);
+        if (hipError_t e = hipGetLastError()) return e;
     }
     return hipSuccess;
 }

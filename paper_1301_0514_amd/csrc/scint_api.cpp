@@ -2189,7 +2189,8 @@ int ps_structure_function(int N, double delta, const void *phi, int n, const dou
     for (int j = 0; j < n_r; ++j) rpx[j] = radii[j] / delta;
     for (int b0 = 0; b0 < n; b0 += nb_max) {
         const int nb = std::min(nb_max, n - b0);
-        const size_t small = (size_t)nb * nbins * 8 + (size_t)nb * std::max(n_r, 1) * 8 + (size_t)nb * 8 + 1024;
+        const size_t small = (size_t)nb * nbins * 8 + (size_t)nb * std::max(n_r, 1) * 8 + (size_t)nb * 8 +
+                             hankel_scratch_bytes(nb) + 1024;
         void *ws = nullptr;
         if (int rc = get_workspace(stream, 2 * cbytes * nb + small, &ws)) return rc;
         Carver c;
@@ -2199,6 +2200,7 @@ int ps_structure_function(int N, double delta, const void *phi, int n, const dou
         double *S = reinterpret_cast<double *>(base + c.take((size_t)nb * nbins * 8));
         double *D = reinterpret_cast<double *>(base + c.take((size_t)nb * std::max(n_r, 1) * 8));
         double *R = reinterpret_cast<double *>(base + c.take((size_t)nb * 8));
+        void *scratch = base + c.take(hankel_scratch_bytes(nb));
         const char *ph = static_cast<const char *>(phi) + (size_t)b0 * nn(N) * real_bytes(dtype);
         // |DFT phi|^2 / N^2: DFT along x, transpose, DFT along y and |.|^2
         ProgBuilder a(N, (int64_t)nb * N);
@@ -2215,7 +2217,7 @@ int ps_structure_function(int N, double delta, const void *phi, int n, const dou
         if (int rc = run_row<ProgAbs2Tag>(dtype, N, d.p, d.n, stream)) return rc;
         HIP_TRY(launch_ring_sums(P, N, nb, dtype == PS_F64, S, nullptr, stream));
         if (n_r > 0 || rdiff_out)
-            HIP_TRY(launch_hankel(S, N, nb, rpx.data(), n_r, D, rdiff_out ? R : nullptr, stream));
+            HIP_TRY(launch_hankel(S, N, nb, rpx.data(), n_r, D, rdiff_out ? R : nullptr, scratch, stream));
         std::vector<double> hS(S_out ? (size_t)nb * nbins : 0), hD((size_t)nb * n_r), hR(rdiff_out ? nb : 0);
         if (S_out) HIP_TRY(hipMemcpyAsync(hS.data(), S, hS.size() * 8, hipMemcpyDeviceToHost, stream));
         if (n_r > 0) HIP_TRY(hipMemcpyAsync(hD.data(), D, hD.size() * 8, hipMemcpyDeviceToHost, stream));
