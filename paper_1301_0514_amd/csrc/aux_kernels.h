@@ -58,9 +58,10 @@ hipError_t launch_light_curves(const void *I, int N, int nbatch, const double *l
                                int mode, bool f64, void *out, double *stats, hipStream_t stream);
 
 // Ring sums of a power map P [nbatch][N][N] (real): S[b][k] = mean of P over
-// the pixels whose signed frequency |k'| rounds to k, k = 0 .. N/2, in FP64;
-// count[k] = their number (if count != NULL).
-hipError_t launch_ring_sums(const void *P, int N, int nbatch, bool f64, double *S, double *count, hipStream_t stream);
+// the pixels whose signed frequency |k'| rounds to k, k = 0 .. N/2, in FP64.
+// scratch: ring_scratch_bytes(N, nbatch), 8-byte aligned.
+size_t ring_scratch_bytes(int N, int nbatch);
+hipError_t launch_ring_sums(const void *P, int N, int nbatch, bool f64, double *S, void *scratch, hipStream_t stream);
 
 // D(r) = 2 (xi(0) - xi(r)) from ring spectra S [nbatch][N/2 + 1] (pixel units,
 // the J0 sum of Eq. crec) at n_r radii (pixels; by value, kRadiiPerLaunch at a

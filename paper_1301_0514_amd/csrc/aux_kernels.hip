@@ -433,61 +433,129 @@ hipError_t launch_light_curves(const void *I, int N, int nbatch, const double *l
 // ---------------------------------------------------------------- structure function
 // Ring sums of a power map P [batch][N][N] (either orientation): ring b holds
 // the pixels of signed frequency k' (components in [-N/2, N/2)) with
-// (2b - 1)^2 <= 4 |k'|^2 < (2b + 1)^2 (|k'| rounds to b).  One workgroup per
-// (ring, batch member); each thread walks whole rows of the ring and the
-// partial sums meet in a fixed-order tree, so the result is reproducible.
+// (2b - 1)^2 <= 4 |k'|^2 < (2b + 1)^2 (|k'| rounds to b).  Bound by the read of
+// P: neighbouring threads take neighbouring rings of one row, whose pixels lie
+// next to each other (one workgroup per ring, its threads on different rows,
+// read every pixel from a line of its own: 231 us for two 4000^2 maps).  A
+// workgroup takes 256 rings of kRingRows values of |ky'|, each of them the two
+// rows +-ky'; every thread sums its ring in a fixed order, and a second kernel
+// adds the row groups in order, so the result is reproducible.  A ring crosses
+// most rows in one or two pixels: the first two of every row are loaded before
+// any is waited for.
+constexpr int kRingRows = 4;
+
 __device__ __forceinline__ int64_t isqrt_floor(int64_t v) {  // floor(sqrt(v)), v >= 0
     int64_t r = (int64_t)sqrt((double)v);
     while (r * r > v) --r;
     while ((r + 1) * (r + 1) <= v) ++r;
     return r;
 }
+// largest k with 4 k^2 < v, v > 0
+__device__ __forceinline__ int ring_edge(int64_t v) { return (int)isqrt_floor((v - 1) / 4); }
 
 template <typename Real>
-__global__ __launch_bounds__(256) void ring_sum_kernel(const Real *__restrict__ P, int N, double *S, double *count) {
-    __shared__ double red[256];
-    const int b = blockIdx.x, bat = blockIdx.y;
+__global__ __launch_bounds__(256) void ring_part_kernel(const Real *__restrict__ P, int N, double *part, double *count) {
+    const int b = blockIdx.x * 256 + (int)threadIdx.x, rows0 = blockIdx.y * kRingRows, bat = blockIdx.z;
+    const int h = N / 2;
+    if (b > h) return;
     const Real *img = P + (int64_t)bat * N * N;
     const int64_t lo2 = b == 0 ? 0 : (int64_t)(2 * b - 1) * (2 * b - 1), hi2 = (int64_t)(2 * b + 1) * (2 * b + 1);
-    const int h = N / 2;
-    double acc = 0.0, cnt = 0.0;
-    for (int ky = -(b + 1) + (int)threadIdx.x; ky <= b + 1; ky += 256) {
-        if (ky < -h || ky >= h) continue;
-        const int64_t t = 4 * (int64_t)ky * ky;
-        if (t >= hi2) continue;
+    int k0[kRingRows], k1[kRingRows];
+    double v[kRingRows][2][4];
+    // the four pixels (+-kx, +-ky') of row a, 0 for those that do not exist:
+    // components lie in [-h, h), and -0 is 0
+    auto pixels = [&](int a, int kx, double (&x)[4]) {
+        const Real *up = img + (int64_t)(a < h ? a : 0) * N, *down = img + (int64_t)(a > 0 ? N - a : 0) * N;
+        const int r = kx < h ? kx : 0, l = kx > 0 ? N - kx : 0;
+        const double ur = (double)up[r], dr = (double)down[r], ul = (double)up[l], dl = (double)down[l];
+        x[0] = kx < h && a < h ? ur : 0.0;
+        x[1] = kx < h && a > 0 ? dr : 0.0;
+        x[2] = kx > 0 && a < h ? ul : 0.0;
+        x[3] = kx > 0 && a > 0 ? dl : 0.0;
+    };
+#pragma unroll
+    for (int i = 0; i < kRingRows; ++i) {
+        const int a = rows0 + i;
+        const int64_t t = 4 * (int64_t)a * a;
+        const bool in = a <= h && t < hi2;
         // kx >= 0 with lo2 <= 4 kx^2 + t < hi2
-        const int64_t kmin = (lo2 - t <= 0) ? 0 : isqrt_floor((lo2 - t + 3) / 4 - 1) + 1;
-        const int64_t kmax = isqrt_floor((hi2 - t - 1) / 4);
-        const Real *row = img + (int64_t)(ky < 0 ? ky + N : ky) * N;
-        for (int64_t kx = kmin; kx <= kmax; ++kx) {
-            if (kx < h) {  // +kx
-                acc += (double)row[kx];
-                cnt += 1.0;
+        k0[i] = in && lo2 > t ? ring_edge(lo2 - t) + 1 : 0;
+        k1[i] = in ? min(ring_edge(hi2 - t), h) : -1;
+#pragma unroll
+        for (int q = 0; q < 2; ++q) pixels(in ? a : 0, min(k0[i] + q, h), v[i][q]);
+    }
+    double acc = 0.0;
+    int cnt = 0;
+#pragma unroll
+    for (int i = 0; i < kRingRows; ++i) {
+        const int a = rows0 + i, rows = (a < h) + (a > 0);
+        for (int kx = k0[i]; kx <= k1[i]; ++kx) {
+            double x[4];
+            if (kx - k0[i] < 2) {
+                const int q = kx - k0[i];
+#pragma unroll
+                for (int e = 0; e < 4; ++e) x[e] = q ? v[i][1][e] : v[i][0][e];
+            } else {
+                pixels(a, kx, x);
             }
-            if (kx > 0 && kx <= h) {  // -kx
-                acc += (double)row[N - kx];
-                cnt += 1.0;
-            }
+#pragma unroll
+            for (int e = 0; e < 4; ++e) acc += x[e];
+            cnt += rows * ((kx < h) + (kx > 0));
         }
     }
-    const double tot = block_tree_sum(acc, red);
+    const int64_t o = (int64_t)blockIdx.y * (h + 1) + b;
+    part[(int64_t)bat * gridDim.y * (h + 1) + o] = acc;
+    if (bat == 0) count[o] = (double)cnt;
+}
+
+// S[screen][b]: the sum over the row groups in order, over the number of the
+// ring's pixels.  A workgroup takes 32 rings, 8 threads each (the groups that
+// can touch ring b end at row b).
+__global__ __launch_bounds__(256) void ring_sum_kernel(const double *part, const double *count, int nbins, int groups,
+                                                       double *S) {
+    __shared__ double red[2][8][32];
+    const int l = threadIdx.x % 32, g = threadIdx.x / 32, b = blockIdx.x * 32 + l, bat = blockIdx.y;
+    double acc = 0.0, cnt = 0.0;
+    if (b < nbins) {
+        const double *p = part + (int64_t)bat * groups * nbins + b;
+        for (int q = g; q < groups && q * kRingRows <= b + 1; q += 8) {
+            acc += p[(int64_t)q * nbins];
+            cnt += count[(int64_t)q * nbins + b];
+        }
+    }
+    red[0][g][l] = acc;
+    red[1][g][l] = cnt;
     __syncthreads();
-    const double c = block_tree_sum(cnt, red);
-    if (threadIdx.x == 0) {
-        S[(int64_t)bat * gridDim.x + b] = c > 0 ? tot / c : 0.0;
-        if (count && bat == 0) count[b] = c;
+    if (g == 0 && b < nbins) {
+        for (int q = 1; q < 8; ++q) {
+            acc += red[0][q][l];
+            cnt += red[1][q][l];
+        }
+        S[(int64_t)bat * nbins + b] = cnt > 0.0 ? acc / cnt : 0.0;
     }
 }
 
-hipError_t launch_ring_sums(const void *P, int N, int nbatch, bool f64, double *S, double *count, hipStream_t stream) {
-    dim3 grid(N / 2 + 1, nbatch);
-    if (f64)
-        hipLaunchKernelGGL((ring_sum_kernel<double>), grid, dim3(256), 0, stream, static_cast<const double *>(P), N, S,
-                           count);
-    else
-        hipLaunchKernelGGL((ring_sum_kernel<float>), grid, dim3(256), 0, stream, static_cast<const float *>(P), N, S,
-                           count);
-    return hipGetLastError();
+static int ring_groups(int N) { return (N / 2 + 1 + kRingRows - 1) / kRingRows; }
+size_t ring_scratch_bytes(int N, int nbatch) { return (size_t)(nbatch + 1) * ring_groups(N) * (N / 2 + 1) * 8; }
+
+hipError_t launch_ring_sums(const void *P, int N, int nbatch, bool f64, double *S, void *scratch, hipStream_t stream) {
+    const int nbins = N / 2 + 1, groups = ring_groups(N);
+    double *count = static_cast<double *>(scratch), *part = count + (size_t)groups * nbins;
+    for (int b0 = 0; b0 < nbatch; b0 += 65535) {
+        const int nb = nbatch - b0 < 65535 ? nbatch - b0 : 65535;
+        const dim3 grid((nbins + 255) / 256, groups, nb);
+        if (f64)
+            hipLaunchKernelGGL((ring_part_kernel<double>), grid, dim3(256), 0, stream,
+                               static_cast<const double *>(P) + (int64_t)b0 * N * N, N, part, count);
+        else
+            hipLaunchKernelGGL((ring_part_kernel<float>), grid, dim3(256), 0, stream,
+                               static_cast<const float *>(P) + (int64_t)b0 * N * N, N, part, count);
+        if (hipError_t e = hipGetLastError()) return e;
+        hipLaunchKernelGGL(ring_sum_kernel, dim3((nbins + 31) / 32, nb), dim3(256), 0, stream, part, count, nbins, groups,
+                           S + (int64_t)b0 * nbins);
+        if (hipError_t e = hipGetLastError()) return e;
+    }
+    return hipSuccess;
 }
 
 // J0, the Bessel function of the first kind of order 0, in FP64: its power
@@ -496,41 +564,33 @@ hipError_t launch_ring_sums(const void *P, int N, int nbatch, bool f64, double *
 // J0 = sqrt(2 / (pi x)) (P cos(x - pi/4) - Q sin(x - pi/4)),
 // P = sum_k (-1)^k a_2k / x^2k, Q = sum_k (-1)^k a_(2k+1) / x^(2k+1),
 // a_k = prod_{j <= k} (2j - 1)^2 / (k! 8^k), summed while the terms shrink.
-// The ratios of successive terms come from tables, so that a term takes two
-// products and no division.
-constexpr int kJ0Series = 80, kJ0Hankel = 60;
-struct J0Ratios {
-    double series[kJ0Series], hankel[kJ0Hankel];  // 1 / k^2, (2k - 1)^2 / (8k)
-    constexpr J0Ratios() : series(), hankel() {
-        for (int k = 1; k < kJ0Series; ++k) series[k] = 1.0 / ((double)k * (double)k);
-        for (int k = 1; k < kJ0Hankel; ++k) hankel[k] = (double)((2 * k - 1) * (2 * k - 1)) / (8.0 * k);
-    }
-};
-__constant__ J0Ratios kJ0 = J0Ratios();
+// Both sums run over a fixed number of terms with compile-time ratios (a
+// loop that divides, or takes the ratios from memory, waits for each): 48 of
+// the series, whose later terms vanish beside any sum, and 28 of the
+// expansion, up to its smallest term at x = 14 (7e-13; below 1e-13 from 15).
+constexpr int kJ0Series = 48, kJ0Hankel = 28;
 
 __device__ double bessel_j0(double x) {
     x = fabs(x);
     if (x < 14.0) {
-        const double y = 0.25 * x * x;
+        const double y = -0.25 * x * x;
         double t = 1.0, sum = 1.0;
-        for (int k = 1; k < kJ0Series; ++k) {
-            t *= -y * kJ0.series[k];
+#pragma unroll
+        for (int k = 1; k <= kJ0Series; ++k) {
+            t *= y * (1.0 / ((double)k * (double)k));
             sum += t;
-            if (fabs(t) < 1e-17 * fabs(sum) && (double)k * k > y) break;
         }
         return sum;
     }
     const double ix = 1.0 / x;
     double P = 1.0, Q = 0.0, term = 1.0;
-    for (int k = 1; k < kJ0Hankel; ++k) {
-        const double next = term * (kJ0.hankel[k] * ix);
-        if (next > term) break;  // the asymptotic series starts to diverge
-        term = next;
+#pragma unroll
+    for (int k = 1; k <= kJ0Hankel; ++k) {
+        term *= ix * ((double)((2 * k - 1) * (2 * k - 1)) / (8.0 * k));
         if (k & 1)
             Q += ((k / 2) & 1) ? term : -term;  // k = 1: -a1/x, k = 3: +a3/x^3, ...
         else
             P += ((k / 2) & 1) ? -term : term;  // k = 2: -a2/x^2, k = 4: +a4/x^4, ...
-        if (term < 1e-17) break;
     }
     double sn, cs;
     sincos(x - 0.25 * kPi, &sn, &cs);

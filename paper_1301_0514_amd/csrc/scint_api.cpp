@@ -2190,7 +2190,7 @@ int ps_structure_function(int N, double delta, const void *phi, int n, const dou
     for (int b0 = 0; b0 < n; b0 += nb_max) {
         const int nb = std::min(nb_max, n - b0);
         const size_t small = (size_t)nb * nbins * 8 + (size_t)nb * std::max(n_r, 1) * 8 + (size_t)nb * 8 +
-                             hankel_scratch_bytes(nb) + 1024;
+                             hankel_scratch_bytes(nb) + ring_scratch_bytes(N, nb) + 1536;
         void *ws = nullptr;
         if (int rc = get_workspace(stream, 2 * cbytes * nb + small, &ws)) return rc;
         Carver c;
@@ -2201,6 +2201,7 @@ int ps_structure_function(int N, double delta, const void *phi, int n, const dou
         double *D = reinterpret_cast<double *>(base + c.take((size_t)nb * std::max(n_r, 1) * 8));
         double *R = reinterpret_cast<double *>(base + c.take((size_t)nb * 8));
         void *scratch = base + c.take(hankel_scratch_bytes(nb));
+        void *rings = base + c.take(ring_scratch_bytes(N, nb));
         const char *ph = static_cast<const char *>(phi) + (size_t)b0 * nn(N) * real_bytes(dtype);
         // |DFT phi|^2 / N^2: DFT along x, transpose, DFT along y and |.|^2
         ProgBuilder a(N, (int64_t)nb * N);
@@ -2215,7 +2216,7 @@ int ps_structure_function(int N, double delta, const void *phi, int n, const dou
             .op(ROP_ACC_ABS2, nullptr, 0, 0, 0, 0, 1.0 / ((double)N * (double)N))
             .op(ROP_STORE_ACC, P, nn(N), N);
         if (int rc = run_row<ProgAbs2Tag>(dtype, N, d.p, d.n, stream)) return rc;
-        HIP_TRY(launch_ring_sums(P, N, nb, dtype == PS_F64, S, nullptr, stream));
+        HIP_TRY(launch_ring_sums(P, N, nb, dtype == PS_F64, S, rings, stream));
         if (n_r > 0 || rdiff_out)
             HIP_TRY(launch_hankel(S, N, nb, rpx.data(), n_r, D, rdiff_out ? R : nullptr, scratch, stream));
         std::vector<double> hS(S_out ? (size_t)nb * nbins : 0), hD((size_t)nb * n_r), hR(rdiff_out ? nb : 0);
