@@ -29,16 +29,12 @@ hipError_t launch_twiddle_table(void *tab, int n_stages, const int *ns, const in
 // (x, y) from the origin), else 0.
 hipError_t launch_disk_image(void *img, int N, double r2, double value, bool f64, hipStream_t stream);
 
-// partials[b * nblk + blk] = sum over block blk's share of batch b of
-// (x - center[b])^power  (center may be NULL = 0; power 1 or 2), FP64.
-hipError_t launch_block_sums(const void *x, int64_t n_per_batch, int nbatch, const double *center,
-                             int power, int nblk, bool f64, double *partials, hipStream_t stream);
-
-// As launch_block_sums over a w x h region of each batch member: rows of
-// w elements, row_stride apart, starting at x + b * batch_stride.
-hipError_t launch_region_sums(const void *x, int64_t batch_stride, int64_t w, int64_t h, int64_t row_stride,
-                              int nbatch, const double *center, int power, int nblk, bool f64, double *partials,
-                              hipStream_t stream);
+// stats[2b], stats[2b + 1] = mean and population variance (FP64) of the w x h
+// region of batch member b: rows of w elements, row_stride apart, starting at
+// x + b * batch_stride.  scratch: moments_scratch_bytes, 8-byte aligned.
+size_t moments_scratch_bytes(int64_t w, int64_t h, int nbatch);
+hipError_t launch_moments(const void *x, int64_t batch_stride, int64_t w, int64_t h, int64_t row_stride, int nbatch,
+                          bool f64, double *stats, void *scratch, hipStream_t stream);
 
 // tab[j] = SF(j + 1/2) exp(i (2 pi a (j - N/2)^2 + pi j)), j < N, with SF the
 // raised-sine window over Lm pixels at each border (Lm = 0: SF = 1); the
@@ -94,8 +90,8 @@ hipError_t launch_low_modes(void *C, void *G, int N, int K, int nbatch, uint32_t
 hipError_t launch_finalize_sums(const double *partials, int nblk, int nbatch, double scale, double *out,
                                 hipStream_t stream);
 
-// grad[i] = 2 (I[i] - It[i]) (if grad != NULL); partials as launch_block_sums
-// of (I - It)^2.
+// grad[i] = 2 (I[i] - It[i]) (if grad != NULL); partials[b * nblk + blk] =
+// sum over block blk's share of batch b of (I - It)^2, FP64.
 hipError_t launch_l2_loss(const void *I, const void *It, void *grad, int64_t n_per_batch, int nbatch,
                           int nblk, bool f64, double *partials, hipStream_t stream);
 

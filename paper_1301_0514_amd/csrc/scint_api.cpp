@@ -2051,6 +2051,25 @@ static int block_count(int64_t n) {
     return (int)std::max<int64_t>(1, std::min<int64_t>(1024, (n + per - 1) / per));
 }
 
+// m (and the mean) of the w x h region from `first` in each of n patterns.
+static int modulation(int N, const void *first, int n, int64_t w, int64_t h, int dtype, double *m_out,
+                      double *mean_out, hipStream_t stream) {
+    void *ws = nullptr;
+    if (int rc = get_workspace(stream, moments_scratch_bytes(w, h, n) + (size_t)n * 16 + 512, &ws)) return rc;
+    Carver c;
+    char *base = static_cast<char *>(ws);
+    double *stats = reinterpret_cast<double *>(base + c.take((size_t)n * 16));
+    HIP_TRY(launch_moments(first, nn(N), w, h, N, n, dtype == PS_F64, stats, base + c.used, stream));
+    std::vector<double> v(2 * (size_t)n);  // mean, variance
+    HIP_TRY(hipMemcpyAsync(v.data(), stats, v.size() * 8, hipMemcpyDeviceToHost, stream));
+    HIP_TRY(hipStreamSynchronize(stream));
+    for (int b = 0; b < n; ++b) {
+        m_out[b] = std::sqrt(v[2 * b + 1]) / v[2 * b];
+        if (mean_out) mean_out[b] = v[2 * b];
+    }
+    return PS_OK;
+}
+
 int ps_modulation_index(int N, const void *I, int n, int dtype, double *m_out, double *mean_out,
                         void *hip_stream) {
     g_last_error.clear();
@@ -2060,29 +2079,7 @@ int ps_modulation_index(int N, const void *I, int n, int dtype, double *m_out, d
     if (int rc = check_aligned({I})) return rc;
     hipStream_t stream = static_cast<hipStream_t>(hip_stream);
     if (int rc = refuse_in_capture(stream, "ps_modulation_index")) return rc;
-    const int64_t per = nn(N);
-    const int nblk = block_count(per);
-    void *ws = nullptr;
-    if (int rc = get_workspace(stream, (size_t)n * nblk * 8 + (size_t)n * 16 + 1024, &ws)) return rc;
-    Carver c;
-    char *base = static_cast<char *>(ws);
-    double *part = reinterpret_cast<double *>(base + c.take((size_t)n * nblk * 8));
-    double *mean = reinterpret_cast<double *>(base + c.take((size_t)n * 8));
-    double *var = reinterpret_cast<double *>(base + c.take((size_t)n * 8));
-    const bool f64 = dtype == PS_F64;
-    HIP_TRY(launch_block_sums(I, per, n, nullptr, 1, nblk, f64, part, stream));
-    HIP_TRY(launch_finalize_sums(part, nblk, n, 1.0 / (double)per, mean, stream));
-    HIP_TRY(launch_block_sums(I, per, n, mean, 2, nblk, f64, part, stream));
-    HIP_TRY(launch_finalize_sums(part, nblk, n, 1.0 / (double)per, var, stream));
-    std::vector<double> hm(n), hv(n);
-    HIP_TRY(hipMemcpyAsync(hm.data(), mean, (size_t)n * 8, hipMemcpyDeviceToHost, stream));
-    HIP_TRY(hipMemcpyAsync(hv.data(), var, (size_t)n * 8, hipMemcpyDeviceToHost, stream));
-    HIP_TRY(hipStreamSynchronize(stream));
-    for (int b = 0; b < n; ++b) {
-        m_out[b] = std::sqrt(hv[b]) / hm[b];
-        if (mean_out) mean_out[b] = hm[b];
-    }
-    return PS_OK;
+    return modulation(N, I, n, N, N, dtype, m_out, mean_out, stream);
 }
 
 int ps_modulation_index_region(int N, const void *I, int n, int x0, int y0, int w, int h, int dtype, double *m_out,
@@ -2096,30 +2093,8 @@ int ps_modulation_index_region(int N, const void *I, int n, int x0, int y0, int 
         return fail(PS_E_PARAM, "the region must be non-empty and lie inside the N x N image");
     hipStream_t stream = static_cast<hipStream_t>(hip_stream);
     if (int rc = refuse_in_capture(stream, "ps_modulation_index_region")) return rc;
-    const int64_t count = (int64_t)w * h;
-    const int nblk = block_count(count);
-    void *ws = nullptr;
-    if (int rc = get_workspace(stream, (size_t)n * nblk * 8 + (size_t)n * 16 + 1024, &ws)) return rc;
-    Carver c;
-    char *base = static_cast<char *>(ws);
-    double *part = reinterpret_cast<double *>(base + c.take((size_t)n * nblk * 8));
-    double *mean = reinterpret_cast<double *>(base + c.take((size_t)n * 8));
-    double *var = reinterpret_cast<double *>(base + c.take((size_t)n * 8));
-    const bool f64 = dtype == PS_F64;
     const char *first = static_cast<const char *>(I) + ((size_t)y0 * N + x0) * real_bytes(dtype);
-    HIP_TRY(launch_region_sums(first, nn(N), w, h, N, n, nullptr, 1, nblk, f64, part, stream));
-    HIP_TRY(launch_finalize_sums(part, nblk, n, 1.0 / (double)count, mean, stream));
-    HIP_TRY(launch_region_sums(first, nn(N), w, h, N, n, mean, 2, nblk, f64, part, stream));
-    HIP_TRY(launch_finalize_sums(part, nblk, n, 1.0 / (double)count, var, stream));
-    std::vector<double> hm(n), hv(n);
-    HIP_TRY(hipMemcpyAsync(hm.data(), mean, (size_t)n * 8, hipMemcpyDeviceToHost, stream));
-    HIP_TRY(hipMemcpyAsync(hv.data(), var, (size_t)n * 8, hipMemcpyDeviceToHost, stream));
-    HIP_TRY(hipStreamSynchronize(stream));
-    for (int b = 0; b < n; ++b) {
-        m_out[b] = std::sqrt(hv[b]) / hm[b];
-        if (mean_out) mean_out[b] = hm[b];
-    }
-    return PS_OK;
+    return modulation(N, first, n, w, h, dtype, m_out, mean_out, stream);
 }
 
 int ps_light_curves(int N, const void *I, int n, const double *lines, int n_lines, int n_samples, int mode,
