@@ -100,47 +100,63 @@ __global__ __launch_bounds__(64) void low_mode_coeff_kernel(double2 *C, LowModeA
         spectrum_coeff_f64(kx, ky, a.N, a.r0 + (uint32_t)b, a.seed_lo, a.seed_hi, a.amp0, a.neg_beta_4);
 }
 
-// G[b][y][k]: one workgroup per (y, b); the W factors exp(2 pi i ky' y / N)
-// (argument reduced exactly in integers) go through LDS, thread k <= K sums
-// B(k) and B(-k) in a fixed order
-__global__ __launch_bounds__(64) void low_mode_rows_kernel(const double2 *__restrict__ C, double2 *__restrict__ G,
-                                                           LowModeArgs a) {
-    __shared__ double2 e[64];
-    const int W = 2 * a.K + 1;
-    const int y = blockIdx.x, b = blockIdx.y, t = threadIdx.x;
-    if (t < W) {
-        int64_t m = ((int64_t)(t - a.K) * y) % a.N;
+// G[b][y][k], k <= K <= 16: a workgroup takes kLowRows rows y, each thread one
+// k of kLowPer of them; the coefficients and the factors exp(2 pi i ky' y / N)
+// (argument reduced exactly in integers) come from LDS, each coefficient once
+// for the thread's rows, and the thread sums B(k) and B(-k) of every row in a
+// fixed order.  Bound by those LDS reads and their latency (a workgroup of 17
+// threads per row, with the coefficients from memory, took 77 us for
+// 16 x 2048 rows).
+constexpr int kLowGroups = 15, kLowPer = 4, kLowRows = kLowGroups * kLowPer, kLowW = 33;
+
+__global__ __launch_bounds__(256) void low_mode_rows_kernel(const double2 *__restrict__ C, double2 *__restrict__ G,
+                                                            LowModeArgs a) {
+    __shared__ double2 c[kLowW * kLowW];
+    __shared__ double2 e[kLowRows][kLowW];
+    const int W = 2 * a.K + 1, K1 = a.K + 1;
+    const int y0 = blockIdx.x * kLowRows, b = blockIdx.y, t = threadIdx.x;
+    const double2 *Cb = C + (int64_t)b * W * W;
+    for (int i = t; i < W * W; i += 256) c[i] = Cb[i];
+    for (int i = t; i < kLowRows * W; i += 256) {
+        const int r = i / W, k = i - r * W;
+        int64_t m = ((int64_t)(k - a.K) * (y0 + r)) % a.N;
         if (m < 0) m += a.N;
         double sn, cs;
         sincospi(2.0 * (double)m / (double)a.N, &sn, &cs);
-        e[t] = make_double2(cs, sn);
+        e[r][k] = make_double2(cs, sn);
     }
     __syncthreads();
-    if (t > a.K) return;
-    const double2 *Cb = C + (int64_t)b * W * W;
-    auto B = [&](int fx) {
-        const double2 *row = Cb + (int64_t)(fx + a.K) * W;
-        double re = 0.0, im = 0.0;
-        for (int j = 0; j < W; ++j) {
-            const double2 c = row[j], w = e[j];
-            re = fma(c.x, w.x, fma(-c.y, w.y, re));
-            im = fma(c.x, w.y, fma(c.y, w.x, im));
+    const int g = t / K1, k = t - g * K1;
+    if (g >= kLowGroups) return;
+    const double2 *up = c + (a.K + k) * W, *down = c + (a.K - k) * W;  // rows kx' = k and -k
+    double2 bp[kLowPer], bm[kLowPer];
+#pragma unroll
+    for (int q = 0; q < kLowPer; ++q) bp[q] = bm[q] = make_double2(0.0, 0.0);
+    for (int j = 0; j < W; ++j) {
+        const double2 u = up[j], v = down[j];
+#pragma unroll
+        for (int q = 0; q < kLowPer; ++q) {
+            const double2 w = e[g * kLowPer + q][j];
+            bp[q].x = fma(u.x, w.x, fma(-u.y, w.y, bp[q].x));
+            bp[q].y = fma(u.x, w.y, fma(u.y, w.x, bp[q].y));
+            bm[q].x = fma(v.x, w.x, fma(-v.y, w.y, bm[q].x));
+            bm[q].y = fma(v.x, w.y, fma(v.y, w.x, bm[q].y));
         }
-        return make_double2(re, im);
-    };
-    constexpr double kSqrt2 = 1.41421356237309504880;
-    const double2 bp = B(t);
-    double2 g = bp;
-    if (t > 0) {
-        const double2 bm = B(-t);
-        g = make_double2(bp.x + bm.x, bp.y - bm.y);
     }
-    G[((int64_t)b * a.N + y) * (a.K + 1) + t] = make_double2(kSqrt2 * g.x, kSqrt2 * g.y);
+    constexpr double kSqrt2 = 1.41421356237309504880;
+#pragma unroll
+    for (int q = 0; q < kLowPer; ++q) {
+        const int y = y0 + g * kLowPer + q;
+        if (y >= a.N) break;
+        double2 s = bp[q];
+        if (k > 0) s = make_double2(s.x + bm[q].x, s.y - bm[q].y);
+        G[((int64_t)b * a.N + y) * K1 + k] = make_double2(kSqrt2 * s.x, kSqrt2 * s.y);
+    }
 }
 
 hipError_t launch_low_modes(void *C, void *G, int N, int K, int nbatch, uint32_t r0, uint32_t seed_lo,
                             uint32_t seed_hi, double amp0, double neg_beta_4, hipStream_t stream, bool swap) {
-    if (K < 0 || 2 * K + 1 > 64 || K >= N / 2 || nbatch < 1) return hipErrorInvalidValue;
+    if (K < 0 || 2 * K + 1 > kLowW || kLowGroups * (K + 1) > 256 || K >= N / 2 || nbatch < 1) return hipErrorInvalidValue;
     const int W = 2 * K + 1;
     for (int b0 = 0; b0 < nbatch; b0 += 65535) {
         const int nb = nbatch - b0 < 65535 ? nbatch - b0 : 65535;
@@ -150,7 +166,7 @@ hipError_t launch_low_modes(void *C, void *G, int N, int K, int nbatch, uint32_t
         hipLaunchKernelGGL(low_mode_coeff_kernel, dim3(W, nb), dim3(64), 0, stream, Cb, a);
         hipError_t e = hipGetLastError();
         if (e != hipSuccess) return e;
-        hipLaunchKernelGGL(low_mode_rows_kernel, dim3(N, nb), dim3(64), 0, stream, Cb, Gb, a);
+        hipLaunchKernelGGL(low_mode_rows_kernel, dim3((N + kLowRows - 1) / kLowRows, nb), dim3(256), 0, stream, Cb, Gb, a);
         e = hipGetLastError();
         if (e != hipSuccess) return e;
     }
