@@ -31,7 +31,7 @@ PROGRAMS = ["ProgNoise", "ProgNoiseSwap", "ProgScreen", "ProgScreenProp", "ProgP
             "ProgRealFwd", "ProgFwdRe", "ProgSmearMid", "ProgInvRe", "ProgVjpY", "ProgVjpX",
             "ProgPropField", "ProgVjpYField", "ProgApertureX", "ProgAbs2"]
 # programs built for float only (their side transposes are complex64)
-PROGRAMS_F32 = ["ProgNoiseT", "ProgNoiseSwapT", "ProgPhasePropT", "ProgPropIntensityT", "ProgRealFwdT", "ProgSmearMidT", "ProgInvReT"]
+PROGRAMS_F32 = ["ProgNoiseT", "ProgNoiseSwapT", "ProgScreenPropT", "ProgApertureXT", "ProgPhasePropT", "ProgPropIntensityT", "ProgRealFwdT", "ProgSmearMidT", "ProgInvReT"]
 
 # gfx950 only; packed FP32 instructions are disabled (the compiler would
 # otherwise form them from float code).

@@ -11,6 +11,10 @@ namespace scint {
 hipError_t launch_transpose(const void *in, void *out, int N, int64_t nbatch, int elem_bytes,
                             hipStream_t stream);
 
+// Units [u0, u1) of that transpose of complex64 matrices (transpose_tile.hpp:
+// matrix, then band of 64 source rows, then 128 source columns).
+hipError_t launch_transpose_units(const void *in, void *out, int N, int64_t u0, int64_t u1, hipStream_t stream);
+
 // tab[j][k] = scale amp[j] exp(-2 pi i a[j] k'^2), k' the signed frequency
 // of k, for j < n (n <= 64); a[j] = pi rho_j^2 / N^2 (turns per k'^2); amp
 // NULL means amp[j] = 1.  The turn count is formed and reduced in FP64 and

@@ -81,6 +81,23 @@ hipError_t launch_transpose(const void *in, void *out, int N, int64_t nbatch, in
     return hipSuccess;
 }
 
+__global__ __launch_bounds__(256) void transpose_units_kernel(const Elem8 *__restrict__ in, Elem8 *__restrict__ out, int N,
+                                                              int64_t u0) {
+    __shared__ TransposeTile<Elem8> tile;
+    const int nx = transpose_units_x(N), ny = transpose_units_y(N);
+    const int64_t u = u0 + blockIdx.x, z = u / ((int64_t)nx * ny);
+    const int rem = (int)(u - z * ((int64_t)nx * ny)), uy = rem / nx, ux = rem - uy * nx;
+    const int64_t base = z * (int64_t)N * N;
+    transpose_unit<Elem8, 256>(in + base, out + base, N, ux, uy, tile, threadIdx.x);
+}
+
+hipError_t launch_transpose_units(const void *in, void *out, int N, int64_t u0, int64_t u1, hipStream_t stream) {
+    if (N % 2 != 0 || u0 < 0 || u1 <= u0 || u1 - u0 > (1ll << 31) - 1) return hipErrorInvalidValue;
+    hipLaunchKernelGGL(transpose_units_kernel, dim3((unsigned)(u1 - u0)), dim3(256), 0, stream,
+                       static_cast<const Elem8 *>(in), static_cast<Elem8 *>(out), N, u0);
+    return hipGetLastError();
+}
+
 // ---------------------------------------------------------------- low modes
 struct LowModeArgs {
     int N, K;

@@ -31,7 +31,7 @@ static hipError_t launch_one(const RowProgram &prog, const void *tw, hipStream_t
     RowProgram p = prog;
     if constexpr (Cfg::IL) {
         // whole sets of 8 XCDs x LINE_GROUPS row groups (row_kernel)
-        const int64_t set = 8 * Cfg::LINE_GROUPS, groups = (prog.total_rows + Cfg::B - 1) / Cfg::B;
+        const int64_t set = 8 * Cfg::LINE_GROUPS, groups = (prog.total_rows - prog.row0 + Cfg::B - 1) / Cfg::B;
         p.iter_split = iter_splittable<SCINT_PROG>() ? std::min(std::max(prog.iter_split, 1), prog.n_iter) : 1;
         const int64_t grid = (groups + set - 1) / set * set * p.iter_split;
         if (grid > (1ll << 31) - 1) return hipErrorInvalidValue;
@@ -41,7 +41,7 @@ static hipError_t launch_one(const RowProgram &prog, const void *tw, hipStream_t
     }
     // two workgroups per row only where the program allows it, the loop has
     // two or more iterations and the row workgroups come in whole eights
-    const int row_wgs = (prog.total_rows + Cfg::B - 1) / Cfg::B;
+    const int row_wgs = (prog.total_rows - prog.row0 + Cfg::B - 1) / Cfg::B;
     p.iter_split = (prog.iter_split == 2 && iter_splittable<SCINT_PROG>() && prog.n_iter >= 2 && row_wgs % 8 == 0)
                        ? 2 : 1;
     const int rows_blocks = row_wgs * p.iter_split;

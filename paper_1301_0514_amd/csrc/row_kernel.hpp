@@ -815,7 +815,7 @@ __attribute__((amdgpu_waves_per_eu(RowCfg<Real, L, V, W>::WAVES_PER_EU))) void r
     int it0 = 0, it1 = prog.n_iter;
     if constexpr (Cfg::IL) {
         // (uniform per workgroup, so the early return comes before any barrier)
-        const int groups = (prog.total_rows + B - 1) / B;
+        const int groups = (prog.total_rows - prog.row0 + B - 1) / B;
         const int parts = iter_splittable<Ops>() ? prog.iter_split : 1;
         const ColumnSlot slot = column_slot(rb, Cfg::LINE_GROUPS, parts);
         rb = slot.group;
@@ -835,14 +835,14 @@ __attribute__((amdgpu_waves_per_eu(RowCfg<Real, L, V, W>::WAVES_PER_EU))) void r
         }
     }
     if constexpr (has_side<Ops>()) {
-        if ((int64_t)rb * B >= prog.total_rows) return;
+        if (prog.row0 + (int64_t)rb * B >= prog.total_rows) return;
     }
     RowState<Real, L, V, W> st;
     st.prog = &prog;
     st.tid = threadIdx.x;
     const int bsub = Cfg::IL ? st.tid % B : st.tid / T;
     st.t = Cfg::IL ? st.tid / B : st.tid - bsub * T;
-    st.g = rb * B + bsub;  // global row over the batch
+    st.g = prog.row0 + rb * B + bsub;  // global row over the batch
     st.valid = st.g < prog.total_rows;
     st.batch = st.valid ? st.g / L : 0;
     st.row = st.valid ? st.g - st.batch * L : 0;
@@ -878,6 +878,8 @@ using ProgNoiseSwapT = OpList<ROP_SIDE_T, ROP_NOISE_SWAP, ROP_FFT_INV, ROP_STORE
 using ProgScreen = OpList<ROP_LOAD_C, ROP_FFT_INV, ROP_SQRT2RE, ROP_STORE_R>;
 using ProgScreenProp = OpList<ROP_LOAD_C, ROP_FFT_INV, ROP_SQRT2RE, ROP_STORE_R, ROP_EXP_RE, ROP_FFT_FWD,
                               ROP_MUL_TAB, ROP_FFT_INV, ROP_STORE_CX>;
+using ProgScreenPropT = OpList<ROP_SIDE_T, ROP_LOAD_C, ROP_FFT_INV, ROP_SQRT2RE, ROP_STORE_R, ROP_EXP_RE, ROP_FFT_FWD,
+                               ROP_MUL_TAB, ROP_FFT_INV, ROP_STORE_CX>;
 // (the phase is re-read for every wavelength: keeping it in registers
 // costs more in occupancy than the cached re-read)
 using ProgPhaseProp = OpList<ROP_LOOP, ROP_LOAD_PHASE, ROP_FFT_FWD, ROP_MUL_TAB, ROP_FFT_INV, ROP_STORE_CX,
@@ -917,6 +919,7 @@ using ProgVjpYField = OpList<ROP_LOAD_C, ROP_MUL_RLOADX, ROP_FFT_FWD, ROP_MUL_TA
 // aperture mode: windowed, chirped exp(i s phi) -> DFT along the row; then
 // DFT along the other axis and |.|^2
 using ProgApertureX = OpList<ROP_LOAD_PHASEX, ROP_MUL_TAB, ROP_MUL_ROWTAB, ROP_FFT_FWD, ROP_STORE_CX>;
+using ProgApertureXT = OpList<ROP_SIDE_T, ROP_LOAD_PHASEX, ROP_MUL_TAB, ROP_MUL_ROWTAB, ROP_FFT_FWD, ROP_STORE_CX>;
 using ProgAbs2 = OpList<ROP_LOAD_C, ROP_FFT_FWD, ROP_ACC_ABS2, ROP_STORE_ACC>;
 
 }  // namespace scint

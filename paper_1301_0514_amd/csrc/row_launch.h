@@ -26,6 +26,8 @@ struct ProgVjpXTag;
 struct ProgApertureXTag;
 struct ProgAbs2Tag;
 struct ProgNoiseTTag;          // complex64 only
+struct ProgScreenPropTTag;     // complex64 only
+struct ProgApertureXTTag;      // complex64 only
 struct ProgNoiseSwapTTag;      // complex64 only
 struct ProgPhasePropTTag;     // complex64 only
 struct ProgPropIntensityTTag;  // complex64 only

@@ -122,7 +122,8 @@ struct RowProgram {
     RowSide side;
     int32_t n_iter;      // iterations of the loop range (>= 1)
     int32_t N;           // row length (= grid size)
-    int32_t total_rows;  // batch * N
+    int32_t row0;        // first row (over the batch) of this launch
+    int32_t total_rows;  // row after its last one (batch * N, or less)
     int32_t r0;          // realisation of batch 0 (ROP_NOISE)
     uint32_t seed_lo, seed_hi;
     double amp0;         // sqrt(C_beta R^(2-beta)) N^(beta/2) / N   (ROP_NOISE)
