@@ -43,12 +43,17 @@ constexpr bool plan_ok(int L, int E, const int *R, int ns) {
 // expands a size list given through another macro
 #define SCINT_PLAN_EXPAND(...) SCINT_PLAN(__VA_ARGS__)
 
+// Rows up to 256 are calls that last as long as one thread's serial work, not
+// as the chip's rates ask: few elements per thread (and more exchanges) spread
+// a grid over more waves.  One FP64 256^2 screen + pattern 45 us with 16
+// elements per thread ({16,16}), 27 with 8 ({8,8,4}), 23 with 4; twelve FP32
+// ones 49, 44 and 43 us.
 // powers of two
 SCINT_PLAN(16, 16, 16)
 SCINT_PLAN(32, 8, 8, 4)
-SCINT_PLAN(64, 8, 8, 8)
-SCINT_PLAN(128, 16, 16, 8)
-SCINT_PLAN(256, 16, 16, 16)
+SCINT_PLAN(64, 4, 4, 4, 4)
+SCINT_PLAN(128, 8, 8, 4, 4)
+SCINT_PLAN(256, 4, 4, 4, 4, 4)
 SCINT_PLAN(512, 8, 8, 8, 8)
 SCINT_PLAN(1024, 16, 16, 16, 4)
 SCINT_PLAN(2048, 16, 16, 16, 8)
@@ -57,10 +62,10 @@ SCINT_PLAN(8192, 32, 32, 8, 32)
 SCINT_PLAN(16384, 32, 32, 32, 16)
 // 2^a 5^b
 SCINT_PLAN(40, 20, 4, 10)
-SCINT_PLAN(80, 20, 4, 20)
+SCINT_PLAN(80, 10, 10, 2, 2, 2)
 SCINT_PLAN(100, 10, 10, 10)
 SCINT_PLAN(160, 20, 4, 4, 10)
-SCINT_PLAN(200, 20, 20, 10)
+SCINT_PLAN(200, 10, 10, 10, 2)
 SCINT_PLAN(320, 20, 4, 4, 20)
 SCINT_PLAN(400, 20, 20, 20)
 SCINT_PLAN(640, 20, 4, 4, 4, 10)
