@@ -145,6 +145,13 @@ template <int L, int V> constexpr int exch_buffer_length(int elem_bytes, int row
 constexpr int kColumnsMaxL = 4096;
 constexpr bool stores_columns(int L) { return L <= kColumnsMaxL; }
 
+// The smear's middle pass keeps a second row in its registers, which four rows
+// of 4000 in one workgroup leave no room for: its passes keep the transposes
+// from 4000 on (8 x 4000^2 x 4 disks: 2.93 ms by columns, 2.69 with them; 2560:
+// 0.92 and 1.11).
+constexpr int kSmearColumnsMaxL = 2560;
+constexpr bool smear_columns(int L) { return L <= kSmearColumnsMaxL; }
+
 // Real arrays are read and written by columns too while they stay in cache;
 // above, runs half as long cost more than their transpose (2048: 140 us more
 // in a pass over 16 patterns, transpose 84-104 us).

@@ -21,9 +21,11 @@ namespace scint {
 template <int L, int V>
 static hipError_t launch_one(const RowProgram &prog, const void *tw, hipStream_t stream) {
     using Cfg = RowCfg<SCINT_REAL, L, V, program_rows<SCINT_REAL, L, V, SCINT_PROG>()>;
-    // sizes that store by columns need no transposes beside their passes, and
-    // only those of real_columns take phase screens by columns
-    constexpr bool wanted = !(stores_columns(L) && has_side<SCINT_PROG>()) &&
+    // passes that store by columns need no transposes beside them, and only the
+    // sizes of real_columns take phase screens by columns
+    constexpr bool smear = std::is_same<SCINT_PROG, ProgSmearFwdT>::value ||
+                           std::is_same<SCINT_PROG, ProgSmearMidT>::value || std::is_same<SCINT_PROG, ProgInvReT>::value;
+    constexpr bool wanted = !(has_side<SCINT_PROG>() && (smear ? smear_columns(L) : stores_columns(L))) &&
                             (real_columns(L) || !std::is_same<SCINT_PROG, ProgPhasePropX>::value);
     if constexpr (!wanted) {
         return hipErrorInvalidValue;

@@ -898,14 +898,16 @@ using ProgPhasePropT = OpList<ROP_SIDE_T, ROP_LOOP, ROP_LOAD_PHASE, ROP_FFT_FWD,
 using ProgPropIntensityT = OpList<ROP_SIDE_T, ROP_LOOP, ROP_LOAD_C, ROP_FFT_FWD, ROP_MUL_TAB, ROP_FFT_INV,
                                   ROP_ACC_ABS2U, ROP_ENDLOOP, ROP_STORE_ACC>;
 using ProgRealFwd = OpList<ROP_LOAD_R, ROP_FFT_FWD, ROP_STORE_CX>;
+using ProgSmearFwd = OpList<ROP_LOAD_R, ROP_FFT_FWD, ROP_STORE_CXS>;
 using ProgFwdRe = OpList<ROP_LOAD_C, ROP_FFT_FWD, ROP_STORE_R>;
 using ProgSmearMid = OpList<ROP_LOAD_C, ROP_FFT_FWD, ROP_SAVE, ROP_LOOP, ROP_RESTORE, ROP_MUL_RTAB2D,
-                            ROP_FFT_INV, ROP_STORE_CX, ROP_ENDLOOP>;
+                            ROP_FFT_INV, ROP_STORE_CXS, ROP_ENDLOOP>;
 using ProgInvRe = OpList<ROP_LOAD_C, ROP_FFT_INV, ROP_STORE_R>;
 // the three smear passes carrying transposes of other data (RowSide)
 using ProgRealFwdT = OpList<ROP_SIDE_T, ROP_LOAD_R, ROP_FFT_FWD, ROP_STORE_CX>;
+using ProgSmearFwdT = OpList<ROP_SIDE_T, ROP_LOAD_R, ROP_FFT_FWD, ROP_STORE_CXS>;
 using ProgSmearMidT = OpList<ROP_SIDE_T, ROP_LOAD_C, ROP_FFT_FWD, ROP_SAVE, ROP_LOOP, ROP_RESTORE, ROP_MUL_RTAB2D,
-                             ROP_FFT_INV, ROP_STORE_CX, ROP_ENDLOOP>;
+                             ROP_FFT_INV, ROP_STORE_CXS, ROP_ENDLOOP>;
 using ProgInvReT = OpList<ROP_SIDE_T, ROP_LOAD_C, ROP_FFT_INV, ROP_STORE_R>;
 using ProgVjpY = OpList<ROP_LOAD_C, ROP_FFT_FWD, ROP_MUL_TAB, ROP_FFT_INV, ROP_MUL_RLOADX, ROP_FFT_FWD,
                         ROP_MUL_TAB, ROP_FFT_INV, ROP_STORE_CX>;

@@ -16,6 +16,7 @@ struct ProgPhasePropTag;
 struct ProgPhasePropXTag;  // sizes of real_columns only
 struct ProgPropIntensityTag;
 struct ProgRealFwdTag;
+struct ProgSmearFwdTag;
 struct ProgFwdReTag;
 struct ProgSmearMidTag;
 struct ProgInvReTag;
@@ -32,6 +33,7 @@ struct ProgNoiseSwapTTag;      // complex64 only
 struct ProgPhasePropTTag;     // complex64 only
 struct ProgPropIntensityTTag;  // complex64 only
 struct ProgRealFwdTTag;        // complex64 only
+struct ProgSmearFwdTTag;       // complex64 only
 struct ProgSmearMidTTag;       // complex64 only
 struct ProgInvReTTag;          // complex64 only
 

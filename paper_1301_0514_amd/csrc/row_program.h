@@ -54,6 +54,7 @@ enum RowOpCode : int32_t {
     // e pitch + row; pitch N, or field_pitch for complex fields).  At other
     // sizes the host transposes and these are the plain ones.
     ROP_STORE_CX,     // ROP_STORE_C
+    ROP_STORE_CXS,    // ROP_STORE_C, at the sizes of smear_columns
     ROP_LOAD_PHASEX,  // ROP_LOAD_PHASE
     ROP_MUL_RLOADX,   // ROP_MUL_RLOAD
     ROP_STORE_ACCX,   // ROP_STORE_ACC
@@ -61,11 +62,11 @@ enum RowOpCode : int32_t {
 
 // the operation an ...X code does, and whether it is one at size L
 constexpr int32_t rop_plain(int32_t c) {
-    return c == ROP_STORE_CX ? ROP_STORE_C : c == ROP_LOAD_PHASEX ? ROP_LOAD_PHASE
+    return c == ROP_STORE_CX || c == ROP_STORE_CXS ? ROP_STORE_C : c == ROP_LOAD_PHASEX ? ROP_LOAD_PHASE
          : c == ROP_MUL_RLOADX ? ROP_MUL_RLOAD : c == ROP_STORE_ACCX ? ROP_STORE_ACC : c;
 }
 constexpr bool lies_across(int32_t c, int L) {
-    return c != rop_plain(c) && (c == ROP_STORE_CX ? stores_columns(L) : real_columns(L));
+    return c == ROP_STORE_CX ? stores_columns(L) : c == ROP_STORE_CXS ? smear_columns(L) : c != rop_plain(c) && real_columns(L);
 }
 
 // Flag bits

@@ -409,6 +409,7 @@ SCINT_PROG_NAME(ProgPhaseProp)
 SCINT_PROG_NAME(ProgPhasePropX)
 SCINT_PROG_NAME(ProgPropIntensity)
 SCINT_PROG_NAME(ProgRealFwd)
+SCINT_PROG_NAME(ProgSmearFwd)
 SCINT_PROG_NAME(ProgFwdRe)
 SCINT_PROG_NAME(ProgSmearMid)
 SCINT_PROG_NAME(ProgInvRe)
@@ -425,6 +426,7 @@ SCINT_PROG_NAME(ProgNoiseSwapT)
 SCINT_PROG_NAME(ProgPhasePropT)
 SCINT_PROG_NAME(ProgPropIntensityT)
 SCINT_PROG_NAME(ProgRealFwdT)
+SCINT_PROG_NAME(ProgSmearFwdT)
 SCINT_PROG_NAME(ProgSmearMidT)
 SCINT_PROG_NAME(ProgInvReT)
 #undef SCINT_PROG_NAME
@@ -1868,7 +1870,7 @@ static void set_side(RowSide &sd, const SmearSide &t, const SideCfg &sc) {
 // the passes in any precision, without side transposes
 static int smear_rf_any(int N, int dtype, const SmearJob &j, hipStream_t stream) {
     ProgBuilder a = smear_rf_prog(N, j, (size_t)nn(N) * real_bytes(dtype), false);
-    return run_row<ProgRealFwdTag>(dtype, N, a.p, a.n, stream);
+    return run_row<ProgSmearFwdTag>(dtype, N, a.p, a.n, stream);
 }
 static int smear_mid_any(int N, int dtype, const SmearJob &j, const void *D, int n_r, hipStream_t stream) {
     ProgBuilder b = smear_mid_prog(N, j, D, n_r, false);
@@ -1883,7 +1885,7 @@ static int smear_rf(int N, const SmearJob &j, const SmearSide *t, const SideCfg 
     if (!t) return smear_rf_any(N, PS_F32, j, stream);
     ProgBuilder a = smear_rf_prog(N, j, (size_t)nn(N) * 4, true);
     set_side(a.p.side, *t, sc);
-    return run_row_side<ProgRealFwdTTag>(N, a.p, a.n, stream);
+    return run_row_side<ProgSmearFwdTTag>(N, a.p, a.n, stream);
 }
 static int smear_mid(int N, const SmearJob &j, const void *D, int n_r, const SmearSide *t, const SideCfg &sc,
                      hipStream_t stream) {
@@ -1919,8 +1921,9 @@ int source_smear(int N, double delta, const void *I_in, const double *radii, int
     for (int j = 0; j < n_r; ++j) rpx[j] = radii[j] / delta;
     const void *D = nullptr;
     if (int rc = get_disk_spectra(N, rpx, dtype, stream, &D)) return rc;
-    const size_t cbytes = field_bytes(N, dtype);
-    const int64_t fe = field_elems(N, dtype), fr = field_row(N, dtype);
+    const bool cols = smear_columns(N);
+    const int64_t fr = cols ? field_row(N, dtype) : N, fe = fr * N;
+    const size_t cbytes = (size_t)fe * 2 * real_bytes(dtype);
     const size_t budget = workspace_budget();
     const int nb_max = (int)std::max<size_t>(1, budget / (cbytes * (2 + 2 * (size_t)n_r)));
     // The disk kernel is real, so two real patterns a and b ride in one
@@ -1944,7 +1947,6 @@ int source_smear(int N, double delta, const void *I_in, const double *radii, int
             const char *Iin = static_cast<const char *>(I_in) + (size_t)(b0 + pb) * rb1;
             // I_out[b][r]: transform q holds realisations b0 + pb + step q (and + 1)
             char *Iout = static_cast<char *>(I_out) + (size_t)(b0 + pb) * n_r * rb1;
-            const bool cols = stores_columns(N);
             SmearJob all{fe, fr, Iin, Iout, np, step, W1, cols ? W1 : W2, V1, cols ? V1 : V2};
             if (dtype == PS_F32 && N >= 2048 && np >= 2 && sc.on && !cols) {
                 // two jobs, the transposes of each riding on the other's passes
