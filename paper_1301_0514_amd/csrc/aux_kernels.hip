@@ -103,18 +103,20 @@ struct LowModeArgs {
     int N, K;
     uint32_t r0, seed_lo, seed_hi;
     double amp0, neg_beta_4;
-    int swap;  // C[b][i][j] = c(kx' = j - K, ky' = i - K) instead
+    int swap;  // the coefficients' kx' and ky' change places
+    // chirp table built by the launch's last workgroups (chirp_value), or NULL
+    cpx<float> *tab;
+    double chirp_a, chirp_scale;
+    int blocks;  // workgroups of the low modes, all screens
 };
 
-// C[b][i][j]: one workgroup per (i, b), thread j
-__global__ __launch_bounds__(64) void low_mode_coeff_kernel(double2 *C, LowModeArgs a) {
-    const int W = 2 * a.K + 1;
-    const int i = blockIdx.x, b = blockIdx.y, j = threadIdx.x;
-    if (j >= W) return;
-    const int fx = (a.swap ? j : i) - a.K, fy = (a.swap ? i : j) - a.K;
-    const int kx = fx < 0 ? fx + a.N : fx, ky = fy < 0 ? fy + a.N : fy;
-    C[((int64_t)b * W + i) * W + j] =
-        spectrum_coeff_f64(kx, ky, a.N, a.r0 + (uint32_t)b, a.seed_lo, a.seed_hi, a.amp0, a.neg_beta_4);
+// scale exp(-2 pi i a k'^2), the turns formed and reduced in FP64
+template <typename Real> __device__ __forceinline__ cpx<Real> chirp_value(int k, int N, double a, double scale) {
+    const double kk = (double)(k < N / 2 ? k : k - N);
+    const double turns = a * (kk * kk);
+    double s, c;
+    sincospi(2.0 * (turns - rint(turns)), &s, &c);
+    return {(Real)(scale * c), (Real)(-scale * s)};
 }
 
 // G[b][y][k], k <= K <= 16: a workgroup takes kLowRows rows y, each thread one
@@ -123,20 +125,37 @@ __global__ __launch_bounds__(64) void low_mode_coeff_kernel(double2 *C, LowModeA
 // for the thread's rows, and the thread sums B(k) and B(-k) of every row in a
 // fixed order.  Bound by those LDS reads and their latency (a workgroup of 17
 // threads per row, with the coefficients from memory, took 77 us for
-// 16 x 2048 rows).
-constexpr int kLowGroups = 15, kLowPer = 4, kLowRows = kLowGroups * kLowPer, kLowW = 33;
+// 16 x 2048 rows).  Every workgroup draws the (2K + 1)^2 coefficients itself,
+// four or five per thread, and the call's chirp table is built by further
+// workgroups of the launch: one launch instead of three (one FP32 256^2 screen
+// + pattern 31.9 -> 28.4 us).  NT 1024 (one row per
+// thread) where the grids have few rows, so that the drawing, one coefficient
+// after the other, does not make the call wait; 256 and four rows else.
+constexpr int kLowRows = 60, kLowW = 33;
 
-__global__ __launch_bounds__(256) void low_mode_rows_kernel(const double2 *__restrict__ C, double2 *__restrict__ G,
-                                                            LowModeArgs a) {
+template <int NT>
+__global__ __launch_bounds__(NT) void low_modes_kernel(double2 *__restrict__ G, LowModeArgs a) {
+    constexpr int kLowGroups = NT / (kLowW / 2 + 1), kLowPer = kLowRows / kLowGroups;
+    static_assert(kLowGroups * kLowPer == kLowRows, "rows of a workgroup");
     __shared__ double2 c[kLowW * kLowW];
     __shared__ double2 e[kLowRows][kLowW];
+    const int t = threadIdx.x;
+    if ((int)blockIdx.x >= a.blocks) {
+        const int k = ((int)blockIdx.x - a.blocks) * NT + t;
+        if (k < a.N) a.tab[k] = chirp_value<float>(k, a.N, a.chirp_a, a.chirp_scale);
+        return;
+    }
     const int W = 2 * a.K + 1, K1 = a.K + 1;
-    const int y0 = blockIdx.x * kLowRows, b = blockIdx.y, t = threadIdx.x;
-    const double2 *Cb = C + (int64_t)b * W * W;
-    for (int i = t; i < W * W; i += 256) c[i] = Cb[i];
-    for (int i = t; i < kLowRows * W; i += 256) {
+    const int per = (a.N + kLowRows - 1) / kLowRows, b = (int)blockIdx.x / per, y0 = ((int)blockIdx.x - b * per) * kLowRows;
+    for (int i = t; i < W * W; i += NT) {
+        const int p = i / W, q = i - p * W;
+        const int fx = (a.swap ? q : p) - a.K, fy = (a.swap ? p : q) - a.K;
+        c[i] = spectrum_coeff_f64(fx < 0 ? fx + a.N : fx, fy < 0 ? fy + a.N : fy, a.N, a.r0 + (uint32_t)b, a.seed_lo,
+                                  a.seed_hi, a.amp0, a.neg_beta_4);
+    }
+    for (int i = t; i < kLowRows * W; i += NT) {
         const int r = i / W, k = i - r * W;
-        int64_t m = ((int64_t)(k - a.K) * (y0 + r)) % a.N;
+        int m = (k - a.K) * (y0 + r) % a.N;  // (|k - K| <= 16: the product fits)
         if (m < 0) m += a.N;
         double sn, cs;
         sincospi(2.0 * (double)m / (double)a.N, &sn, &cs);
@@ -171,23 +190,25 @@ __global__ __launch_bounds__(256) void low_mode_rows_kernel(const double2 *__res
     }
 }
 
-hipError_t launch_low_modes(void *C, void *G, int N, int K, int nbatch, uint32_t r0, uint32_t seed_lo,
-                            uint32_t seed_hi, double amp0, double neg_beta_4, hipStream_t stream, bool swap) {
-    if (K < 0 || 2 * K + 1 > kLowW || kLowGroups * (K + 1) > 256 || K >= N / 2 || nbatch < 1) return hipErrorInvalidValue;
-    const int W = 2 * K + 1;
-    for (int b0 = 0; b0 < nbatch; b0 += 65535) {
-        const int nb = nbatch - b0 < 65535 ? nbatch - b0 : 65535;
-        LowModeArgs a{N, K, r0 + (uint32_t)b0, seed_lo, seed_hi, amp0, neg_beta_4, swap ? 1 : 0};
-        double2 *Cb = static_cast<double2 *>(C) + (int64_t)b0 * W * W;
-        double2 *Gb = static_cast<double2 *>(G) + (int64_t)b0 * N * (K + 1);
-        hipLaunchKernelGGL(low_mode_coeff_kernel, dim3(W, nb), dim3(64), 0, stream, Cb, a);
-        hipError_t e = hipGetLastError();
-        if (e != hipSuccess) return e;
-        hipLaunchKernelGGL(low_mode_rows_kernel, dim3((N + kLowRows - 1) / kLowRows, nb), dim3(256), 0, stream, Cb, Gb, a);
-        e = hipGetLastError();
-        if (e != hipSuccess) return e;
-    }
-    return hipSuccess;
+hipError_t launch_low_modes(void *G, int N, int K, int nbatch, uint32_t r0, uint32_t seed_lo, uint32_t seed_hi,
+                            double amp0, double neg_beta_4, hipStream_t stream, bool swap, void *chirp_tab,
+                            double chirp_a, double chirp_scale) {
+    if (K < 0 || 2 * K + 1 > kLowW || K >= N / 2 || nbatch < 1) return hipErrorInvalidValue;
+    const int per = (N + kLowRows - 1) / kLowRows;
+    const int64_t blocks = (int64_t)per * nbatch;
+    const bool small = blocks <= 256;  // one per CU
+    const int nt = small ? 1024 : 256;
+    const int64_t chirp = chirp_tab ? (N + nt - 1) / nt : 0;
+    if (blocks + chirp > (1ll << 31) - 1) return hipErrorInvalidValue;
+    LowModeArgs a{N, K, r0, seed_lo, seed_hi, amp0, neg_beta_4, swap ? 1 : 0, static_cast<cpx<float> *>(chirp_tab),
+                  chirp_a, chirp_scale, (int)blocks};
+    if (small)
+        hipLaunchKernelGGL((low_modes_kernel<1024>), dim3((unsigned)(blocks + chirp)), dim3(1024), 0, stream,
+                           static_cast<double2 *>(G), a);
+    else
+        hipLaunchKernelGGL((low_modes_kernel<256>), dim3((unsigned)(blocks + chirp)), dim3(256), 0, stream,
+                           static_cast<double2 *>(G), a);
+    return hipGetLastError();
 }
 
 // ---------------------------------------------------------------- twiddles
@@ -242,13 +263,7 @@ __global__ __launch_bounds__(256) void chirp_kernel(cpx<Real> *tab, int N, Chirp
     const int k = blockIdx.x * 256 + threadIdx.x;
     const int j = blockIdx.y;
     if (k >= N || j >= n) return;
-    const double kk = (double)(k < N / 2 ? k : k - N);
-    const double turns = args.a[j] * (kk * kk);
-    const double f = turns - rint(turns);
-    double s, c;
-    sincospi(2.0 * f, &s, &c);
-    const double g = scale * args.amp[j];
-    tab[(int64_t)j * N + k] = {(Real)(g * c), (Real)(-g * s)};
+    tab[(int64_t)j * N + k] = chirp_value<Real>(k, N, args.a[j], scale * args.amp[j]);
 }
 
 hipError_t launch_chirp_tables(void *tab, int N, const double *a, int n, double scale, bool f64,

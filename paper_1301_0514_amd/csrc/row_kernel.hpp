@@ -657,7 +657,7 @@ __device__ __forceinline__ void exec_op(RowState<Real, L, V, W> &st, const RowOp
             }
         }
     } else if constexpr (CODE == ROP_ACC_ABS2) {
-        const Real w = (Real)((op.flags & RF_ITER_WEIGHT) ? st.prog->weight[st.it] : op.param);
+        const Real w = (Real)op.param;
 #pragma unroll
         for (int m = 0; m < E; ++m) st.acc[m] += w * (v[m].re * v[m].re + v[m].im * v[m].im);
     } else if constexpr (CODE == ROP_ACC_ABS2U) {

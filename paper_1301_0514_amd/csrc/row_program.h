@@ -36,7 +36,7 @@ enum RowOpCode : int32_t {
     ROP_EXP_RE,      // v = exp(i s Re v); FP32: exp(i s (Re v + Im v)), the sum in FP64
     ROP_STORE_C,     // dst[e] = v
     ROP_STORE_R,     // dst[e] = param * Re v
-    ROP_ACC_ABS2,    // acc += w |v|^2
+    ROP_ACC_ABS2,    // acc += param |v|^2
     ROP_STORE_ACC,   // dst[e] = acc   (flag 1: dst[e] += acc)
     ROP_SAVE,        // keepc = v
     ROP_RESTORE,     // v = keepc
@@ -74,7 +74,6 @@ enum : int32_t {
     RF_CONJ = 1,       // ROP_MUL_TAB: multiply by the conjugate
     RF_ADD = 1,        // ROP_STORE_ACC: accumulate into dst
     RF_ITER_SCALE = 2, // phase scale s = scale[it] (else param)
-    RF_ITER_WEIGHT = 4, // ROP_ACC_ABS2: w = weight[it] (else param)
     RF_PAIR = 8         // ROP_LOAD_R: v = (src[e], ptr2[e]); ROP_STORE_R: dst[e] = Re, ptr2[e] = Im
 };
 
@@ -92,7 +91,7 @@ struct RowOp {
     double param;
 };
 
-constexpr int kRowMaxOps = 20;
+constexpr int kRowMaxOps = 12;
 constexpr int kRowMaxIter = 64;
 
 // Half-width of the square of lowest Fourier modes, |kx'|, |ky'| <= K, that
@@ -130,7 +129,6 @@ struct RowProgram {
     double amp0;         // sqrt(C_beta R^(2-beta)) N^(beta/2) / N   (ROP_NOISE)
     double neg_beta_4;   // -beta/4                                 (ROP_NOISE)
     double scale[kRowMaxIter];
-    double weight[kRowMaxIter];
     // 1, or 2: each row is taken by two workgroups, 8 apart in launch order
     // (one XCD, dispatched together), the first doing the loop's first
     // ceil(n_iter/2) iterations and the second the rest, so that per-row

@@ -12,6 +12,7 @@
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
+#include <cassert>
 #include <cmath>
 #include <cstdint>
 #include <cstdio>
@@ -319,13 +320,11 @@ struct ProgBuilder {
         p.N = N;
         p.total_rows = (int32_t)total_rows;
         p.n_iter = 1;
-        for (int i = 0; i < kRowMaxIter; ++i) {
-            p.scale[i] = 1.0;
-            p.weight[i] = 1.0;
-        }
+        for (int i = 0; i < kRowMaxIter; ++i) p.scale[i] = 1.0;
     }
     ProgBuilder &op(int code, const void *ptr = nullptr, int64_t batch_stride = 0, int64_t row_stride = 0,
                     int64_t iter_stride = 0, int flags = 0, double param = 0.0, void *ptr2 = nullptr) {
+        assert(n < kRowMaxOps);
         RowOp &o = p.op[n++];
         o.code = code;
         o.ptr = ptr;
@@ -677,8 +676,7 @@ int64_t nn(int N) { return (int64_t)N * N; }
 // Workspace of the FP64 low-mode tables of nb FP32 screens (0 for FP64).
 size_t low_mode_bytes(int N, int nb, int dtype) {
     if (dtype != PS_F32) return 0;
-    const size_t K = (size_t)low_modes_k_of(N), W = 2 * K + 1;
-    return (size_t)nb * ((size_t)N * (K + 1) + W * W) * 16 + 512;
+    return (size_t)nb * N * ((size_t)low_modes_k_of(N) + 1) * 16 + 512;
 }
 
 // The FP64 low modes of FP32 screens r0 .. r0 + nb - 1 (Sect. 3.1): the FP32
@@ -687,19 +685,18 @@ size_t low_mode_bytes(int N, int nb, int dtype) {
 // row table built here at `tab` (low_mode_bytes of workspace), to the
 // screen.  Sets p.low_k and p.low_tab of that pass (nothing for FP64).  With
 // swap the table serves screens made transposed ([b][x][y]; screen_passes
-// with swap).
+// with swap).  With H the launch also builds the chirp table of rho there (in
+// FP64 a launch of its own).
 int low_mode_pass(RowProgram &p, int N, double R, double beta, uint64_t seed, uint32_t r0, int nb, int dtype,
-                  void *tab, hipStream_t stream, bool swap) {
-    if (dtype != PS_F32) return PS_OK;
+                  void *tab, hipStream_t stream, bool swap, void *H = nullptr, double rho = 0.0) {
+    if (dtype != PS_F32) return H ? chirp_tables(H, N, {rho}, dtype, true, stream) : PS_OK;
     RowProgram q;
     std::memset(&q, 0, sizeof(q));
     set_noise(q, N, R, beta, seed, r0, dtype);
-    const int K = q.low_k;
-    char *G = static_cast<char *>(tab);
-    char *C = G + (size_t)nb * N * (K + 1) * 16;
-    HIP_TRY(launch_low_modes(C, G, N, K, nb, r0, q.seed_lo, q.seed_hi, q.amp0, q.neg_beta_4, stream, swap));
-    p.low_k = K;
-    p.low_tab = G;
+    HIP_TRY(launch_low_modes(tab, N, q.low_k, nb, r0, q.seed_lo, q.seed_hi, q.amp0, q.neg_beta_4, stream, swap, H,
+                             kPiD * rho * rho / ((double)N * (double)N), 1.0 / N));
+    p.low_k = q.low_k;
+    p.low_tab = tab;
     return PS_OK;
 }
 
@@ -1120,7 +1117,6 @@ int ps_screen_fresnel(int N, double delta, double r_diff, double beta, uint64_t 
         void *W3 = buffers > 2 ? base + c.take(cbytes * nb) : nullptr;
         void *H = base + c.take(tbytes);
         void *LT = base + c.take(low_mode_bytes(N, nb, dtype));
-        if (int rc = chirp_tables(H, N, {rho}, dtype, true, stream)) return rc;
         // Without the screen and the field to return, the screens are made
         // transposed ([b][x][y]: the first pass along kx), the first
         // propagation pass runs along y and the second along x, so that the
@@ -1134,7 +1130,7 @@ int ps_screen_fresnel(int N, double delta, double r_diff, double beta, uint64_t 
         char *phi = phi_out ? static_cast<char *>(phi_out) + (size_t)b0 * nn(N) * real_bytes(dtype) : nullptr;
         RowProgram low;
         std::memset(&low, 0, sizeof(low));
-        if (int rc = low_mode_pass(low, N, r_diff / delta, beta, seed, r0, nb, dtype, LT, stream, swap)) return rc;
+        if (int rc = low_mode_pass(low, N, r_diff / delta, beta, seed, r0, nb, dtype, LT, stream, swap, H, rho)) return rc;
         auto build = [&](ProgBuilder &b) {
             b.p.low_k = low.low_k;
             b.p.low_tab = low.low_tab;
