@@ -28,7 +28,7 @@ LIB = os.path.join(LIBDIR, "libscint.so")
 HIPCC = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
 
 PROGRAMS = ["ProgNoise", "ProgNoiseSwap", "ProgScreen", "ProgScreenProp", "ProgPhaseProp", "ProgPhasePropX", "ProgPropIntensity",
-            "ProgRealFwd", "ProgSmearFwd", "ProgFwdRe", "ProgSmearMid", "ProgInvRe", "ProgVjpY", "ProgVjpX",
+            "ProgRealFwd", "ProgSmearFwd", "ProgFwdRe", "ProgSmearMid", "ProgInvRe", "ProgInvReL", "ProgVjpY", "ProgVjpX",
             "ProgPropField", "ProgVjpYField", "ProgApertureX", "ProgAbs2"]
 # programs built for float only (their side transposes are complex64)
 PROGRAMS_F32 = ["ProgNoiseT", "ProgNoiseSwapT", "ProgScreenPropT", "ProgApertureXT", "ProgPhasePropT", "ProgPropIntensityT", "ProgRealFwdT", "ProgSmearFwdT", "ProgSmearMidT", "ProgInvReT"]

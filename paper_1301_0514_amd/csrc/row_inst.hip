@@ -44,8 +44,11 @@ static hipError_t launch_one(const RowProgram &prog, const void *tw, hipStream_t
     // two workgroups per row only where the program allows it, the loop has
     // two or more iterations and the row workgroups come in whole eights
     const int row_wgs = (prog.total_rows - prog.row0 + Cfg::B - 1) / Cfg::B;
-    p.iter_split = (prog.iter_split == 2 && iter_splittable<SCINT_PROG>() && prog.n_iter >= 2 && row_wgs % 8 == 0)
-                       ? 2 : 1;
+    p.iter_split = !iter_splittable<SCINT_PROG>() || prog.n_iter < 2   ? 1
+                   : prog.iter_split > 2 && !has_side<SCINT_PROG>()     ? std::min(prog.iter_split, prog.n_iter)
+                   : prog.iter_split >= 2 && row_wgs % 8 == 0           ? 2
+                                                                        : 1;
+    if (p.iter_split == 2 && row_wgs % 8 != 0) p.iter_split = 1;
     const int rows_blocks = row_wgs * p.iter_split;
     if constexpr (has_side<SCINT_PROG>()) {
         // groups of fft_blocks row workgroups and side_blocks transpose

@@ -543,7 +543,7 @@ __device__ __forceinline__ void exec_op(RowState<Real, L, V, W> &st, const RowOp
         }
     } else if constexpr (CODE == ROP_LOAD_R) {
         const Real *src = static_cast<const Real *>(op.ptr) + off;
-        if (op.flags & RF_PAIR) {  // two real rows as one complex row
+        if ((op.flags & RF_PAIR) && st.batch < st.prog->pairs) {  // two real rows as one complex row
             const Real *src2 = static_cast<const Real *>(op.ptr2) + off;
 #pragma unroll
             for (int m = 0; m < E; ++m) v[m] = {src[m * T], src2[m * T]};
@@ -650,7 +650,7 @@ __device__ __forceinline__ void exec_op(RowState<Real, L, V, W> &st, const RowOp
             const Real sc = (Real)op.param;
 #pragma unroll
             for (int m = 0; m < E; ++m) dst[m * T] = sc * v[m].re;
-            if (op.flags & RF_PAIR) {  // the imaginary part to the second row
+            if ((op.flags & RF_PAIR) && st.batch < st.prog->pairs) {  // the imaginary part to the second row
                 Real *dst2 = static_cast<Real *>(op.ptr2) + off;
 #pragma unroll
                 for (int m = 0; m < E; ++m) dst2[m * T] = sc * v[m].im;
@@ -746,7 +746,7 @@ template <class Ops> constexpr bool iter_splittable() {
     for (++i; i < Ops::n && Ops::code[i] != ROP_ENDLOOP; ++i) {
         const int c = Ops::code[i];
         if (c != ROP_LOAD_PHASE && c != ROP_LOAD_PHASEX && c != ROP_LOAD_C && c != ROP_FFT_FWD && c != ROP_FFT_INV && c != ROP_MUL_TAB &&
-            c != ROP_STORE_C && c != ROP_STORE_CX)
+            c != ROP_STORE_C && c != ROP_STORE_CX && c != ROP_STORE_R)
             return false;
     }
     return i == Ops::n - 1;
@@ -832,6 +832,11 @@ __attribute__((amdgpu_waves_per_eu(RowCfg<Real, L, V, W>::WAVES_PER_EU))) void r
             const int h = (prog.n_iter + 1) / 2;
             it0 = half ? h : 0;
             it1 = half ? prog.n_iter : h;
+        } else if (prog.iter_split > 2) {
+            const int h = (prog.n_iter + prog.iter_split - 1) / prog.iter_split;
+            it0 = min(rb % prog.iter_split * h, prog.n_iter);
+            it1 = min(it0 + h, prog.n_iter);
+            rb /= prog.iter_split;
         }
     }
     if constexpr (has_side<Ops>()) {
@@ -903,6 +908,8 @@ using ProgFwdRe = OpList<ROP_LOAD_C, ROP_FFT_FWD, ROP_STORE_R>;
 using ProgSmearMid = OpList<ROP_LOAD_C, ROP_FFT_FWD, ROP_SAVE, ROP_LOOP, ROP_RESTORE, ROP_MUL_RTAB2D,
                             ROP_FFT_INV, ROP_STORE_CXS, ROP_ENDLOOP>;
 using ProgInvRe = OpList<ROP_LOAD_C, ROP_FFT_INV, ROP_STORE_R>;
+// several radii
+using ProgInvReL = OpList<ROP_LOOP, ROP_LOAD_C, ROP_FFT_INV, ROP_STORE_R, ROP_ENDLOOP>;
 // the three smear passes carrying transposes of other data (RowSide)
 using ProgRealFwdT = OpList<ROP_SIDE_T, ROP_LOAD_R, ROP_FFT_FWD, ROP_STORE_CX>;
 using ProgSmearFwdT = OpList<ROP_SIDE_T, ROP_LOAD_R, ROP_FFT_FWD, ROP_STORE_CXS>;

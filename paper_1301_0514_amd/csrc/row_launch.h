@@ -20,6 +20,7 @@ struct ProgSmearFwdTag;
 struct ProgFwdReTag;
 struct ProgSmearMidTag;
 struct ProgInvReTag;
+struct ProgInvReLTag;
 struct ProgVjpYTag;
 struct ProgPropFieldTag;
 struct ProgVjpYFieldTag;

@@ -129,12 +129,14 @@ struct RowProgram {
     double amp0;         // sqrt(C_beta R^(2-beta)) N^(beta/2) / N   (ROP_NOISE)
     double neg_beta_4;   // -beta/4                                 (ROP_NOISE)
     double scale[kRowMaxIter];
+    int32_t pairs;       // RF_PAIR: batches that hold two rows (the others one, its imaginary part 0)
     // 1, or 2: each row is taken by two workgroups, 8 apart in launch order
     // (one XCD, dispatched together), the first doing the loop's first
     // ceil(n_iter/2) iterations and the second the rest, so that per-row
     // operands re-read in every iteration are fetched by both from one L2.
-    // Only for programs whose iterations are independent; the launcher
-    // falls back to 1 where it does not apply (the results are the same).
+    // More: that many workgroups, next to each other.  Only for programs whose
+    // iterations are independent; the launcher falls back to 1 where it does
+    // not apply (the results are the same).
     int32_t iter_split;
     // FP32 screens: ROP_NOISE leaves out the Fourier modes with |kx'|,
     // |ky'| <= low_k (low_modes_k_of(N); 0 in every other program and in

@@ -320,6 +320,7 @@ struct ProgBuilder {
         p.N = N;
         p.total_rows = (int32_t)total_rows;
         p.n_iter = 1;
+        p.pairs = INT32_MAX;
         for (int i = 0; i < kRowMaxIter; ++i) p.scale[i] = 1.0;
     }
     ProgBuilder &op(int code, const void *ptr = nullptr, int64_t batch_stride = 0, int64_t row_stride = 0,
@@ -412,6 +413,7 @@ SCINT_PROG_NAME(ProgSmearFwd)
 SCINT_PROG_NAME(ProgFwdRe)
 SCINT_PROG_NAME(ProgSmearMid)
 SCINT_PROG_NAME(ProgInvRe)
+SCINT_PROG_NAME(ProgInvReL)
 SCINT_PROG_NAME(ProgVjpY)
 SCINT_PROG_NAME(ProgPropField)
 SCINT_PROG_NAME(ProgVjpYField)
@@ -1808,7 +1810,7 @@ struct SmearJob {
     int64_t fe, fr;  // elements of a complex field and of its rows
     const char *Iin;
     char *Iout;
-    int np, step;
+    int np, step, pairs;  // transforms, realisations per transform, transforms that hold two
     char *W1, *W2, *V1, *V2;
 };
 // transposes [u0, u1) of complex64 matrices in -> out, carried by a pass
@@ -1821,6 +1823,7 @@ struct SmearSide {
 static ProgBuilder smear_rf_prog(int N, const SmearJob &j, size_t rb1, bool side) {
     const bool pair = j.step == 2;
     ProgBuilder a(N, (int64_t)j.np * N);
+    a.p.pairs = j.pairs;
     if (side) a.op(ROP_SIDE_T);
     a.op(ROP_LOAD_R, j.Iin, (int64_t)j.step * nn(N), N, 0, pair ? RF_PAIR : 0, 0.0,
          pair ? const_cast<char *>(j.Iin) + rb1 : nullptr)
@@ -1843,16 +1846,24 @@ static ProgBuilder smear_mid_prog(int N, const SmearJob &j, const void *D, int n
         .op(ROP_ENDLOOP);
     return b;
 }
-static ProgBuilder smear_ir_prog(int N, const SmearJob &j, int r, int n_r, size_t rb1, bool side) {
+// radii r .. r + m - 1 (m = 1 with side transposes)
+static ProgBuilder smear_ir_prog(int N, const SmearJob &j, int r, int m, int n_r, size_t rb1, bool side) {
     const bool pair = j.step == 2;
     const size_t cbytes = (size_t)j.fe * 2 * (rb1 / nn(N));
     ProgBuilder d(N, (int64_t)j.np * N);
+    d.p.pairs = j.pairs;
     char *dst = j.Iout + (size_t)r * rb1;
-    if (side) d.op(ROP_SIDE_T);
-    d.op(ROP_LOAD_C, j.V2 + (size_t)r * cbytes, (int64_t)n_r * j.fe, j.fr)
+    if (side)
+        d.op(ROP_SIDE_T);
+    else if (m > 1)
+        d.op(ROP_LOOP);
+    d.p.n_iter = m;
+    d.p.iter_split = m;
+    d.op(ROP_LOAD_C, j.V2 + (size_t)r * cbytes, (int64_t)n_r * j.fe, j.fr, j.fe)
         .op(ROP_FFT_INV)
-        .op(ROP_STORE_R, dst, (int64_t)j.step * n_r * nn(N), N, 0, pair ? RF_PAIR : 0, 1.0,
+        .op(ROP_STORE_R, dst, (int64_t)j.step * n_r * nn(N), N, nn(N), pair ? RF_PAIR : 0, 1.0,
             pair ? dst + (size_t)n_r * rb1 : nullptr);
+    if (m > 1) d.op(ROP_ENDLOOP);
     return d;
 }
 static void set_side(RowSide &sd, const SmearSide &t, const SideCfg &sc) {
@@ -1872,9 +1883,9 @@ static int smear_mid_any(int N, int dtype, const SmearJob &j, const void *D, int
     ProgBuilder b = smear_mid_prog(N, j, D, n_r, false);
     return run_row<ProgSmearMidTag>(dtype, N, b.p, b.n, stream);
 }
-static int smear_ir_any(int N, int dtype, const SmearJob &j, int r, int n_r, hipStream_t stream) {
-    ProgBuilder d = smear_ir_prog(N, j, r, n_r, (size_t)nn(N) * real_bytes(dtype), false);
-    return run_row<ProgInvReTag>(dtype, N, d.p, d.n, stream);
+static int smear_ir_any(int N, int dtype, const SmearJob &j, int r, int m, int n_r, hipStream_t stream) {
+    ProgBuilder d = smear_ir_prog(N, j, r, m, n_r, (size_t)nn(N) * real_bytes(dtype), false);
+    return m > 1 ? run_row<ProgInvReLTag>(dtype, N, d.p, d.n, stream) : run_row<ProgInvReTag>(dtype, N, d.p, d.n, stream);
 }
 // FP32 passes carrying the transposes `t` (none if NULL)
 static int smear_rf(int N, const SmearJob &j, const SmearSide *t, const SideCfg &sc, hipStream_t stream) {
@@ -1892,8 +1903,8 @@ static int smear_mid(int N, const SmearJob &j, const void *D, int n_r, const Sme
 }
 static int smear_ir(int N, const SmearJob &j, int r, int n_r, const SmearSide *t, const SideCfg &sc,
                     hipStream_t stream) {
-    if (!t) return smear_ir_any(N, PS_F32, j, r, n_r, stream);
-    ProgBuilder d = smear_ir_prog(N, j, r, n_r, (size_t)nn(N) * 4, true);
+    if (!t) return smear_ir_any(N, PS_F32, j, r, 1, n_r, stream);
+    ProgBuilder d = smear_ir_prog(N, j, r, 1, n_r, (size_t)nn(N) * 4, true);
     set_side(d.p.side, *t, sc);
     return run_row_side<ProgInvReTTag>(N, d.p, d.n, stream);
 }
@@ -1924,7 +1935,9 @@ int source_smear(int N, double delta, const void *I_in, const double *radii, int
     const int nb_max = (int)std::max<size_t>(1, budget / (cbytes * (2 + 2 * (size_t)n_r)));
     // The disk kernel is real, so two real patterns a and b ride in one
     // complex transform: (a + i b) * d = a * d + i (b * d).  Realisations are
-    // paired; an odd last one goes alone (imaginary part zero).
+    // paired; an odd last one goes alone (imaginary part zero), in the launches
+    // of the pairs, and one launch inverts all radii (5 x 1280^2 x 3 disks, the
+    // last pattern and every radius in launches of their own: 165 us)
     for (int b0 = 0; b0 < n_real; b0 += nb_max) {
         const int nb = std::min(nb_max, n_real - b0);
         void *ws = nullptr;
@@ -1938,18 +1951,22 @@ int source_smear(int N, double delta, const void *I_in, const double *radii, int
         const SideCfg sc = side_cfg();
         for (int pb = 0; pb < nb;) {
             const bool pair = nb - pb >= 2;
-            const int np = pair ? (nb - pb) / 2 : 1;  // complex transforms in this group
-            const int step = pair ? 2 : 1;            // realisations per transform
+            const int pairs = pair ? (nb - pb) / 2 : 0;
+            // the pipelined jobs take pairs only; the other passes an odd last
+            // realisation too, as a pair whose second is zero
+            const bool piped = dtype == PS_F32 && N >= 2048 && pairs >= 2 && sc.on && !cols;
+            const int np = piped ? pairs : (nb - pb + 1) / 2;  // complex transforms in this group
+            const int step = pair ? 2 : 1;                     // realisations per transform
             const char *Iin = static_cast<const char *>(I_in) + (size_t)(b0 + pb) * rb1;
             // I_out[b][r]: transform q holds realisations b0 + pb + step q (and + 1)
             char *Iout = static_cast<char *>(I_out) + (size_t)(b0 + pb) * n_r * rb1;
-            SmearJob all{fe, fr, Iin, Iout, np, step, W1, cols ? W1 : W2, V1, cols ? V1 : V2};
-            if (dtype == PS_F32 && N >= 2048 && np >= 2 && sc.on && !cols) {
+            SmearJob all{fe, fr, Iin, Iout, np, step, pairs, W1, cols ? W1 : W2, V1, cols ? V1 : V2};
+            if (piped) {
                 // two jobs, the transposes of each riding on the other's passes
                 const int q0 = (np + 1) / 2;
-                const SmearJob j0{fe, fr, Iin, Iout, q0, step, W1, W2, V1, V2};
+                const SmearJob j0{fe, fr, Iin, Iout, q0, step, q0, W1, W2, V1, V2};
                 const size_t o = (size_t)q0 * cbytes;  // offset of job 1 in the complex buffers
-                const SmearJob j1{fe, fr, Iin + (size_t)q0 * step * rb1, Iout + (size_t)q0 * step * n_r * rb1, np - q0, step,
+                const SmearJob j1{fe, fr, Iin + (size_t)q0 * step * rb1, Iout + (size_t)q0 * step * n_r * rb1, np - q0, step, np - q0,
                                   W1 + o, W2 + o, V1 + o * n_r, V2 + o * n_r};
                 const int64_t upm = (int64_t)transpose_units_x(N) * transpose_units_y(N);
                 const SmearSide t1_0{j0.W1, j0.W2, 0, upm * j0.np}, t1_1{j1.W1, j1.W2, 0, upm * j1.np};
@@ -1963,8 +1980,7 @@ int source_smear(int N, double delta, const void *I_in, const double *radii, int
                     const SmearSide t2_1{j1.V1, j1.V2, U2 * r / n_r, U2 * (r + 1) / n_r};
                     if (int rc = smear_ir(N, j0, r, n_r, t2_1.u1 > t2_1.u0 ? &t2_1 : nullptr, sc, stream)) return rc;
                 }
-                for (int r = 0; r < n_r; ++r)
-                    if (int rc = smear_ir(N, j1, r, n_r, nullptr, sc, stream)) return rc;
+                if (int rc = smear_ir_any(N, PS_F32, j1, 0, n_r, n_r, stream)) return rc;
             } else {
                 if (int rc = smear_rf_any(N, dtype, all, stream)) return rc;
                 if (!cols)
@@ -1972,10 +1988,9 @@ int source_smear(int N, double delta, const void *I_in, const double *radii, int
                 if (int rc = smear_mid_any(N, dtype, all, D, n_r, stream)) return rc;
                 if (!cols)
                     if (int rc = transpose(V1, V2, N, (int64_t)np * n_r, 2 * (int)real_bytes(dtype), stream)) return rc;
-                for (int r = 0; r < n_r; ++r)
-                    if (int rc = smear_ir_any(N, dtype, all, r, n_r, stream)) return rc;
+                if (int rc = smear_ir_any(N, dtype, all, 0, n_r, n_r, stream)) return rc;
             }
-            pb += np * step;
+            pb += piped ? np * step : nb - pb;
         }
     }
     return PS_OK;
