@@ -2228,9 +2228,9 @@ int ps_structure_function(int N, double delta, const void *phi, int n, const dou
         char *base = static_cast<char *>(ws);
         void *W1 = base + c.take(cbytes * nb);
         void *W2 = base + c.take(cbytes * nb);
-        double *S = reinterpret_cast<double *>(base + c.take((size_t)nb * nbins * 8));
-        double *D = reinterpret_cast<double *>(base + c.take((size_t)nb * std::max(n_r, 1) * 8));
-        double *R = reinterpret_cast<double *>(base + c.take((size_t)nb * 8));
+        // the results, next to each other for one copy to the host: R, D, S
+        const size_t nR = nb, nD = (size_t)nb * n_r, nS = (size_t)nb * nbins;
+        double *R = reinterpret_cast<double *>(base + c.take((nR + nD + nS) * 8)), *D = R + nR, *S = D + nD;
         void *scratch = base + c.take(hankel_scratch_bytes(nb));
         void *rings = base + c.take(ring_scratch_bytes(N, nb));
         const char *ph = static_cast<const char *>(phi) + (size_t)b0 * nn(N) * real_bytes(dtype);
@@ -2250,15 +2250,15 @@ int ps_structure_function(int N, double delta, const void *phi, int n, const dou
         HIP_TRY(launch_ring_sums(P, N, nb, dtype == PS_F64, S, rings, stream));
         if (n_r > 0 || rdiff_out)
             HIP_TRY(launch_hankel(S, N, nb, rpx.data(), n_r, D, rdiff_out ? R : nullptr, scratch, stream));
-        std::vector<double> hS(S_out ? (size_t)nb * nbins : 0), hD((size_t)nb * n_r), hR(rdiff_out ? nb : 0);
-        if (S_out) HIP_TRY(hipMemcpyAsync(hS.data(), S, hS.size() * 8, hipMemcpyDeviceToHost, stream));
-        if (n_r > 0) HIP_TRY(hipMemcpyAsync(hD.data(), D, hD.size() * 8, hipMemcpyDeviceToHost, stream));
-        if (rdiff_out) HIP_TRY(hipMemcpyAsync(hR.data(), R, hR.size() * 8, hipMemcpyDeviceToHost, stream));
+        std::vector<double> h(nR + nD + (S_out ? nS : 0));
+        if (rdiff_out || n_r > 0 || S_out)
+            HIP_TRY(hipMemcpyAsync(h.data(), R, h.size() * 8, hipMemcpyDeviceToHost, stream));
         HIP_TRY(hipStreamSynchronize(stream));
         // physical units: S in (length unit)^2 rad^2, R_diff^rec in the length unit
-        for (size_t i = 0; i < hS.size(); ++i) S_out[(size_t)b0 * nbins + i] = hS[i] * delta * delta;
-        for (size_t i = 0; i < hD.size(); ++i) D_out[(size_t)b0 * n_r + i] = hD[i];
-        for (int i = 0; i < (int)hR.size(); ++i) {
+        const double *hR = h.data(), *hD = hR + nR, *hS = hD + nD;
+        for (size_t i = 0; S_out && i < nS; ++i) S_out[(size_t)b0 * nbins + i] = hS[i] * delta * delta;
+        for (size_t i = 0; i < nD; ++i) D_out[(size_t)b0 * n_r + i] = hD[i];
+        for (int i = 0; rdiff_out && i < nb; ++i) {
             rdiff_out[b0 + i] = hR[i] * delta;
             if (!std::isfinite(hR[i])) g_last_warning = "D_rec = 1 is not reached between 1e-3 and N/2 pixels";
         }

@@ -425,8 +425,7 @@ def ps_modulation_index(I: torch.Tensor, want_mean=False):
     rc = load_library().ps_modulation_index(int(N), _ptr(I), n, _dtype_code(I.dtype), m, mean,
                                             _stream(I.device))
     _check("ps_modulation_index", rc)
-    ms = [m[i] for i in range(n)]
-    return (ms, [mean[i] for i in range(n)]) if want_mean else ms
+    return (m[:], mean[:]) if want_mean else m[:]
 
 
 def ps_modulation_index_region(I: torch.Tensor, x0: int, y0: int, w: int, h: int, want_mean=False):
@@ -439,8 +438,7 @@ def ps_modulation_index_region(I: torch.Tensor, x0: int, y0: int, w: int, h: int
     rc = load_library().ps_modulation_index_region(int(N), _ptr(I), n, int(x0), int(y0), int(w), int(h),
                                                    _dtype_code(I.dtype), m, mean, _stream(I.device))
     _check("ps_modulation_index_region", rc)
-    ms = [m[i] for i in range(n)]
-    return (ms, [mean[i] for i in range(n)]) if want_mean else ms
+    return (m[:], mean[:]) if want_mean else m[:]
 
 
 def light_curves(I: torch.Tensor, lines, n_samples: int, mode: int = 0, want_m: bool = True):
@@ -461,7 +459,7 @@ def light_curves(I: torch.Tensor, lines, n_samples: int, mode: int = 0, want_m: 
     _check("ps_light_curves", rc)
     if not want_m:
         return curves
-    return curves, [[m[b * n_lines + l] for l in range(n_lines)] for b in range(n)]
+    return curves, [m[b * n_lines:(b + 1) * n_lines] for b in range(n)]
 
 
 def structure_function(phi: torch.Tensor, delta, radii=(), want_spectrum=False):
@@ -478,10 +476,11 @@ def structure_function(phi: torch.Tensor, delta, radii=(), want_spectrum=False):
     rc = load_library().ps_structure_function(int(N), float(delta), _ptr(phi), n, r if nr else None, nr,
                                               _dtype_code(phi.dtype), S, D if nr else None, R, _stream(phi.device))
     _check("ps_structure_function", rc)
-    Ds = [[D[b * nr + j] for j in range(nr)] for b in range(n)]
-    Rs = [R[b] for b in range(n)]
+    Ds = [D[b * nr:(b + 1) * nr] for b in range(n)]
+    Rs = R[:]
     if want_spectrum:
-        return Ds, Rs, [[S[b * (N // 2 + 1) + k] for k in range(N // 2 + 1)] for b in range(n)]
+        w = N // 2 + 1
+        return Ds, Rs, [S[b * w:(b + 1) * w] for b in range(n)]
     return Ds, Rs
 
 
