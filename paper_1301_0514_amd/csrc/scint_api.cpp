@@ -2,8 +2,9 @@
 // validation, per-device caches (twiddle tables, disk spectra), per-stream
 // workspace, and the sequence of passes behind each entry point.
 //
-// Every 2-D transform is a row pass, a batched transpose and a second row
-// pass; the pointwise steps of the method are fused into the row passes:
+// Every 2-D transform is two row passes, with an exchange T between them: up
+// to 4096 the first pass's own stores by columns, above a batched transpose.
+// The pointwise steps of the method are fused into the row passes:
 //   screen:      [noise -> IDFT along ky] T [IDFT along kx -> sqrt2 Re]
 //   propagation: [exp(i s phi) -> DFT_x -> H1 -> IDFT_x] T
 //                [DFT_y -> H1 -> IDFT_y -> |.|^2 (sum over wavelengths)] T
@@ -1315,9 +1316,8 @@ static int poly_pipelined(int N, const char *phi_ref, const std::vector<PolyJob>
 // Jobs of the pipelined propagation (FP32): up to 64 wavelengths and as many
 // realisations per job as four complex buffers of the job's grids fit the
 // budget; work that fits one job is split in two (realisations, else
-// wavelengths): two pipelined jobs beat one plain job by ~10 % at 2048^2 and
-// 4096^2 (8 realisations x 32 wavelengths), more jobs than the memory needs do
-// not gain further.  False if the work does not make two jobs or one job does
+// wavelengths); more jobs than the memory needs do not gain further.  Used
+// above 4096 only: below, the passes store by columns and need no transposes.  False if the work does not make two jobs or one job does
 // not fit.
 static bool plan_poly_jobs(int N, int n_real, int n_lambda, size_t budget, std::vector<PolyJob> *jobs, int *Cp_out,
                            int *nbp_out) {
