@@ -226,6 +226,18 @@ int get_workspace(hipStream_t stream, size_t bytes, void **out) {
     return PS_OK;
 }
 
+// Whether the stream's workspace has `bytes`, or may grow to them in the free
+// device memory (never while the stream is captured).
+bool workspace_can_hold(hipStream_t stream, size_t bytes) {
+    int dev = 0;
+    if (hipGetDevice(&dev) != hipSuccess) return false;
+    std::lock_guard<std::mutex> lock(g_mutex);
+    const size_t have = g_cache[dev].workspace[stream].second;
+    if (have >= bytes) return true;
+    size_t free_b = 0, total_b = 0;
+    return !capturing(stream) && hipMemGetInfo(&free_b, &total_b) == hipSuccess && bytes <= have + free_b;
+}
+
 // Carves aligned sub-buffers out of one workspace allocation.
 struct Carver {
     size_t used = 0;
@@ -781,7 +793,7 @@ static SideCfg side_cfg() {
 // A pass over nb grids whose complex result goes to `from`, and the exchange
 // that hands it to the pass along the other axis (*next: `from` or `to`, which
 // must hold no operand of the pass).  build(p) appends the pass's operations.
-// In FP32 at the sizes with transposes the rows run in up to screen_jobs blocks
+// In FP32 at the sizes with transposes the rows run in row_blocks() blocks
 // of whole 64-row bands: the pass over block k carries the transpose of block
 // k - 1 as extra workgroups (the FFTs' arithmetic leaves memory bandwidth
 // free), and only the last block's runs on its own.  One 10000^2 screen +
@@ -789,11 +801,18 @@ static SideCfg side_cfg() {
 // whose launches no longer fill the chip to their end.  Each element is
 // computed by the same kernel code either way, so the results do not depend on
 // the blocks.
+//
+// With blocks = 1 the whole pass comes first, and `to` may hold its operand.
+int row_blocks(int N, int dtype) {
+    const SideCfg sc = side_cfg();
+    return (dtype == PS_F32 && sc.on && !stores_columns(N)) ? sc.screen_jobs : 1;
+}
 template <class Tag, class TagT, class Build>
-int pass_exchange(int N, int nb, int dtype, void *from, void *to, void **next, hipStream_t stream, Build build) {
+int pass_exchange(int N, int nb, int dtype, int blocks, void *from, void *to, void **next, hipStream_t stream,
+                  Build build) {
     const SideCfg sc = side_cfg();
     const int64_t nx = transpose_units_x(N), ny = transpose_units_y(N), bands = ny * nb;
-    const int J = (dtype == PS_F32 && sc.on && !stores_columns(N)) ? sc.screen_jobs : 1;
+    const int J = blocks;
     if (J == 1) {
         ProgBuilder p(N, (int64_t)nb * N);
         build(p);
@@ -837,8 +856,8 @@ int screen_passes(int N, double R, double beta, uint64_t seed, uint32_t r0, int 
             .op(ROP_FFT_INV)
             .op(ROP_STORE_C, W1, field_elems(N, dtype), field_row(N, dtype));
     };
-    return swap ? pass_exchange<ProgNoiseSwapTag, ProgNoiseSwapTTag>(N, nb, dtype, W1, W2, next, stream, build)
-                : pass_exchange<ProgNoiseTag, ProgNoiseTTag>(N, nb, dtype, W1, W2, next, stream, build);
+    return swap ? pass_exchange<ProgNoiseSwapTag, ProgNoiseSwapTTag>(N, nb, dtype, row_blocks(N, dtype), W1, W2, next, stream, build)
+                : pass_exchange<ProgNoiseTag, ProgNoiseTTag>(N, nb, dtype, row_blocks(N, dtype), W1, W2, next, stream, build);
 }
 
 // Second propagation pass of nb screens on the exchanged field W: DFT,
@@ -1103,16 +1122,19 @@ int ps_screen_fresnel(int N, double delta, double r_diff, double beta, uint64_t 
     const double rho = std::sqrt(lambda * z / (2.0 * kPiD)) / delta;
     const size_t cbytes = field_bytes(N, dtype);
     const size_t tbytes = (size_t)N * 2 * real_bytes(dtype);
-    // the second pass's transpose rides on the pass itself, whose operand it
-    // must leave alone: a third buffer
-    const size_t buffers = stores_columns(N) ? 2 : 3;
-    const int nb_max = (int)std::max<size_t>(1, workspace_budget() / (buffers * cbytes));
+    // Where transposes ride on the second pass, it must leave its operand alone
+    // and a third buffer takes them: if the budget and the memory hold three.
+    // With two, the second pass runs in one block and its transpose replaces
+    // its operand.
+    const bool ride = row_blocks(N, dtype) > 1 && 3 * cbytes <= workspace_budget();
+    const int nb_max = (int)std::max<size_t>(1, workspace_budget() / ((ride ? 3 : 2) * cbytes));
     for (int b0 = 0; b0 < n_real; b0 += nb_max) {
         const int nb = std::min(nb_max, n_real - b0);
         const uint32_t r0 = first_realisation + (uint32_t)b0;
         void *ws = nullptr;
-        if (int rc = get_workspace(stream, buffers * cbytes * nb + tbytes + low_mode_bytes(N, nb, dtype) + 1536, &ws))
-            return rc;
+        const size_t rest = tbytes + low_mode_bytes(N, nb, dtype) + 1536;
+        const int buffers = ride && workspace_can_hold(stream, 3 * cbytes * nb + rest) ? 3 : 2;
+        if (int rc = get_workspace(stream, buffers * cbytes * nb + rest, &ws)) return rc;
         Carver c;
         char *base = static_cast<char *>(ws);
         void *W1 = base + c.take(cbytes * nb);
@@ -1147,11 +1169,14 @@ int ps_screen_fresnel(int N, double delta, double r_diff, double beta, uint64_t 
                 .op(ROP_FFT_INV)
                 .op(ROP_STORE_C, X, field_elems(N, dtype), field_row(N, dtype));
         };
-        if (int rc = pass_exchange<ProgScreenPropTag, ProgScreenPropTTag>(N, nb, dtype, X, W3, &A, stream, build)) return rc;
+        const int blocks = W3 ? row_blocks(N, dtype) : 1;
+        if (int rc = pass_exchange<ProgScreenPropTag, ProgScreenPropTTag>(N, nb, dtype, blocks, X, W3 ? W3 : S, &A,
+                                                                          stream, build))
+            return rc;
         char *F = field_out ? static_cast<char *>(field_out) + (size_t)b0 * nn(N) * 2 * real_bytes(dtype) : nullptr;
         char *I = static_cast<char *>(I_out) + (size_t)b0 * nn(N) * real_bytes(dtype);
         const int rc = swap ? prop_pass(N, dtype, nb, A, H, I, stream)
-                            : prop_y_pass(N, dtype, nb, A, H, S, I, F, stream);
+                            : prop_y_pass(N, dtype, nb, A, H, A == S ? X : S, I, F, stream);
         if (rc) return rc;
     }
     return PS_OK;
@@ -1188,7 +1213,7 @@ static int poly_chunk(int N, const void *phi, int nb, const std::vector<double> 
                              : run_row<ProgPhasePropTag>(dtype, N, a.p, a.n, stream))
             return rc;
         if (int rc = exchange(W1, W2, N, (int64_t)nb * C, dtype, &A, stream)) return rc;
-    } else if (int rc = pass_exchange<ProgPhasePropTag, ProgPhasePropTTag>(N, nb, dtype, W1, W2, &A, stream, build)) {
+    } else if (int rc = pass_exchange<ProgPhasePropTag, ProgPhasePropTTag>(N, nb, dtype, row_blocks(N, dtype), W1, W2, &A, stream, build)) {
         return rc;
     }
     ProgBuilder b(N, (int64_t)nb * N);
@@ -1504,7 +1529,7 @@ int fresnel_propagate_field(int N, double delta, double lambda, double z, const 
                 .op(ROP_ENDLOOP);
         };
         void *A = nullptr;
-        if (int rc = pass_exchange<ProgPhasePropTag, ProgPhasePropTTag>(N, nb, dtype, W1, W2, &A, stream, build)) return rc;
+        if (int rc = pass_exchange<ProgPhasePropTag, ProgPhasePropTTag>(N, nb, dtype, row_blocks(N, dtype), W1, W2, &A, stream, build)) return rc;
         char *F = static_cast<char *>(field_out) + (size_t)b0 * nn(N) * 2 * real_bytes(dtype);
         char *I = static_cast<char *>(I_out) + (size_t)b0 * nn(N) * real_bytes(dtype);
         if (int rc = prop_y_pass(N, dtype, nb, A, H, A == W1 ? W2 : W1, I, F, stream)) return rc;
@@ -1558,7 +1583,7 @@ int fresnel_aperture(int N, double delta, double lambda, double z, const void *p
                 .op(ROP_STORE_C, W1, field_elems(N, dtype), field_row(N, dtype));
         };
         void *G = nullptr;
-        if (int rc = pass_exchange<ProgApertureXTag, ProgApertureXTTag>(N, nb, dtype, W1, W2, &G, stream, build)) return rc;
+        if (int rc = pass_exchange<ProgApertureXTag, ProgApertureXTTag>(N, nb, dtype, row_blocks(N, dtype), W1, W2, &G, stream, build)) return rc;
         // rows kx: DFT along y, |.|^2 / (2 pi rho^2)^2 (transposed intensity in
         // the buffer that is free)
         char *I = static_cast<char *>(I_out) + (size_t)b0 * nn(N) * real_bytes(dtype);
@@ -2239,7 +2264,7 @@ int ps_structure_function(int N, double delta, const void *phi, int n, const dou
             a.op(ROP_LOAD_R, ph, nn(N), N).op(ROP_FFT_FWD).op(ROP_STORE_C, W1, field_elems(N, dtype), field_row(N, dtype));
         };
         void *F = nullptr;
-        if (int rc = pass_exchange<ProgRealFwdTag, ProgRealFwdTTag>(N, nb, dtype, W1, W2, &F, stream, build)) return rc;
+        if (int rc = pass_exchange<ProgRealFwdTag, ProgRealFwdTTag>(N, nb, dtype, row_blocks(N, dtype), W1, W2, &F, stream, build)) return rc;
         void *P = F == W1 ? W2 : W1;
         ProgBuilder d(N, (int64_t)nb * N);
         d.op(ROP_LOAD_C, F, field_elems(N, dtype), field_row(N, dtype))

@@ -1,0 +1,66 @@
+"""Device memory that a call's workspace takes, from the free memory before and
+after its first call: no more field buffers than the passes use, and no more
+than the budget where a single grid fits it with fewer.  What a call holds
+beside its fields (tables, chirps, low modes) is a few per cent of one.
+"""
+import numpy as np
+import pytest
+import torch
+
+pytestmark = pytest.mark.gpu
+
+LAM = 5e-7
+MiB = 1 << 20
+
+
+@pytest.fixture(scope="module")
+def S():
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    from paper_1301_0514_amd import scint
+    scint.load_library()
+    return scint
+
+
+def taken(S, call, budget=0):
+    """Workspace of call() in bytes, and its result; the arrays that torch
+    allocates for it are in its cache already."""
+    keep = call()
+    torch.cuda.synchronize()
+    del keep
+    S.release_cache()
+    if budget:
+        S.set_workspace_budget(budget)
+    before = torch.cuda.mem_get_info()[0]
+    out = call()
+    torch.cuda.synchronize()
+    used = before - torch.cuda.mem_get_info()[0]
+    S.release_cache()
+    return used, out
+
+
+# a screen of 5000^2 has fields of 191 MiB in FP32 and 381 MiB in FP64; the
+# call takes three where the second pass carries transposes, else two
+@pytest.mark.parametrize("dtype,env,budget,fields", [
+    (torch.float32, {}, 0, 3), (torch.float32, {"SCINT_PIPELINE": "0"}, 0, 2),
+    (torch.float32, {"SCINT_SCREEN_JOBS": "1"}, 0, 2), (torch.float32, {}, 500 * MiB, 2),
+    (torch.float64, {}, 0, 2)])
+@pytest.mark.parametrize("n,phi", [(2, False), (2, True)])
+def test_screen_fresnel_fields(S, monkeypatch, dtype, env, budget, fields, n, phi):
+    N = 5000
+    monkeypatch.setenv("SCINT_PLAN_VARIANT", "0")
+    z = N / LAM
+
+    def call():
+        return S.ps_screen_fresnel(N, 1.0, 20.0, 11 / 3, 5, LAM, z, n_real=n, dtype=dtype, want_phi=phi)
+
+    ref = call()
+    for k, v in env.items():
+        monkeypatch.setenv(k, v)
+    used, out = taken(S, call, budget)
+    chunk = 1 if budget else n
+    field = N * N * (8 if dtype == torch.float32 else 16)
+    print("fields", used / (field * chunk))
+    assert used < (fields + 0.5) * field * chunk
+    for a, b in zip(out if phi else (out,), ref if phi else (ref,)):
+        assert torch.equal(a, b)
