@@ -646,6 +646,14 @@ int exchange(void *from, void *to, int N, int64_t nbatch, int dtype, void **next
     return transpose(from, to, N, nbatch, 2 * (int)real_bytes(dtype), stream);
 }
 
+// Bytes per screen of the second buffer of a call with one field: at the sizes
+// that store by columns nothing but the transposed pattern goes there (nothing
+// at all at those of real_columns), else the exchanged field.
+size_t second_bytes(int N, int dtype) {
+    const size_t pattern = (size_t)N * N * real_bytes(dtype);
+    return !stores_columns(N) ? field_bytes(N, dtype) : real_columns(N) ? 0 : pattern;
+}
+
 // Chirp tables H1(k)/N for n wavelengths with Fresnel radii rho[j] pixels.
 // amp (optional, one per wavelength) multiplies each table.
 int chirp_tables(void *tab, int N, const std::vector<double> &rho, int dtype, bool normalise, hipStream_t stream,
@@ -1079,16 +1087,17 @@ int ps_generate(int N, double delta, double r_diff, double beta, uint64_t seed, 
     if (delta >= r_diff / 2.0) g_last_warning = "pixel side >= R_diff/2: the phase variations are undersampled";
     hipStream_t stream = static_cast<hipStream_t>(hip_stream);
     const size_t cbytes = field_bytes(N, dtype);
-    const int nb_max = (int)std::max<size_t>(1, workspace_budget() / (2 * cbytes));
+    const size_t cbytes2 = stores_columns(N) ? 0 : cbytes;  // the exchanged fields
+    const int nb_max = (int)std::max<size_t>(1, workspace_budget() / (cbytes + cbytes2));
     for (int b0 = 0; b0 < n_real; b0 += nb_max) {
         const int nb = std::min(nb_max, n_real - b0);
         const uint32_t r0 = first_realisation + (uint32_t)b0;
         void *ws = nullptr;
-        if (int rc = get_workspace(stream, 2 * cbytes * nb + low_mode_bytes(N, nb, dtype) + 1024, &ws)) return rc;
+        if (int rc = get_workspace(stream, (cbytes + cbytes2) * nb + low_mode_bytes(N, nb, dtype) + 1024, &ws)) return rc;
         Carver c;
         char *base = static_cast<char *>(ws);
         void *W1 = base + c.take(cbytes * nb);
-        void *W2 = base + c.take(cbytes * nb);
+        void *W2 = base + c.take(cbytes2 * nb);
         void *LT = base + c.take(low_mode_bytes(N, nb, dtype));
         void *S = nullptr;
         if (int rc = screen_passes(N, r_diff / delta, beta, seed, r0, nb, dtype, W1, W2, &S, stream, false)) return rc;
@@ -1398,15 +1407,16 @@ int fresnel_propagate(int N, double delta, double lambda, double z, const void *
     }
     const size_t cbytes = field_bytes(N, dtype);
     const size_t tbytes = (size_t)N * 2 * real_bytes(dtype);
-    const int nb_max = (int)std::max<size_t>(1, workspace_budget() / (2 * cbytes));
+    const size_t cbytes2 = second_bytes(N, dtype);
+    const int nb_max = (int)std::max<size_t>(1, workspace_budget() / (cbytes + cbytes2));
     for (int b0 = 0; b0 < n; b0 += nb_max) {
         const int nb = std::min(nb_max, n - b0);
         void *ws = nullptr;
-        if (int rc = get_workspace(stream, 2 * cbytes * nb + tbytes + 1024, &ws)) return rc;
+        if (int rc = get_workspace(stream, (cbytes + cbytes2) * nb + tbytes + 1024, &ws)) return rc;
         Carver c;
         char *base = static_cast<char *>(ws);
         void *W1 = base + c.take(cbytes * nb);
-        void *W2 = base + c.take(cbytes * nb);
+        void *W2 = base + c.take(cbytes2 * nb);
         void *H = base + c.take(tbytes);
         const char *ph = static_cast<const char *>(phi) + (size_t)b0 * nn(N) * real_bytes(dtype);
         char *I = static_cast<char *>(I_out) + (size_t)b0 * nn(N) * real_bytes(dtype);
@@ -1507,15 +1517,16 @@ int fresnel_propagate_field(int N, double delta, double lambda, double z, const 
     const double rho = std::sqrt(lambda * z / (2.0 * kPiD)) / delta;
     const size_t cbytes = field_bytes(N, dtype);
     const size_t tbytes = (size_t)N * 2 * real_bytes(dtype);
-    const int nb_max = (int)std::max<size_t>(1, workspace_budget() / (2 * cbytes));
+    const size_t cbytes2 = second_bytes(N, dtype);
+    const int nb_max = (int)std::max<size_t>(1, workspace_budget() / (cbytes + cbytes2));
     for (int b0 = 0; b0 < n; b0 += nb_max) {
         const int nb = std::min(nb_max, n - b0);
         void *ws = nullptr;
-        if (int rc = get_workspace(stream, 2 * cbytes * nb + tbytes + 1024, &ws)) return rc;
+        if (int rc = get_workspace(stream, (cbytes + cbytes2) * nb + tbytes + 1024, &ws)) return rc;
         Carver c;
         char *base = static_cast<char *>(ws);
         void *W1 = base + c.take(cbytes * nb);
-        void *W2 = base + c.take(cbytes * nb);
+        void *W2 = base + c.take(cbytes2 * nb);
         void *H = base + c.take(tbytes);
         if (int rc = chirp_tables(H, N, {rho}, dtype, true, stream)) return rc;
         const char *ph = static_cast<const char *>(phi) + (size_t)b0 * nn(N) * real_bytes(dtype);
@@ -1559,16 +1570,17 @@ int fresnel_aperture(int N, double delta, double lambda, double z, const void *p
     hipStream_t stream = static_cast<hipStream_t>(hip_stream);
     const size_t cbytes = field_bytes(N, dtype);
     const size_t tbytes = (size_t)N * 2 * real_bytes(dtype);
-    const int nb_max = (int)std::max<size_t>(1, workspace_budget() / (2 * cbytes));
+    const size_t cbytes2 = second_bytes(N, dtype);
+    const int nb_max = (int)std::max<size_t>(1, workspace_budget() / (cbytes + cbytes2));
     const double norm = 1.0 / (two_pi_rho2 * two_pi_rho2);
     for (int b0 = 0; b0 < n; b0 += nb_max) {
         const int nb = std::min(nb_max, n - b0);
         void *ws = nullptr;
-        if (int rc = get_workspace(stream, 2 * cbytes * nb + tbytes + 1024, &ws)) return rc;
+        if (int rc = get_workspace(stream, (cbytes + cbytes2) * nb + tbytes + 1024, &ws)) return rc;
         Carver c;
         char *base = static_cast<char *>(ws);
         void *W1 = base + c.take(cbytes * nb);
-        void *W2 = base + c.take(cbytes * nb);
+        void *W2 = base + c.take(cbytes2 * nb);
         void *A = base + c.take(tbytes);
         HIP_TRY(launch_aperture_table(A, N, 1.0 / (4.0 * kPiD * rho * rho), Lm, dtype == PS_F64, stream));
         const char *ph = static_cast<const char *>(phi) + (size_t)b0 * nn(N) * real_bytes(dtype);
@@ -1957,7 +1969,8 @@ int source_smear(int N, double delta, const void *I_in, const double *radii, int
     const int64_t fr = cols ? field_row(N, dtype) : N, fe = fr * N;
     const size_t cbytes = (size_t)fe * 2 * real_bytes(dtype);
     const size_t budget = workspace_budget();
-    const int nb_max = (int)std::max<size_t>(1, budget / (cbytes * (2 + 2 * (size_t)n_r)));
+    const size_t buffers = cols ? 1 : 2;  // transforms, and their transposes if there are any
+    const int nb_max = (int)std::max<size_t>(1, budget / (cbytes * buffers * (1 + (size_t)n_r)));
     // The disk kernel is real, so two real patterns a and b ride in one
     // complex transform: (a + i b) * d = a * d + i (b * d).  Realisations are
     // paired; an odd last one goes alone (imaginary part zero), in the launches
@@ -1966,13 +1979,13 @@ int source_smear(int N, double delta, const void *I_in, const double *radii, int
     for (int b0 = 0; b0 < n_real; b0 += nb_max) {
         const int nb = std::min(nb_max, n_real - b0);
         void *ws = nullptr;
-        if (int rc = get_workspace(stream, cbytes * nb * (2 + 2 * (size_t)n_r) + 4096, &ws)) return rc;
+        if (int rc = get_workspace(stream, cbytes * nb * buffers * (1 + (size_t)n_r) + 4096, &ws)) return rc;
         Carver c;
         char *base = static_cast<char *>(ws);
         char *W1 = base + c.take(cbytes * nb);
-        char *W2 = base + c.take(cbytes * nb);
+        char *W2 = cols ? W1 : base + c.take(cbytes * nb);
         char *V1 = base + c.take(cbytes * nb * n_r);
-        char *V2 = base + c.take(cbytes * nb * n_r);
+        char *V2 = cols ? V1 : base + c.take(cbytes * nb * n_r);
         const SideCfg sc = side_cfg();
         for (int pb = 0; pb < nb;) {
             const bool pair = nb - pb >= 2;
@@ -1985,7 +1998,7 @@ int source_smear(int N, double delta, const void *I_in, const double *radii, int
             const char *Iin = static_cast<const char *>(I_in) + (size_t)(b0 + pb) * rb1;
             // I_out[b][r]: transform q holds realisations b0 + pb + step q (and + 1)
             char *Iout = static_cast<char *>(I_out) + (size_t)(b0 + pb) * n_r * rb1;
-            SmearJob all{fe, fr, Iin, Iout, np, step, pairs, W1, cols ? W1 : W2, V1, cols ? V1 : V2};
+            SmearJob all{fe, fr, Iin, Iout, np, step, pairs, W1, W2, V1, V2};
             if (piped) {
                 // two jobs, the transposes of each riding on the other's passes
                 const int q0 = (np + 1) / 2;
@@ -2042,19 +2055,22 @@ int fresnel_propagate_vjp(int N, double delta, double lambda, double z, const vo
     const double rho = std::sqrt(lambda * z / (2.0 * kPiD)) / delta;
     const size_t cbytes = field_bytes(N, dtype);
     const size_t tbytes = (size_t)N * 2 * real_bytes(dtype);
-    const int nb_max = (int)std::max<size_t>(1, workspace_budget() / (2 * cbytes + rb1 + N * 8));
+    // the second field: the transposed one, or the recomputed forward one; the
+    // transposed grad_I where it is not read by columns
+    const size_t cbytes2 = stores_columns(N) && field ? 0 : cbytes, gbytes = real_columns(N) ? 0 : rb1;
+    const int nb_max = (int)std::max<size_t>(1, workspace_budget() / (cbytes + cbytes2 + gbytes + N * 8));
     std::vector<double> dots(n, 0.0);
     for (int b0 = 0; b0 < n; b0 += nb_max) {
         const int nb = std::min(nb_max, n - b0);
         void *ws = nullptr;
-        if (int rc = get_workspace(stream, (2 * cbytes + rb1) * nb + tbytes + (size_t)nb * N * 8 + nb * 8 + 4096,
+        if (int rc = get_workspace(stream, (cbytes + cbytes2 + gbytes) * nb + tbytes + (size_t)nb * N * 8 + nb * 8 + 4096,
                                    &ws))
             return rc;
         Carver c;
         char *base = static_cast<char *>(ws);
         char *W1 = base + c.take(cbytes * nb);
-        char *W2 = base + c.take(cbytes * nb);
-        char *Gt = base + c.take(rb1 * nb);
+        char *W2 = base + c.take(cbytes2 * nb);
+        char *Gt = base + c.take(gbytes * nb);
         char *H = base + c.take(tbytes);
         double *rowdot = reinterpret_cast<double *>(base + c.take((size_t)nb * N * 8));
         double *bdot = reinterpret_cast<double *>(base + c.take((size_t)nb * 8));

@@ -64,3 +64,31 @@ def test_screen_fresnel_fields(S, monkeypatch, dtype, env, budget, fields, n, ph
     assert used < (fields + 0.5) * field * chunk
     for a, b in zip(out if phi else (out,), ref if phi else (ref,)):
         assert torch.equal(a, b)
+
+
+# Fields of the sizes that store by columns have padded rows and need no
+# transposed copy.  `most`: bytes of workspace per screen, in units of one
+# unpadded real grid: fields of 2 (padded 2.3 at most), patterns of 1.
+@pytest.mark.parametrize("dtype", [torch.float32, torch.float64])
+@pytest.mark.parametrize("N,n,kind,most", [
+    (4096, 3, "generate", 2.3), (640, 60, "generate", 2.3), (4096, 3, "propagate", 3.3), (640, 60, "propagate", 2.3),
+    (2048, 8, "field", 3.3), (2048, 8, "aperture", 3.3), (1280, 20, "smear", 6.9), (2048, 8, "vjpfield", 3.3),
+    (640, 60, "vjpfield", 2.3), (640, 60, "vjp", 4.6)])
+def test_column_sizes_take_no_second_field(S, dtype, N, n, kind, most):
+    z = 2 * np.pi * 40.0 ** 2 / LAM
+    phi = torch.rand((n, N, N), dtype=dtype, device="cuda")
+    field = torch.rand((n, N, N, 2), dtype=dtype, device="cuda") if kind == "vjpfield" else None
+    calls = {
+        "generate": lambda: S.ps_generate(N, 1.0, 20.0, 11 / 3, 5, 0, n, dtype=dtype),
+        "propagate": lambda: S.fresnel_propagate(phi, 1.0, LAM, z),
+        "field": lambda: S.fresnel_propagate_field(phi, 1.0, LAM, z),
+        "aperture": lambda: S.fresnel_aperture(phi, 1.0, LAM, N / LAM),
+        "smear": lambda: S.source_smear(phi, 1.0, [2.0, 5.0]),
+        "vjp": lambda: S.fresnel_propagate_vjp(phi, 1.0, LAM, z, phi),
+        "vjpfield": lambda: S.fresnel_propagate_vjp(phi, 1.0, LAM, z, phi, field=field),
+    }
+    used, _ = taken(S, calls[kind])
+    grid = N * N * phi.element_size()
+    low = n * N * 17 * 16 if kind == "generate" and dtype == torch.float32 else 0  # the table of low modes
+    print(kind, N, dtype, "grids per screen", (used - low) / (grid * n))
+    assert used - low < most * grid * n + 6 * MiB
