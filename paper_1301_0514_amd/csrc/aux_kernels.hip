@@ -770,11 +770,12 @@ __global__ __launch_bounds__(256) void hankel_kernel(const double *S, int N, Rad
 }
 
 // R_diff^rec solves D = 1 by bisection on [1e-3, N/2] to a relative 1e-12 (NaN
-// when the root is not bracketed), kRootLevels levels of it per launch: one
+// when the root is not bracketed), several levels of it per launch: one
 // workgroup for each of the 2^levels - 1 midpoints that these levels can come
 // to evaluates D there, and the next launch walks down the tree.  On one
-// workgroup the 40-60 evaluations, one after the other, took 1.5 ms for two
-// 4000^2 screens; the launches take 0.1 ms.  RootState of a screen: the
+// workgroup per screen the 40-60 evaluations run one after the other (the whole
+// call for one 4000^2 screen 503 us, for one of 20000^2 5.91 ms; by launches of
+// eight levels 313 us and 4.74 ms).  RootState of a screen: the
 // bracket before the launch's levels and D at their midpoints (node 1 the
 // first, nodes 2n and 2n + 1 below and above it); two alternate.
 constexpr int kRootLevels = 8, kRootNodes = 1 << kRootLevels;
@@ -784,12 +785,26 @@ struct RootState {
     double D[kRootNodes];
 };
 
+// Levels per launch: a level more doubles the evaluations, so as many as keep
+// a launch within kRootGroups workgroups; 0, every screen's bisection on a
+// workgroup of its own, where fewer than kRootLeast are left (from 69 screens).
+// Screens of 64^2, us per call, eight levels always / on one workgroup / this
+// rule: 4 116 / 143 / 106, 32 231 / 148 / 123, 128 614 / 154 / 147,
+// 4096 16494 / 930 / 931; of 1000^2: 8 229 / 239 / 205, 64 1098 / 720 / 719.
+// (2048 workgroups, 64^2: 32 155, 128 197; 4096: 175 and 215.)
+constexpr int kRootGroups = 1024, kRootLeast = 4;
+static int root_levels(int nbatch) {
+    int levels = kRootLevels;
+    while (levels >= kRootLeast && (int64_t)nbatch * ((1 << levels) - 1) > kRootGroups) --levels;
+    return levels >= kRootLeast ? levels : 0;
+}
+
 __device__ __forceinline__ bool root_found(double lo, double hi) { return !(hi - lo > 1e-12 * hi); }
 
-__device__ __forceinline__ void root_walk(const RootState &s, double &lo, double &hi) {
+__device__ __forceinline__ void root_walk(const RootState &s, int nodes, double &lo, double &hi) {
     lo = s.lo;
     hi = s.hi;
-    for (int node = 1; node < kRootNodes && !root_found(lo, hi);) {
+    for (int node = 1; node < nodes && !root_found(lo, hi);) {
         const double mid = 0.5 * (lo + hi);
         const bool below = s.D[node] < 1.0;
         (below ? lo : hi) = mid;
@@ -798,14 +813,14 @@ __device__ __forceinline__ void root_walk(const RootState &s, double &lo, double
 }
 
 // ends: D at the two ends of the first bracket, [screen][2]; first: the
-// bracket is the whole range
+// bracket is the whole range.  Nodes 1 .. gridDim.x.
 __global__ __launch_bounds__(256) void root_kernel(const double *S, int N, const double *ends, const RootState *from,
                                                    RootState *to, int first) {
     __shared__ double red[256];
     const int node = blockIdx.x + 1, bat = blockIdx.y;
     if (!(ends[2 * bat] < 1.0 && ends[2 * bat + 1] >= 1.0)) return;
     double lo = kRootLo, hi = 0.5 * N;
-    if (!first) root_walk(from[bat], lo, hi);
+    if (!first) root_walk(from[bat], (int)gridDim.x + 1, lo, hi);
     if (node == 1 && threadIdx.x == 0) {
         to[bat].lo = lo;
         to[bat].hi = hi;
@@ -821,7 +836,8 @@ __global__ __launch_bounds__(256) void root_kernel(const double *S, int N, const
     if (threadIdx.x == 0) to[bat].D[node] = d;
 }
 
-__global__ __launch_bounds__(64) void root_finish_kernel(int n, const double *ends, const RootState *from, double *rdiff) {
+__global__ __launch_bounds__(64) void root_finish_kernel(int n, int nodes, const double *ends, const RootState *from,
+                                                         double *rdiff) {
     const int bat = blockIdx.x * 64 + threadIdx.x;
     if (bat >= n) return;
     if (!(ends[2 * bat] < 1.0 && ends[2 * bat + 1] >= 1.0)) {
@@ -829,11 +845,29 @@ __global__ __launch_bounds__(64) void root_finish_kernel(int n, const double *en
         return;
     }
     double lo, hi;
-    root_walk(from[bat], lo, hi);
+    root_walk(from[bat], nodes, lo, hi);
     rdiff[bat] = 0.5 * (lo + hi);
 }
 
-size_t hankel_scratch_bytes(int nbatch) { return (size_t)nbatch * (2 * sizeof(RootState) + 2 * sizeof(double)); }
+// The same midpoints and decisions, one screen per workgroup.
+__global__ __launch_bounds__(256) void root_serial_kernel(const double *S, int N, const double *ends, double *rdiff) {
+    __shared__ double red[256];
+    const int bat = blockIdx.x;
+    if (!(ends[2 * bat] < 1.0 && ends[2 * bat + 1] >= 1.0)) {
+        if (threadIdx.x == 0) rdiff[bat] = __longlong_as_double(0x7ff8000000000000LL);
+        return;
+    }
+    double lo = kRootLo, hi = 0.5 * N;
+    for (int it = 0; it < 200 && !root_found(lo, hi); ++it) {  // every thread sees the same lo, hi
+        const double mid = 0.5 * (lo + hi);
+        (structure_at(S + (int64_t)bat * (N / 2 + 1), N, mid, red) < 1.0 ? lo : hi) = mid;
+    }
+    if (threadIdx.x == 0) rdiff[bat] = 0.5 * (lo + hi);
+}
+
+size_t hankel_scratch_bytes(int nbatch) {
+    return (size_t)nbatch * ((root_levels(nbatch) ? 2 * sizeof(RootState) : 0) + 2 * sizeof(double));
+}
 
 hipError_t launch_hankel(const double *S, int N, int nbatch, const double *radii, int n_r, double *D, double *rdiff,
                          void *scratch, hipStream_t stream) {
@@ -848,23 +882,29 @@ hipError_t launch_hankel(const double *S, int N, int nbatch, const double *radii
             if (hipError_t e = hipGetLastError()) return e;
         }
         if (!rdiff) continue;
+        const int lv = root_levels(nbatch);
         RootState *state = static_cast<RootState *>(scratch);
-        double *ends = reinterpret_cast<double *>(state + 2 * (size_t)nbatch);
+        double *ends = reinterpret_cast<double *>(state + (lv ? 2 * (size_t)nbatch : 0));
         RadiusSet rs{};
         rs.r[0] = kRootLo;
         rs.r[1] = 0.5 * N;
         hipLaunchKernelGGL(hankel_kernel, dim3(2, nb), dim3(256), 0, stream, Sb, N, rs, ends, 2, 0);
         if (hipError_t e = hipGetLastError()) return e;
+        if (!lv) {
+            hipLaunchKernelGGL(root_serial_kernel, dim3(nb), dim3(256), 0, stream, Sb, N, ends, rdiff + b0);
+            if (hipError_t e = hipGetLastError()) return e;
+            continue;
+        }
         // the bracket shrinks from N/2 to 1e-12 of a root that is at least
         // 1e-3 pixels: at most log2(N/2 / 1e-15) halvings
         const int levels = (int)std::ceil(std::log2(0.5 * N / (1e-12 * kRootLo)));
-        const int rounds = (levels + kRootLevels - 1) / kRootLevels;
+        const int rounds = (levels + lv - 1) / lv, nodes = 1 << lv;
         for (int k = 0; k < rounds; ++k) {
-            hipLaunchKernelGGL(root_kernel, dim3(kRootNodes - 1, nb), dim3(256), 0, stream, Sb, N, ends,
+            hipLaunchKernelGGL(root_kernel, dim3(nodes - 1, nb), dim3(256), 0, stream, Sb, N, ends,
                                state + (size_t)((k + 1) % 2) * nb, state + (size_t)(k % 2) * nb, k == 0 ? 1 : 0);
             if (hipError_t e = hipGetLastError()) return e;
         }
-        hipLaunchKernelGGL(root_finish_kernel, dim3((nb + 63) / 64), dim3(64), 0, stream, nb, ends,
+        hipLaunchKernelGGL(root_finish_kernel, dim3((nb + 63) / 64), dim3(64), 0, stream, nb, nodes, ends,
                            state + (size_t)((rounds - 1) % 2) * nb, rdiff + b0);
         if (hipError_t e = hipGetLastError()) return e;
     }
