@@ -2256,24 +2256,27 @@ int ps_structure_function(int N, double delta, const void *phi, int n, const dou
     if (int rc = refuse_in_capture(stream, "ps_structure_function")) return rc;
     const int nbins = N / 2 + 1;
     const size_t cbytes = field_bytes(N, dtype);
-    const int nb_max = (int)std::max<size_t>(1, workspace_budget() / (2 * cbytes));
+    // the second buffer: the exchanged field, or the power map alone; beside the
+    // fields the results and what the root search needs per screen
+    const size_t cbytes2 = stores_columns(N) ? (size_t)nn(N) * real_bytes(dtype) : cbytes;
+    // (two doubles, and the trees of a small batch, below 1 MiB in all)
+    const size_t sbytes = ((size_t)nbins + n_r + 1 + 2) * 8;
+    const int nb_max = (int)std::max<size_t>(1, (workspace_budget() - ((size_t)1 << 20)) / (cbytes + cbytes2 + sbytes));
     std::vector<double> rpx(n_r);
     for (int j = 0; j < n_r; ++j) rpx[j] = radii[j] / delta;
     for (int b0 = 0; b0 < n; b0 += nb_max) {
         const int nb = std::min(nb_max, n - b0);
-        const size_t small = (size_t)nb * nbins * 8 + (size_t)nb * std::max(n_r, 1) * 8 + (size_t)nb * 8 +
-                             hankel_scratch_bytes(nb) + ring_scratch_bytes(N, nb) + 1536;
+        const size_t small = (size_t)nb * (nbins + n_r + 1) * 8 + hankel_scratch_bytes(nb) + 1536;
         void *ws = nullptr;
-        if (int rc = get_workspace(stream, 2 * cbytes * nb + small, &ws)) return rc;
+        if (int rc = get_workspace(stream, (cbytes + cbytes2) * nb + small, &ws)) return rc;
         Carver c;
         char *base = static_cast<char *>(ws);
         void *W1 = base + c.take(cbytes * nb);
-        void *W2 = base + c.take(cbytes * nb);
+        void *W2 = base + c.take(cbytes2 * nb);
         // the results, next to each other for one copy to the host: R, D, S
         const size_t nR = nb, nD = (size_t)nb * n_r, nS = (size_t)nb * nbins;
         double *R = reinterpret_cast<double *>(base + c.take((nR + nD + nS) * 8)), *D = R + nR, *S = D + nD;
         void *scratch = base + c.take(hankel_scratch_bytes(nb));
-        void *rings = base + c.take(ring_scratch_bytes(N, nb));
         const char *ph = static_cast<const char *>(phi) + (size_t)b0 * nn(N) * real_bytes(dtype);
         // |DFT phi|^2 / N^2: DFT along x, transpose, DFT along y and |.|^2
         auto build = [&](ProgBuilder &a) {
@@ -2281,7 +2284,10 @@ int ps_structure_function(int N, double delta, const void *phi, int n, const dou
         };
         void *F = nullptr;
         if (int rc = pass_exchange<ProgRealFwdTag, ProgRealFwdTTag>(N, nb, dtype, row_blocks(N, dtype), W1, W2, &F, stream, build)) return rc;
-        void *P = F == W1 ? W2 : W1;
+        // the power map to the other buffer; the fields are free after it, and
+        // hold the ring sums' scratch (a quarter of N^2 doubles at most)
+        void *P = F == W1 ? W2 : W1, *rings = F;
+        assert(ring_scratch_bytes(N, nb) <= cbytes * nb);
         ProgBuilder d(N, (int64_t)nb * N);
         d.op(ROP_LOAD_C, F, field_elems(N, dtype), field_row(N, dtype))
             .op(ROP_FFT_FWD)

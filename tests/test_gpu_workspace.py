@@ -92,3 +92,17 @@ def test_column_sizes_take_no_second_field(S, dtype, N, n, kind, most):
     low = n * N * 17 * 16 if kind == "generate" and dtype == torch.float32 else 0  # the table of low modes
     print(kind, N, dtype, "grids per screen", (used - low) / (grid * n))
     assert used - low < most * grid * n + 6 * MiB
+
+
+# the structure function: two fields (one and the power map where fields are
+# stored by columns), the scratch of its ring sums inside them and that of its
+# root search inside the budget
+@pytest.mark.parametrize("dtype", [torch.float32, torch.float64])
+@pytest.mark.parametrize("N,n,budget,most", [(5000, 2, 0, 4.0), (1280, 20, 0, 3.3), (16, 60000, 64 * MiB, 0),
+                                             (64, 6000, 100 * MiB, 0)])
+def test_structure_function_scratch(S, monkeypatch, dtype, N, n, budget, most):
+    phi = torch.rand((n, N, N), dtype=dtype, device="cuda")
+    used, _ = taken(S, lambda: S.structure_function(phi, 1.0, [1.0, 2.0]), budget)
+    bound = budget or most * n * N * N * phi.element_size()
+    print(N, dtype, used / bound)
+    assert used < bound + 4 * MiB
