@@ -396,11 +396,13 @@ struct MomentSums {
 };
 
 // VEC elements per load: 16 bytes for a contiguous run (w == row_stride, h
-// rows of it), else 1.  Rows of a narrower region are walked by whole rows of
-// threads.
+// rows of it), else 1.  Rows of a narrower region are walked by rows of
+// 2^log_tx threads, as many as its width asks for, up to a workgroup's 256; up
+// to there each thread keeps to one column (a 2 x 4096 strip by whole rows of
+// 256, two of them busy: 396 us per call; with the rows dealt out to all 32).
 template <typename Real, int VEC>
 __global__ __launch_bounds__(256) void moments_kernel(const Real *__restrict__ x, int64_t batch_stride, int64_t w,
-                                                      int64_t h, int64_t row_stride, Moments *partials) {
+                                                      int64_t h, int64_t row_stride, int log_tx, Moments *partials) {
     __shared__ Moments red[256];
     const int b = blockIdx.y, nblk = gridDim.x;
     const Real *xb = x + (int64_t)b * batch_stride;
@@ -427,17 +429,33 @@ __global__ __launch_bounds__(256) void moments_kernel(const Real *__restrict__ x
             for (int e = 0; e < VEC; ++e) a.add((double)v[e]);
         }
     } else {
-        for (int64_t y = blockIdx.x; y < h; y += nblk) {
-            const Real *row = xb + y * row_stride;
-            int64_t i = threadIdx.x;
-            for (; i + 3 * 256 < w; i += 4 * 256) {
-                const Real v0 = row[i], v1 = row[i + 256], v2 = row[i + 512], v3 = row[i + 768];
+        if (w <= 256) {
+            const int lane = threadIdx.x & ((1 << log_tx) - 1), rows = 256 >> log_tx;
+            const int64_t step = (int64_t)nblk * rows;
+            int64_t y = lane < w ? (int64_t)blockIdx.x * rows + (threadIdx.x >> log_tx) : h;
+            const Real *col = xb + lane;
+            for (; y + 3 * step < h; y += 4 * step) {  // four loads in flight
+                const Real v0 = col[y * row_stride], v1 = col[(y + step) * row_stride],
+                           v2 = col[(y + 2 * step) * row_stride], v3 = col[(y + 3 * step) * row_stride];
                 a.add((double)v0);
                 a.add((double)v1);
                 a.add((double)v2);
                 a.add((double)v3);
             }
-            for (; i < w; i += 256) a.add((double)row[i]);
+            for (; y < h; y += step) a.add((double)col[y * row_stride]);
+        } else {
+            for (int64_t y = blockIdx.x; y < h; y += nblk) {
+                const Real *row = xb + y * row_stride;
+                int64_t i = threadIdx.x;
+                for (; i + 3 * 256 < w; i += 4 * 256) {
+                    const Real v0 = row[i], v1 = row[i + 256], v2 = row[i + 512], v3 = row[i + 768];
+                    a.add((double)v0);
+                    a.add((double)v1);
+                    a.add((double)v2);
+                    a.add((double)v3);
+                }
+                for (; i < w; i += 256) a.add((double)row[i]);
+            }
         }
     }
     const Moments tot = block_merge(a.get(), red);
@@ -457,9 +475,15 @@ __global__ __launch_bounds__(256) void moments_finish_kernel(const Moments *part
     }
 }
 
+static int moment_log_tx(int64_t w) {
+    int l = 0;
+    while (l < 8 && ((int64_t)1 << l) < w) ++l;
+    return l;
+}
 static int moment_blocks(int64_t w, int64_t h, bool run) {
     // at least 16 elements per thread, at most four workgroups per CU
-    const int64_t want = (w * h + 4095) / 4096, most = run ? 1024 : (h < 1024 ? h : 1024);
+    const int64_t rows = 256 >> moment_log_tx(w), sets = run ? 1024 : (h + rows - 1) / rows;
+    const int64_t want = (w * h + 4095) / 4096, most = sets < 1024 ? sets : 1024;
     return (int)(want < 1 ? 1 : want < most ? want : most);
 }
 size_t moments_scratch_bytes(int64_t w, int64_t h, int nbatch) {
@@ -473,7 +497,7 @@ hipError_t launch_moments(const void *x, int64_t batch_stride, int64_t w, int64_
     // loads where every batch member starts on one
     const bool run = w == row_stride || h == 1;
     const bool wide = run && (w * h) % vec == 0 && ((uintptr_t)x & 15u) == 0 && batch_stride % vec == 0;
-    const int nblk = moment_blocks(w, h, wide);
+    const int nblk = moment_blocks(w, h, wide), log_tx = moment_log_tx(w);
     Moments *part = static_cast<Moments *>(scratch);
     const int64_t rs = h == 1 ? w : row_stride;
     for (int b0 = 0; b0 < nbatch; b0 += 65535) {
@@ -484,15 +508,15 @@ hipError_t launch_moments(const void *x, int64_t batch_stride, int64_t w, int64_
         if (f64) {
             const double *xd = static_cast<const double *>(x) + off;
             if (wide)
-                hipLaunchKernelGGL((moments_kernel<double, 2>), grid, dim3(256), 0, stream, xd, batch_stride, w, h, rs, p);
+                hipLaunchKernelGGL((moments_kernel<double, 2>), grid, dim3(256), 0, stream, xd, batch_stride, w, h, rs, log_tx, p);
             else
-                hipLaunchKernelGGL((moments_kernel<double, 1>), grid, dim3(256), 0, stream, xd, batch_stride, w, h, rs, p);
+                hipLaunchKernelGGL((moments_kernel<double, 1>), grid, dim3(256), 0, stream, xd, batch_stride, w, h, rs, log_tx, p);
         } else {
             const float *xf = static_cast<const float *>(x) + off;
             if (wide)
-                hipLaunchKernelGGL((moments_kernel<float, 4>), grid, dim3(256), 0, stream, xf, batch_stride, w, h, rs, p);
+                hipLaunchKernelGGL((moments_kernel<float, 4>), grid, dim3(256), 0, stream, xf, batch_stride, w, h, rs, log_tx, p);
             else
-                hipLaunchKernelGGL((moments_kernel<float, 1>), grid, dim3(256), 0, stream, xf, batch_stride, w, h, rs, p);
+                hipLaunchKernelGGL((moments_kernel<float, 1>), grid, dim3(256), 0, stream, xf, batch_stride, w, h, rs, log_tx, p);
         }
         if (hipError_t e = hipGetLastError()) return e;
         hipLaunchKernelGGL(moments_finish_kernel, dim3(nb), dim3(256), 0, stream, p, nblk, stats + 2 * (size_t)b0);
