@@ -391,7 +391,9 @@ struct MomentSums {
     }
     __device__ __forceinline__ Moments get() const {
         if (n == 0.0) return {0.0, 0.0, 0.0, 0.0};
-        return {n, s0, c + s1 / n, fmax(s2 - s1 * (s1 / n), 0.0 * s2)};  // (>= 0, and NaN where a sum is)
+        // (>= 0, NaN where a sum is, infinite where only the squares overflow)
+        const double m2 = isinf(s2) && isfinite(s1) ? s2 : fmax(s2 - s1 * (s1 / n), 0.0 * s2);
+        return {n, s0, c + s1 / n, m2};
     }
 };
 

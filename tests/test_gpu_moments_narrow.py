@@ -52,3 +52,12 @@ def test_strip_costs_no_more_than_the_pattern(S):
     whole, strip = best(lambda: S.ps_modulation_index(I)), best(lambda: S.ps_modulation_index_region(I, 5, 0, 2, N))
     print("whole %.4f ms, strip %.4f ms" % (whole, strip))
     assert strip < 3 * whole
+
+
+def test_squares_that_overflow(S):
+    # the deviations are finite and their squares are not: m is infinite, as numpy's std is
+    I = 1e200 * (torch.rand((2, 100, 100), dtype=torch.float64, device="cuda") + 0.5)
+    I[1] *= 1e-200
+    for m, mean in (S.ps_modulation_index(I, want_mean=True), S.ps_modulation_index_region(I, 3, 5, 90, 80, True)):
+        assert m[0] == float("inf") and 0.9e200 < mean[0] < 1.1e200
+        assert m[1] == pytest.approx(0.29, abs=0.02)
