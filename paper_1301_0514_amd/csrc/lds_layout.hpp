@@ -158,16 +158,23 @@ constexpr bool smear_columns(int L) { return L <= kSmearColumnsMaxL; }
 constexpr int kRealColumnsMaxL = 1024;
 constexpr bool real_columns(int L) { return L <= kRealColumnsMaxL; }
 
-// Rows that such a workgroup interleaves: runs of 32 bytes in FP32 (16 x
-// 2048^2 forward + adjoint: 1.97 ms; 16 bytes 2.26, 64 bytes 2.24 ms, whose
-// 1024-thread workgroups fill a CU alone), 64 in FP64, fewer where the LDS
-// would hold one workgroup only, and fewer at the small sizes, whose rows
-// would not occupy the chip.
+// Rows that such a workgroup interleaves: up to four, runs of 32 bytes in FP32
+// (16 x 2048^2 forward + adjoint: 1.97 ms; 16 bytes 2.26, 64 bytes 2.24 ms,
+// whose 1024-thread workgroups fill a CU alone) and 64 in FP64, fewer where the
+// LDS would hold one workgroup only, and fewer at the small sizes, whose rows
+// would not occupy the chip.  Where the threads of a row divide a wave, at
+// least a whole wave of them: 32 threads gave single calls the same time and
+// batches half the rate (327 x 320^2 adjoints 458 us with two rows, 361 with
+// four; 8192 x 64^2 FP64 screens 930 and 553 us).  Rows of 10 and 20 threads do
+// not fill whole waves with more rows either: 100 keeps 40 threads, and 200 and
+// 400 do in FP64 (26 x 400^2 screens 129 us, 139 with 80 threads).
 template <int L, int V> constexpr int column_rows(int elem_bytes) {
     const int T = Plan<L, V>::T;
+    const bool whole = 64 % T == 0 || T % 64 == 0;
+    const int least = whole || elem_bytes == 8 ? 60 : 120;  // of a row's length per row
     int rows = 1;
-    while (2 * rows <= 4 && 2 * rows * 120 <= L) rows *= 2;
-    while (T * rows < 32) rows *= 2;
+    while (2 * rows <= 4 && 2 * rows * least <= L) rows *= 2;
+    while (T * rows < (64 % T == 0 ? 64 : 32)) rows *= 2;
     while (rows > 1 && (T * rows > 1024 || rows * exch_buffer_length<L, V>(elem_bytes, rows) * elem_bytes >
                                                (rows * elem_bytes > 32 ? 80 : 160) * 1024))
         rows /= 2;

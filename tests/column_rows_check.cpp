@@ -1,0 +1,47 @@
+// Host check of the rows that a workgroup of the passes by columns interleaves
+// (lds_layout.hpp), built and run by tests/test_column_rows_host.py: whole waves
+// where the threads of a row divide one, within the limits of a workgroup, and
+// the exchanges of every element in a slot of its own.
+#include <cstdio>
+#include <vector>
+
+#include "lds_layout.hpp"
+
+using namespace scint;
+
+static int failures = 0;
+
+template <int L, int V> static bool slots_ok(int eb, int W) {
+    using P = Plan<L, V>;
+    const int buf = exch_buffer_length<L, V>(eb, W), sh = lds_pad_shift<L>();
+    if (W < 1 || P::T * W > 1024 || (long long)W * buf * eb > 160 * 1024) return false;
+    for (int s = 0; s + 1 < P::NS; ++s) {
+        const ExchLayout lay = exch_layout<L, V>(s, eb, W);
+        std::vector<char> used((size_t)W * buf, 0);
+        for (int b = 0; b < W; ++b)
+            for (int p = 0; p < L; ++p) {
+                const int a = layout_at(lay, sh, p) * W + b;
+                if (a < 0 || a >= W * buf || used[a]) return false;
+                used[a] = 1;
+            }
+    }
+    return true;
+}
+
+template <int L, int V> static void check(int eb) {
+    if (!stores_columns(L)) return;
+    const int T = Plan<L, V>::T, W = column_rows<L, V>(eb);
+    bool ok = slots_ok<L, V>(eb, W);
+    if (64 % T == 0 && T * W % 64 != 0) ok = false;  // an unfilled wave
+    std::printf("%s L=%d V=%d eb=%d threads per row %d, rows %d\n", ok ? "ok" : "FAIL", L, V, eb, T, W);
+    failures += !ok;
+}
+
+int main() {
+#define SCINT_F64_CASE(LL) check<LL, 0>(16), check<LL, 0>(8);
+    SCINT_SIZES_F64(SCINT_F64_CASE)
+#define SCINT_V_CASE(LL, VV) check<LL, VV>(8);
+    SCINT_VARIANTS_F32(SCINT_V_CASE)
+    std::printf("%d failures\n", failures);
+    return failures ? 1 : 0;
+}
