@@ -168,7 +168,16 @@ constexpr bool real_columns(int L) { return L <= kRealColumnsMaxL; }
 // four; 8192 x 64^2 FP64 screens 930 and 553 us).  Rows of 10 and 20 threads do
 // not fill whole waves with more rows either: 100 keeps 40 threads, and 200 and
 // 400 do in FP64 (26 x 400^2 screens 129 us, 139 with 80 threads).
-template <int L, int V> constexpr int column_rows(int elem_bytes) {
+// Passes of two or more transforms outside a wavelength loop (heavy: screen +
+// propagation, the adjoint's first) keep so many registers at 20 elements per
+// thread that a CU holds 8 waves: from 2000 on they take as many rows as let
+// two workgroups share it, since one alone waits at each of its barriers
+// (adjoint from the kept field of 2 x 4000^2: 460 us with transposes, 500 with
+// four rows, 471 with one; of 5 x 2560^2 446, 468, and 421 with two; FP64 screen
+// + pattern of 5 x 2560^2 1665, 1702 with two, 1514 with one).
+constexpr bool heavy_columns(int L, int E) { return L >= 2000 && E % 16 != 0; }
+
+template <int L, int V> constexpr int column_rows(int elem_bytes, bool heavy = false) {
     const int T = Plan<L, V>::T;
     const bool whole = 64 % T == 0 || T % 64 == 0;
     const int least = whole || elem_bytes == 8 ? 60 : 120;  // of a row's length per row
@@ -178,6 +187,10 @@ template <int L, int V> constexpr int column_rows(int elem_bytes) {
     while (rows > 1 && (T * rows > 1024 || rows * exch_buffer_length<L, V>(elem_bytes, rows) * elem_bytes >
                                                (rows * elem_bytes > 32 ? 80 : 160) * 1024))
         rows /= 2;
+    if (heavy && heavy_columns(L, Plan<L, V>::E))
+        while (rows > 1 && (2 * ((T * rows + 63) / 64) > 8 ||
+                            2 * rows * exch_buffer_length<L, V>(elem_bytes, rows) * elem_bytes > 160 * 1024))
+            rows /= 2;
     return rows;
 }
 

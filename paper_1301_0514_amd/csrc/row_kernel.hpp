@@ -752,11 +752,21 @@ template <class Ops> constexpr bool iter_splittable() {
     return i == Ops::n - 1;
 }
 
+// Two or more transforms outside a loop (column_rows).
+template <class Ops> constexpr bool heavy_program() {
+    int ffts = 0;
+    for (int i = 0; i < Ops::n; ++i) {
+        if (Ops::code[i] == ROP_LOOP) return false;
+        ffts += Ops::code[i] == ROP_FFT_FWD || Ops::code[i] == ROP_FFT_INV;
+    }
+    return ffts >= 2;
+}
+
 // Rows interleaved in the lanes (0: none): the programs with an operand that
 // lies the other way round at this size.
 template <typename Real, int L, int V, class Ops> constexpr int program_rows() {
     for (int i = 0; i < Ops::n; ++i)
-        if (lies_across(Ops::code[i], L)) return column_rows<L, V>(2 * (int)sizeof(Real));
+        if (lies_across(Ops::code[i], L)) return column_rows<L, V>(2 * (int)sizeof(Real), heavy_program<Ops>());
     return 0;
 }
 

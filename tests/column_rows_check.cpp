@@ -33,7 +33,15 @@ template <int L, int V> static void check(int eb) {
     const int T = Plan<L, V>::T, W = column_rows<L, V>(eb);
     bool ok = slots_ok<L, V>(eb, W);
     if (64 % T == 0 && T * W % 64 != 0) ok = false;  // an unfilled wave
-    std::printf("%s L=%d V=%d eb=%d threads per row %d, rows %d\n", ok ? "ok" : "FAIL", L, V, eb, T, W);
+    // the passes of many transforms: two workgroups on a CU at the sizes that ask for it
+    const int H = column_rows<L, V>(eb, true);
+    ok = ok && slots_ok<L, V>(eb, H) && H <= W;
+    if (heavy_columns(L, Plan<L, V>::E)) {
+        if (2 * ((T * H + 63) / 64) > 8 || 2 * H * exch_buffer_length<L, V>(eb, H) * eb > 160 * 1024) ok = false;
+    } else if (H != W) {
+        ok = false;
+    }
+    std::printf("%s L=%d V=%d eb=%d threads per row %d, rows %d, %d\n", ok ? "ok" : "FAIL", L, V, eb, T, W, H);
     failures += !ok;
 }
 
