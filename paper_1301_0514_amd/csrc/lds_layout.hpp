@@ -194,6 +194,19 @@ template <int L, int V> constexpr int column_rows(int elem_bytes, bool heavy = f
     return rows;
 }
 
+// The first pass over several wavelengths (poly) writes that many fields.  Up to
+// 320, where they are more than the 256 MB cache holds, its runs go to memory
+// as they are: whole lines of 128 bytes, within 512 threads (XX).
+constexpr int kPolyColumnsMaxL = 320;
+constexpr long long kPolyCacheBytes = 256ll << 20;
+template <int L, int V> constexpr int poly_column_rows(int elem_bytes) {
+    const int T = Plan<L, V>::T;
+    int rows = column_rows<L, V>(elem_bytes);
+    if (L > kPolyColumnsMaxL || (64 % T != 0 && T % 64 != 0)) return rows;
+    while (rows * elem_bytes < 128 && 2 * T * rows <= 512) rows *= 2;
+    return rows;
+}
+
 // Row group and part (of `parts` workgroups that share a group's loop
 // iterations) of workgroup w.  Workgroup w runs on XCD w % 8: the `line` row
 // groups that share cache lines of what they store go to one XCD, next to each

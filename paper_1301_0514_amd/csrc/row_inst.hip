@@ -18,9 +18,10 @@
 
 namespace scint {
 
-template <int L, int V>
-static hipError_t launch_one(const RowProgram &prog, const void *tw, hipStream_t stream) {
-    using Cfg = RowCfg<SCINT_REAL, L, V, program_rows<SCINT_REAL, L, V, SCINT_PROG>()>;
+// W rows interleaved in a workgroup (0: none)
+template <int L, int V, int W>
+static hipError_t launch_rows(const RowProgram &prog, const void *tw, hipStream_t stream) {
+    using Cfg = RowCfg<SCINT_REAL, L, V, W>;
     // passes that store by columns need no transposes beside them, and only the
     // sizes of real_columns take phase screens by columns
     constexpr bool smear = std::is_same<SCINT_PROG, ProgSmearFwdT>::value ||
@@ -37,7 +38,7 @@ static hipError_t launch_one(const RowProgram &prog, const void *tw, hipStream_t
         p.iter_split = iter_splittable<SCINT_PROG>() ? std::min(std::max(prog.iter_split, 1), prog.n_iter) : 1;
         const int64_t grid = (groups + set - 1) / set * set * p.iter_split;
         if (grid > (1ll << 31) - 1) return hipErrorInvalidValue;
-        hipLaunchKernelGGL((row_kernel<SCINT_REAL, L, V, SCINT_PROG>), dim3((unsigned)grid), dim3(Cfg::THREADS), 0,
+        hipLaunchKernelGGL((row_kernel<SCINT_REAL, L, V, SCINT_PROG, W>), dim3((unsigned)grid), dim3(Cfg::THREADS), 0,
                            stream, p, static_cast<const cpx<SCINT_REAL> *>(tw));
         return hipGetLastError();
     }
@@ -64,14 +65,25 @@ static hipError_t launch_one(const RowProgram &prog, const void *tw, hipStream_t
             return hipErrorInvalidValue;
         sd.units_per_block = (int32_t)per;
         const int grid = sd.groups * (sd.fft_blocks + sd.side_blocks);
-        hipLaunchKernelGGL((row_kernel<SCINT_REAL, L, V, SCINT_PROG>), dim3(grid), dim3(Cfg::THREADS), 0, stream, p,
+        hipLaunchKernelGGL((row_kernel<SCINT_REAL, L, V, SCINT_PROG, W>), dim3(grid), dim3(Cfg::THREADS), 0, stream, p,
                            static_cast<const cpx<SCINT_REAL> *>(tw));
     } else {
-        hipLaunchKernelGGL((row_kernel<SCINT_REAL, L, V, SCINT_PROG>), dim3(rows_blocks), dim3(Cfg::THREADS), 0,
+        hipLaunchKernelGGL((row_kernel<SCINT_REAL, L, V, SCINT_PROG, W>), dim3(rows_blocks), dim3(Cfg::THREADS), 0,
                            stream, p, static_cast<const cpx<SCINT_REAL> *>(tw));
     }
     return hipGetLastError();
     }
+}
+
+template <int L, int V>
+static hipError_t launch_one(const RowProgram &prog, const void *tw, hipStream_t stream) {
+    constexpr int W = program_rows<SCINT_REAL, L, V, SCINT_PROG>(), elem = 2 * (int)sizeof(SCINT_REAL);
+    if constexpr (std::is_same<SCINT_PROG, ProgPhaseProp>::value && stores_columns(L)) {
+        constexpr int WP = poly_column_rows<L, V>(elem);
+        const int64_t bytes = (int64_t)(prog.total_rows - prog.row0) * prog.n_iter * field_pitch(L, elem) * elem;
+        if (WP != W && bytes > kPolyCacheBytes) return launch_rows<L, V, WP>(prog, tw, stream);
+    }
+    return launch_rows<L, V, W>(prog, tw, stream);
 }
 
 template <>

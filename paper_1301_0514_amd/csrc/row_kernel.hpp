@@ -772,8 +772,8 @@ template <typename Real, int L, int V, class Ops> constexpr int program_rows() {
 
 // LDS of a row kernel: the row pass's, or the transpose tile's if larger
 // (programs with side transposes)
-template <typename Real, int L, int V, class Ops> constexpr int row_kernel_lds() {
-    constexpr int a = RowCfg<Real, L, V, program_rows<Real, L, V, Ops>()>::LDS_BYTES, b = (int)sizeof(TransposeTile<cpx<float>>);
+template <typename Real, int L, int V, class Ops, int W> constexpr int row_kernel_lds() {
+    constexpr int a = RowCfg<Real, L, V, W>::LDS_BYTES, b = (int)sizeof(TransposeTile<cpx<float>>);
     return has_side<Ops>() && a < b ? b : a;
 }
 
@@ -805,7 +805,7 @@ __attribute__((amdgpu_waves_per_eu(RowCfg<Real, L, V, W>::WAVES_PER_EU))) void r
                                                                            const cpx<Real> *__restrict__ tw) {
     using Cfg = RowCfg<Real, L, V, W>;
     constexpr int E = Plan<L, V>::E, T = Plan<L, V>::T, B = Cfg::B;
-    __shared__ __align__(16) unsigned char lds_raw[row_kernel_lds<Real, L, V, Ops>()];
+    __shared__ __align__(16) unsigned char lds_raw[row_kernel_lds<Real, L, V, Ops, W>()];
     int rb = blockIdx.x;  // row workgroup number
     if constexpr (has_side<Ops>()) {
         // groups of fft_blocks row workgroups followed by side_blocks

@@ -41,7 +41,10 @@ template <int L, int V> static void check(int eb) {
     } else if (H != W) {
         ok = false;
     }
-    std::printf("%s L=%d V=%d eb=%d threads per row %d, rows %d, %d\n", ok ? "ok" : "FAIL", L, V, eb, T, W, H);
+    // the first pass over many wavelengths
+    const int Q = poly_column_rows<L, V>(eb);
+    ok = ok && slots_ok<L, V>(eb, Q) && Q >= W && (Q == W || (L <= kPolyColumnsMaxL && T * Q <= 512));
+    std::printf("%s L=%d V=%d eb=%d threads per row %d, rows %d, %d, %d\n", ok ? "ok" : "FAIL", L, V, eb, T, W, H, Q);
     failures += !ok;
 }
 
