@@ -196,7 +196,9 @@ template <int L, int V> constexpr int column_rows(int elem_bytes, bool heavy = f
 
 // The first pass over several wavelengths (poly) writes that many fields.  Up to
 // 320, where they are more than the 256 MB cache holds, its runs go to memory
-// as they are: whole lines of 128 bytes, within 512 threads (XX).
+// as they are: whole lines of 128 bytes, within 512 threads (11 wavelengths of
+// 8192 x 64^2 screens 2.47 ms with transposes, 2.72 with runs of 32 bytes, 1.84
+// with whole lines; of 512 x 256^2 2.39, 2.88 and 2.14).
 constexpr int kPolyColumnsMaxL = 320;
 constexpr long long kPolyCacheBytes = 256ll << 20;
 template <int L, int V> constexpr int poly_column_rows(int elem_bytes) {
