@@ -100,11 +100,11 @@ int ps_supported_size_at(int dtype, int i);
  *   phi_out           device [n_real][N][N] real (dtype)
  * A warning (ps_last_warning) is set when delta >= r_diff/2, the sampling
  * criterion of Sect. 3.2.2.
- * In FP32 from N = 5000 the first pass runs in four blocks of rows, each
- * carrying the previous block's transpose as extra workgroups
- * (SCINT_SCREEN_JOBS=<n> in the environment sets the number, here and in the
- * other calls with such passes; 1 turns the split off); every value is the
- * same bit for bit.
+ * In FP32 from N = 5000 and 8000 rows of a batch on, the first pass runs in
+ * four blocks of rows, each carrying the previous block's transpose as extra
+ * workgroups (SCINT_SCREEN_JOBS=<n> in the environment sets the number, here
+ * and in the other calls with such passes; 1 turns the split off); every value
+ * is the same bit for bit.
  */
 int ps_generate(int N, double delta, double r_diff, double beta, uint64_t seed,
                 uint32_t first_realisation, int n_real, int dtype, void *phi_out,

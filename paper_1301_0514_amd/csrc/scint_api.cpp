@@ -756,8 +756,8 @@ size_t workspace_budget() {
 // job's), in groups of 32 + 8.  SCINT_PIPELINE=0 in the environment turns
 // the pipeline and the row blocks of pass_exchange off; SCINT_SIDE_SPLIT=<f> and SCINT_SIDE_GROUPS=
 // <rows_x>:<side_x>:<rows_y>:<side_y> override the defaults.  Single passes
-// run in screen_jobs row blocks (pass_exchange; SCINT_SCREEN_JOBS=<n>, 1 turns
-// them off).  The x passes of the pipelined propagation
+// run in row_blocks row blocks (pass_exchange; SCINT_SCREEN_JOBS=<n> sets their
+// number, 1 turns them off).  The x passes of the pipelined propagation
 // give each row two workgroups, each taking half of the wavelengths, so that
 // the phase row both re-read for every wavelength is fetched from one L2
 // (measured at 8192^2 x 32 wavelengths, per x pass with transposes: 10.29
@@ -767,7 +767,7 @@ struct SideCfg {
     bool on = true;
     double split = 1.0;
     int fft_x = 32, side_x = 8, fft_y = 32, side_y = 8;
-    int screen_jobs = 4;
+    int screen_jobs = 0;  // 0: by row_blocks
     int iter_split = 2;
 };
 static SideCfg side_cfg() {
@@ -798,6 +798,21 @@ static SideCfg side_cfg() {
     return c;
 }
 
+// Row blocks of a pass over nb grids (pass_exchange): four from 2000 rows in
+// each on (below, a launch ends before it fills
+// the chip: one 5000^2 screen + pattern 512 us in one block, 543 in four, two of
+// them 1018 and 979, one of 8000^2 1665 and 1582).  Passes of one transform
+// without noise (light: real input, aperture) have too little arithmetic to
+// hide a transpose at 5000: power maps of 2 x 5000^2 672 us in one block, 719 in
+// four; aperture 489 and 513; from 8000 on 1.00-1.07 times as fast.
+constexpr int kRowBlocks = 4, kBlockRows = 2000, kLightBlocksMinN = 8000;
+int row_blocks(int N, int nb, int dtype, bool light = false) {
+    const SideCfg sc = side_cfg();
+    if (dtype != PS_F32 || !sc.on || stores_columns(N)) return 1;
+    if (sc.screen_jobs > 0) return sc.screen_jobs;
+    return (int64_t)N * nb < kRowBlocks * kBlockRows || (light && N < kLightBlocksMinN) ? 1 : kRowBlocks;
+}
+
 // A pass over nb grids whose complex result goes to `from`, and the exchange
 // that hands it to the pass along the other axis (*next: `from` or `to`, which
 // must hold no operand of the pass).  build(p) appends the pass's operations.
@@ -811,10 +826,6 @@ static SideCfg side_cfg() {
 // the blocks.
 //
 // With blocks = 1 the whole pass comes first, and `to` may hold its operand.
-int row_blocks(int N, int dtype) {
-    const SideCfg sc = side_cfg();
-    return (dtype == PS_F32 && sc.on && !stores_columns(N)) ? sc.screen_jobs : 1;
-}
 template <class Tag, class TagT, class Build>
 int pass_exchange(int N, int nb, int dtype, int blocks, void *from, void *to, void **next, hipStream_t stream,
                   Build build) {
@@ -864,8 +875,8 @@ int screen_passes(int N, double R, double beta, uint64_t seed, uint32_t r0, int 
             .op(ROP_FFT_INV)
             .op(ROP_STORE_C, W1, field_elems(N, dtype), field_row(N, dtype));
     };
-    return swap ? pass_exchange<ProgNoiseSwapTag, ProgNoiseSwapTTag>(N, nb, dtype, row_blocks(N, dtype), W1, W2, next, stream, build)
-                : pass_exchange<ProgNoiseTag, ProgNoiseTTag>(N, nb, dtype, row_blocks(N, dtype), W1, W2, next, stream, build);
+    return swap ? pass_exchange<ProgNoiseSwapTag, ProgNoiseSwapTTag>(N, nb, dtype, row_blocks(N, nb, dtype), W1, W2, next, stream, build)
+                : pass_exchange<ProgNoiseTag, ProgNoiseTTag>(N, nb, dtype, row_blocks(N, nb, dtype), W1, W2, next, stream, build);
 }
 
 // Second propagation pass of nb screens on the exchanged field W: DFT,
@@ -1135,7 +1146,7 @@ int ps_screen_fresnel(int N, double delta, double r_diff, double beta, uint64_t 
     // and a third buffer takes them: if the budget and the memory hold three.
     // With two, the second pass runs in one block and its transpose replaces
     // its operand.
-    const bool ride = row_blocks(N, dtype) > 1 && 3 * cbytes <= workspace_budget();
+    const bool ride = row_blocks(N, n_real, dtype) > 1 && 3 * cbytes <= workspace_budget();
     const int nb_max = (int)std::max<size_t>(1, workspace_budget() / ((ride ? 3 : 2) * cbytes));
     for (int b0 = 0; b0 < n_real; b0 += nb_max) {
         const int nb = std::min(nb_max, n_real - b0);
@@ -1178,7 +1189,7 @@ int ps_screen_fresnel(int N, double delta, double r_diff, double beta, uint64_t 
                 .op(ROP_FFT_INV)
                 .op(ROP_STORE_C, X, field_elems(N, dtype), field_row(N, dtype));
         };
-        const int blocks = W3 ? row_blocks(N, dtype) : 1;
+        const int blocks = W3 ? row_blocks(N, nb, dtype) : 1;
         if (int rc = pass_exchange<ProgScreenPropTag, ProgScreenPropTTag>(N, nb, dtype, blocks, X, W3 ? W3 : S, &A,
                                                                           stream, build))
             return rc;
@@ -1222,7 +1233,7 @@ static int poly_chunk(int N, const void *phi, int nb, const std::vector<double> 
                              : run_row<ProgPhasePropTag>(dtype, N, a.p, a.n, stream))
             return rc;
         if (int rc = exchange(W1, W2, N, (int64_t)nb * C, dtype, &A, stream)) return rc;
-    } else if (int rc = pass_exchange<ProgPhasePropTag, ProgPhasePropTTag>(N, nb, dtype, row_blocks(N, dtype), W1, W2, &A, stream, build)) {
+    } else if (int rc = pass_exchange<ProgPhasePropTag, ProgPhasePropTTag>(N, nb, dtype, row_blocks(N, nb, dtype), W1, W2, &A, stream, build)) {
         return rc;
     }
     ProgBuilder b(N, (int64_t)nb * N);
@@ -1540,7 +1551,7 @@ int fresnel_propagate_field(int N, double delta, double lambda, double z, const 
                 .op(ROP_ENDLOOP);
         };
         void *A = nullptr;
-        if (int rc = pass_exchange<ProgPhasePropTag, ProgPhasePropTTag>(N, nb, dtype, row_blocks(N, dtype), W1, W2, &A, stream, build)) return rc;
+        if (int rc = pass_exchange<ProgPhasePropTag, ProgPhasePropTTag>(N, nb, dtype, row_blocks(N, nb, dtype), W1, W2, &A, stream, build)) return rc;
         char *F = static_cast<char *>(field_out) + (size_t)b0 * nn(N) * 2 * real_bytes(dtype);
         char *I = static_cast<char *>(I_out) + (size_t)b0 * nn(N) * real_bytes(dtype);
         if (int rc = prop_y_pass(N, dtype, nb, A, H, A == W1 ? W2 : W1, I, F, stream)) return rc;
@@ -1595,7 +1606,7 @@ int fresnel_aperture(int N, double delta, double lambda, double z, const void *p
                 .op(ROP_STORE_C, W1, field_elems(N, dtype), field_row(N, dtype));
         };
         void *G = nullptr;
-        if (int rc = pass_exchange<ProgApertureXTag, ProgApertureXTTag>(N, nb, dtype, row_blocks(N, dtype), W1, W2, &G, stream, build)) return rc;
+        if (int rc = pass_exchange<ProgApertureXTag, ProgApertureXTTag>(N, nb, dtype, row_blocks(N, nb, dtype, true), W1, W2, &G, stream, build)) return rc;
         // rows kx: DFT along y, |.|^2 / (2 pi rho^2)^2 (transposed intensity in
         // the buffer that is free)
         char *I = static_cast<char *>(I_out) + (size_t)b0 * nn(N) * real_bytes(dtype);
@@ -2283,7 +2294,7 @@ int ps_structure_function(int N, double delta, const void *phi, int n, const dou
             a.op(ROP_LOAD_R, ph, nn(N), N).op(ROP_FFT_FWD).op(ROP_STORE_C, W1, field_elems(N, dtype), field_row(N, dtype));
         };
         void *F = nullptr;
-        if (int rc = pass_exchange<ProgRealFwdTag, ProgRealFwdTTag>(N, nb, dtype, row_blocks(N, dtype), W1, W2, &F, stream, build)) return rc;
+        if (int rc = pass_exchange<ProgRealFwdTag, ProgRealFwdTTag>(N, nb, dtype, row_blocks(N, nb, dtype, true), W1, W2, &F, stream, build)) return rc;
         // the power map to the other buffer; the fields are free after it, and
         // hold the ring sums' scratch (a quarter of N^2 doubles at most)
         void *P = F == W1 ? W2 : W1, *rings = F;
