@@ -194,21 +194,25 @@ hipError_t launch_low_modes(void *G, int N, int K, int nbatch, uint32_t r0, uint
                             double amp0, double neg_beta_4, hipStream_t stream, bool swap, void *chirp_tab,
                             double chirp_a, double chirp_scale) {
     if (K < 0 || 2 * K + 1 > kLowW || K >= N / 2 || nbatch < 1) return hipErrorInvalidValue;
-    const int per = (N + kLowRows - 1) / kLowRows;
-    const int64_t blocks = (int64_t)per * nbatch;
-    const bool small = blocks <= 256;  // one per CU
+    const int64_t per = (N + kLowRows - 1) / kLowRows;
+    const bool small = per * nbatch <= 256;  // one per CU
     const int nt = small ? 1024 : 256;
-    const int64_t chirp = chirp_tab ? (N + nt - 1) / nt : 0;
-    if (blocks + chirp > (1ll << 31) - 1) return hipErrorInvalidValue;
-    LowModeArgs a{N, K, r0, seed_lo, seed_hi, amp0, neg_beta_4, swap ? 1 : 0, static_cast<cpx<float> *>(chirp_tab),
-                  chirp_a, chirp_scale, (int)blocks};
-    if (small)
-        hipLaunchKernelGGL((low_modes_kernel<1024>), dim3((unsigned)(blocks + chirp)), dim3(1024), 0, stream,
-                           static_cast<double2 *>(G), a);
-    else
-        hipLaunchKernelGGL((low_modes_kernel<256>), dim3((unsigned)(blocks + chirp)), dim3(256), 0, stream,
-                           static_cast<double2 *>(G), a);
-    return hipGetLastError();
+    // (a grid's threads are counted in 32 bits)
+    const int64_t most = (((1ll << 32) - 1) / nt - (N + nt - 1) / nt) / per;
+    for (int64_t b0 = 0; b0 < nbatch; b0 += most) {
+        const int64_t nb = nbatch - b0 < most ? nbatch - b0 : most;
+        // (the chirp table with the first screens)
+        const int64_t blocks = per * nb, chirp = chirp_tab && b0 == 0 ? (N + nt - 1) / nt : 0;
+        LowModeArgs a{N, K, r0 + (uint32_t)b0, seed_lo, seed_hi, amp0, neg_beta_4, swap ? 1 : 0,
+                      static_cast<cpx<float> *>(chirp_tab), chirp_a, chirp_scale, (int)blocks};
+        double2 *Gb = static_cast<double2 *>(G) + b0 * N * (K + 1);
+        if (small)
+            hipLaunchKernelGGL((low_modes_kernel<1024>), dim3((unsigned)(blocks + chirp)), dim3(1024), 0, stream, Gb, a);
+        else
+            hipLaunchKernelGGL((low_modes_kernel<256>), dim3((unsigned)(blocks + chirp)), dim3(256), 0, stream, Gb, a);
+        if (hipError_t e = hipGetLastError()) return e;
+    }
+    return hipSuccess;
 }
 
 // ---------------------------------------------------------------- twiddles

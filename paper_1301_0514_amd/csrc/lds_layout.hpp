@@ -221,6 +221,13 @@ constexpr ColumnSlot column_slot(int w, int line, int parts) {
     return ColumnSlot{(set * 8 + (w & 7)) * line + q % line, q / line % parts};
 }
 
+// Rows of one launch whose workgroups of `threads` take `rows` rows each, `parts`
+// of them per group, in whole sets of `set` groups: a grid's threads are counted
+// in 32 bits.
+constexpr long long rows_per_launch(int threads, int rows, int set, long long parts) {
+    return ((1ll << 32) - 1) / threads / parts / set * set * rows;
+}
+
 // Elements from one row of such a field to the next.  Stores by columns step
 // by whole rows: whole lines of 128 bytes, and 13 lines more from 2000 on,
 // which spreads them over the channels of the L2 (runs of 32 bytes written

@@ -75,15 +75,32 @@ static hipError_t launch_rows(const RowProgram &prog, const void *tw, hipStream_
     }
 }
 
+// the same in pieces of whole sets of row groups, as many rows as the threads
+// of a launch can be counted for
+template <int L, int V, int W>
+static hipError_t launch_pieces(const RowProgram &prog, const void *tw, hipStream_t stream) {
+    using Cfg = RowCfg<SCINT_REAL, L, V, W>;
+    const int64_t parts = iter_splittable<SCINT_PROG>() ? std::min(std::max(prog.iter_split, 1), prog.n_iter) : 1;
+    const int64_t most = rows_per_launch(Cfg::THREADS, Cfg::B, Cfg::IL ? 8 * Cfg::LINE_GROUPS : 8, parts);
+    if (has_side<SCINT_PROG>() || prog.total_rows - prog.row0 <= most) return launch_rows<L, V, W>(prog, tw, stream);
+    RowProgram p = prog;
+    for (int64_t r = prog.row0; r < prog.total_rows; r += most) {
+        p.row0 = (int32_t)r;
+        p.total_rows = (int32_t)std::min<int64_t>(r + most, prog.total_rows);
+        if (hipError_t e = launch_rows<L, V, W>(p, tw, stream)) return e;
+    }
+    return hipSuccess;
+}
+
 template <int L, int V>
 static hipError_t launch_one(const RowProgram &prog, const void *tw, hipStream_t stream) {
     constexpr int W = program_rows<SCINT_REAL, L, V, SCINT_PROG>(), elem = 2 * (int)sizeof(SCINT_REAL);
     if constexpr (std::is_same<SCINT_PROG, ProgPhaseProp>::value && stores_columns(L)) {
         constexpr int WP = poly_column_rows<L, V>(elem);
         const int64_t bytes = (int64_t)(prog.total_rows - prog.row0) * prog.n_iter * field_pitch(L, elem) * elem;
-        if (WP != W && bytes > kPolyCacheBytes) return launch_rows<L, V, WP>(prog, tw, stream);
+        if (WP != W && bytes > kPolyCacheBytes) return launch_pieces<L, V, WP>(prog, tw, stream);
     }
-    return launch_rows<L, V, W>(prog, tw, stream);
+    return launch_pieces<L, V, W>(prog, tw, stream);
 }
 
 template <>

@@ -48,7 +48,23 @@ template <int L, int V> static void check(int eb) {
     failures += !ok;
 }
 
+// launches of more rows than a grid's 32-bit thread count allows are cut
+static void check_launches() {
+    for (int threads : {32, 64, 250, 256, 1000, 1024})
+        for (int rows : {1, 2, 4, 64, 256})
+            for (int set : {8, 64, 128})
+                for (long long parts : {1, 2, 7, 64}) {
+                    const long long most = rows_per_launch(threads, rows, set, parts);
+                    const long long grid = (most / rows + set - 1) / set * set * parts;
+                    const bool ok = most >= (long long)rows * set && most % ((long long)rows * set) == 0 &&
+                                    grid * threads < (1ll << 32) && most + (long long)rows * set * 2 > ((1ll << 32) - 1) / threads / parts * rows;
+                    if (!ok) std::printf("FAIL threads=%d rows=%d set=%d parts=%lld: %lld\n", threads, rows, set, parts, most);
+                    failures += !ok;
+                }
+}
+
 int main() {
+    check_launches();
 #define SCINT_F64_CASE(LL) check<LL, 0>(16), check<LL, 0>(8);
     SCINT_SIZES_F64(SCINT_F64_CASE)
 #define SCINT_V_CASE(LL, VV) check<LL, VV>(8);
