@@ -47,9 +47,12 @@ constexpr bool plan_ok(int L, int E, const int *R, int ns) {
 // as the chip's rates ask: few elements per thread (and more exchanges) spread
 // a grid over more waves.  One FP64 256^2 screen + pattern 45 us with 16
 // elements per thread ({16,16}), 27 with 8 ({8,8,4}), 23 with 4; twelve FP32
-// ones 49, 44 and 43 us.  At 80 the radix 10 comes last: FP32 propagations
-// round to 2.21e-7 of the pattern's RMS so, 2.53e-7 with it first, 2.34e-7 as
-// {4,20}.
+// ones 49, 44 and 43 us.  Fewer elements mean other radices, and a plan is
+// taken only if no call's FP32 results round worse than with the larger ones.
+// At 80 none of those tried does: {2,2,2,10} propagates at 0.93 of {4,20}'s
+// error but its aperture is at 1.08 ({10,2,2,2}: 1.08 and 1.03), so {4,20} stays.
+// At 200 {10,2,10} is below {20,10} in every call (0.84-0.995; {10,10,2} smears
+// at 1.01).
 // powers of two
 SCINT_PLAN(16, 16, 16)
 SCINT_PLAN(32, 8, 8, 4)
@@ -64,10 +67,10 @@ SCINT_PLAN(8192, 32, 32, 8, 32)
 SCINT_PLAN(16384, 32, 32, 32, 16)
 // 2^a 5^b
 SCINT_PLAN(40, 20, 4, 10)
-SCINT_PLAN(80, 10, 2, 2, 2, 10)
+SCINT_PLAN(80, 20, 4, 20)
 SCINT_PLAN(100, 10, 10, 10)
 SCINT_PLAN(160, 20, 4, 4, 10)
-SCINT_PLAN(200, 10, 10, 10, 2)
+SCINT_PLAN(200, 10, 10, 2, 10)
 SCINT_PLAN(320, 20, 4, 4, 20)
 SCINT_PLAN(400, 20, 20, 20)
 SCINT_PLAN(640, 20, 4, 4, 4, 10)
