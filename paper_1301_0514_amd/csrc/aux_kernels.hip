@@ -748,7 +748,7 @@ hipError_t launch_ring_sums(const void *P, int N, int nbatch, bool f64, double *
 // Both sums run over a fixed number of terms with compile-time ratios (a
 // loop that divides, or takes the ratios from memory, waits for each): 48 of
 // the series, whose later terms vanish beside any sum, and 28 of the
-// expansion, up to its smallest term at x = 14 (7e-13; below 1e-13 from 15).
+// expansion, up to its smallest term at x = 14 (1.0e-13; 1.5e-14 at 15).
 constexpr int kJ0Series = 48, kJ0Hankel = 28;
 
 __device__ double bessel_j0(double x) {

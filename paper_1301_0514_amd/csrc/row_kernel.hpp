@@ -696,13 +696,13 @@ __device__ __forceinline__ void exec_op(RowState<Real, L, V, W> &st, const RowOp
         double part = 0.0;
 #pragma unroll
         for (int m = 0; m < E; ++m) part += (double)src[m * T] * (double)v[m].re;
+        static_assert(W == 0, "a row's threads next to each other");
         double *red = st.red;
         __syncthreads();
         red[st.tid] = part;
         __syncthreads();
-        constexpr int LS = RowCfg<Real, L, V, W>::LS;
         for (int width = 1; width < T; width *= 2) {
-            if ((st.t % (2 * width)) == 0 && st.t + width < T) red[st.tid] += red[st.tid + width * LS];
+            if ((st.t % (2 * width)) == 0 && st.t + width < T) red[st.tid] += red[st.tid + width];
             __syncthreads();
         }
         if (st.t == 0 && valid) static_cast<double *>(op.ptr2)[st.g] = red[st.tid];

@@ -816,7 +816,7 @@ int row_blocks(int N, int nb, int dtype, bool light = false) {
 // A pass over nb grids whose complex result goes to `from`, and the exchange
 // that hands it to the pass along the other axis (*next: `from` or `to`, which
 // must hold no operand of the pass).  build(p) appends the pass's operations.
-// In FP32 at the sizes with transposes the rows run in row_blocks() blocks
+// In FP32 at the sizes with transposes the rows run in J = row_blocks() blocks
 // of whole 64-row bands: the pass over block k carries the transpose of block
 // k - 1 as extra workgroups (the FFTs' arithmetic leaves memory bandwidth
 // free), and only the last block's runs on its own.  One 10000^2 screen +
@@ -825,13 +825,12 @@ int row_blocks(int N, int nb, int dtype, bool light = false) {
 // computed by the same kernel code either way, so the results do not depend on
 // the blocks.
 //
-// With blocks = 1 the whole pass comes first, and `to` may hold its operand.
+// With J = 1 the whole pass comes first, and `to` may hold its operand.
 template <class Tag, class TagT, class Build>
-int pass_exchange(int N, int nb, int dtype, int blocks, void *from, void *to, void **next, hipStream_t stream,
+int pass_exchange(int N, int nb, int dtype, int J, void *from, void *to, void **next, hipStream_t stream,
                   Build build) {
     const SideCfg sc = side_cfg();
     const int64_t nx = transpose_units_x(N), ny = transpose_units_y(N), bands = ny * nb;
-    const int J = blocks;
     if (J == 1) {
         ProgBuilder p(N, (int64_t)nb * N);
         build(p);
@@ -1250,7 +1249,10 @@ static int poly_chunk(int N, const void *phi, int nb, const std::vector<double> 
 }
 
 // Workgroups per row group of a first pass over C wavelengths at the smaller
-// sizes: more where the rows alone leave the chip idle.
+// sizes: more where the rows alone leave the chip idle, about 4096 rows x parts
+// in all (12 wavelengths of one 64^2 screen 41 us with one part, 30 so, of one
+// 640^2 168 and 118; with 16384, 12 x 160^2 118 -> 107, but 30 wavelengths of
+// 2 x 1024^2 397 -> 515).
 static int rows_iter_split(int64_t rows, int C) {
     return (int)std::max<int64_t>(1, std::min<int64_t>(C, 4096 / std::max<int64_t>(rows, 1)));
 }
@@ -1361,9 +1363,8 @@ static int poly_pipelined(int N, const char *phi_ref, const std::vector<PolyJob>
 // Jobs of the pipelined propagation (FP32): up to 64 wavelengths and as many
 // realisations per job as four complex buffers of the job's grids fit the
 // budget; work that fits one job is split in two (realisations, else
-// wavelengths); more jobs than the memory needs do not gain further.  Used
-// above 4096 only: below, the passes store by columns and need no transposes.  False if the work does not make two jobs or one job does
-// not fit.
+// wavelengths); more jobs than the memory needs do not gain further.  False if
+// the work does not make two jobs or one job does not fit.
 static bool plan_poly_jobs(int N, int n_real, int n_lambda, size_t budget, std::vector<PolyJob> *jobs, int *Cp_out,
                            int *nbp_out) {
     const size_t cbytes = (size_t)nn(N) * 8, rb1 = (size_t)nn(N) * 4;
@@ -1646,10 +1647,12 @@ int ps_aperture_geometry(int N, double delta, double lambda, double z, double r_
 }
 
 // The split of a polychromatic call (also reported by ps_plan_polychromatic):
-// in FP32 from 2048 up, the pipelined jobs when four complex buffers of a
+// in FP32 from 2048 up, the jobs of the pipeline when four complex buffers of a
 // job's grids fit (and there are two or more); otherwise chunks of C <= 64
 // wavelengths and nb realisations such that two complex buffers of C nb
-// grids plus the accumulator fit the budget.
+// grids plus the accumulator fit the budget.  From 5000 the jobs run pipelined;
+// up to 4096, where no transposes are carried, one after the other in one field
+// buffer, by the same split, so that a call's sums and reported plan stay.
 struct PolyPlan {
     bool pipelined = false;
     int C = 1, nb = 1;
@@ -2003,7 +2006,7 @@ int source_smear(int N, double delta, const void *I_in, const double *radii, int
             const int pairs = pair ? (nb - pb) / 2 : 0;
             // the pipelined jobs take pairs only; the other passes an odd last
             // realisation too, as a pair whose second is zero
-            const bool piped = dtype == PS_F32 && N >= 2048 && pairs >= 2 && sc.on && !cols;
+            const bool piped = dtype == PS_F32 && !cols && pairs >= 2 && sc.on;
             const int np = piped ? pairs : (nb - pb + 1) / 2;  // complex transforms in this group
             const int step = pair ? 2 : 1;                     // realisations per transform
             const char *Iin = static_cast<const char *>(I_in) + (size_t)(b0 + pb) * rb1;
