@@ -167,7 +167,8 @@ constexpr bool real_columns(int L) { return L <= kRealColumnsMaxL; }
 // batches half the rate (327 x 320^2 adjoints 458 us with two rows, 361 with
 // four; 8192 x 64^2 FP64 screens 930 and 553 us).  Rows of 10 and 20 threads do
 // not fill whole waves with more rows either: 100 keeps 40 threads, and 200 and
-// 400 do in FP64 (26 x 400^2 screens 129 us, 139 with 80 threads).
+// 400 do in FP64 (26 x 400^2 screens 129 us, 139 with 80 threads).  16, a thread
+// per row, keeps 32 (kept fields of 16384 FP64 screens 86 us, 131 with 64).
 // Passes of two or more transforms outside a wavelength loop (heavy: screen +
 // propagation, the adjoint's first) keep so many registers at 20 elements per
 // thread that a CU holds 8 waves: from 2000 on they take as many rows as let
@@ -183,7 +184,7 @@ template <int L, int V> constexpr int column_rows(int elem_bytes, bool heavy = f
     const int least = whole || elem_bytes == 8 ? 60 : 120;  // of a row's length per row
     int rows = 1;
     while (2 * rows <= 4 && 2 * rows * least <= L) rows *= 2;
-    while (T * rows < (64 % T == 0 ? 64 : 32)) rows *= 2;
+    while (T * rows < (64 % T == 0 && T > 1 ? 64 : 32)) rows *= 2;
     while (rows > 1 && (T * rows > 1024 || rows * exch_buffer_length<L, V>(elem_bytes, rows) * elem_bytes >
                                                (rows * elem_bytes > 32 ? 80 : 160) * 1024))
         rows /= 2;

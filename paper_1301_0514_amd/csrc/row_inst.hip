@@ -108,7 +108,7 @@ hipError_t launch_row<SCINT_REAL, SCINT_CAT(SCINT_PROG, Tag)>(int L, int V, cons
                                                                hipStream_t stream) {
 #define SCINT_CASE(LL) \
     case LL:           \
-        if (V == 0) return launch_one<LL, 0>(prog, tw, stream); \
+        if (V == 0) return launch_one<LL, SCINT_IS_F64 ? f64_plan(LL) : 0>(prog, tw, stream); \
         break;
 #define SCINT_VCASE(LL, VV) \
     if (L == LL && V == VV) return launch_one<LL, VV>(prog, tw, stream);

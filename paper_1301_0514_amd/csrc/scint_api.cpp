@@ -170,6 +170,7 @@ int get_twiddles(int L, int V, int dtype, const void **out, hipStream_t stream) 
     if (int rc = current_device(&dev)) return rc;
     std::lock_guard<std::mutex> lock(g_mutex);
     auto &dc = g_cache[dev];
+    if (dtype == PS_F64) V = f64_plan(L);
     auto key = std::make_tuple(L, V, dtype);
     auto it = dc.twiddles.find(key);
     if (it != dc.twiddles.end()) {
@@ -1458,7 +1459,7 @@ int fresnel_propagate_noalloc(int N, double delta, double lambda, double z, cons
     const size_t rbytes = (size_t)nn(N) * rb * n;
     if (overlaps(phi, rbytes, I_out, rbytes)) return fail(PS_E_ALIAS, "I_out overlaps phi");
     TwiddleStages ts;
-    if (!twiddle_stages(N, 0, &ts)) return fail(PS_E_SIZE, "no FFT plan for this size");
+    if (!twiddle_stages(N, dtype == PS_F64 ? f64_plan(N) : 0, &ts)) return fail(PS_E_SIZE, "no FFT plan for this size");
     // scratch: two complex fields per screen, the chirp table, the twiddles
     Carver c;
     const size_t oW1 = c.take(cb * (size_t)nn(N) * n), oW2 = c.take(cb * (size_t)nn(N) * n);

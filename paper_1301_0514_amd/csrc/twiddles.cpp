@@ -67,6 +67,7 @@ int twiddle_entries(int L, int V) {
 #define SCINT_VCASE(LL, VV) \
     if (L == LL && V == VV) return twiddle_count<LL, VV>();
     SCINT_VARIANTS_F32(SCINT_VCASE)
+    SCINT_VARIANTS_F64(SCINT_VCASE)
 #undef SCINT_VCASE
     if (V != 0) return 0;
 #define SCINT_CASE(LL) \
@@ -104,6 +105,7 @@ bool twiddle_stages(int L, int V, TwiddleStages *d) {
         return true;                         \
     }
     SCINT_VARIANTS_F32(SCINT_VCASE)
+    SCINT_VARIANTS_F64(SCINT_VCASE)
 #undef SCINT_VCASE
     if (V != 0) return false;
 #define SCINT_CASE(LL)      \
@@ -125,6 +127,7 @@ bool build_twiddles(int L, int V, double *out) {
         return true;            \
     }
     SCINT_VARIANTS_F32(SCINT_VCASE)
+    SCINT_VARIANTS_F64(SCINT_VCASE)
 #undef SCINT_VCASE
     if (V != 0) return false;
 #define SCINT_CASE(LL)     \
