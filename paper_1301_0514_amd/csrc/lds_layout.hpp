@@ -195,6 +195,17 @@ template <int L, int V> constexpr int column_rows(int elem_bytes, bool heavy = f
     return rows;
 }
 
+// Between 240 and 480, where two rows are more than half a wave (256, and 400 in
+// FP32), a call on few rows takes two per workgroup (0: no such rule), twice the
+// workgroups for a chip that they do not fill: up to 512 rows of 256 (one FP64
+// screen + pattern 21.8 us, 22.6 with four rows; four of them 27.7 and 25.2), up
+// to 8192 of 400, whose 80 threads fill a wave and a quarter (four screens +
+// patterns 45.7 and 49.8 us; 209 adjoints from the kept field 440 and 380).
+template <int L, int V> constexpr int few_column_limit() { return Plan<L, V>::T % 64 == 0 ? 512 : 8192; }
+template <int L, int V> constexpr int few_column_rows(int elem_bytes) {
+    return L >= 240 && L < 480 && 2 * Plan<L, V>::T > 32 && column_rows<L, V>(elem_bytes) > 2 ? 2 : 0;
+}
+
 // The first pass over several wavelengths (poly) writes that many fields.  Up to
 // 320, where they are more than the 256 MB cache holds, its runs go to memory
 // as they are: whole lines of 128 bytes, within 512 threads (11 wavelengths of

@@ -95,6 +95,11 @@ static hipError_t launch_pieces(const RowProgram &prog, const void *tw, hipStrea
 template <int L, int V>
 static hipError_t launch_one(const RowProgram &prog, const void *tw, hipStream_t stream) {
     constexpr int W = program_rows<SCINT_REAL, L, V, SCINT_PROG>(), elem = 2 * (int)sizeof(SCINT_REAL);
+    if constexpr (W > 0) {
+        constexpr int WF = few_column_rows<L, V>(elem);
+        if constexpr (WF > 0)
+            if (prog.total_rows - prog.row0 <= few_column_limit<L, V>()) return launch_pieces<L, V, WF>(prog, tw, stream);
+    }
     if constexpr (std::is_same<SCINT_PROG, ProgPhaseProp>::value && stores_columns(L)) {
         constexpr int WP = poly_column_rows<L, V>(elem);
         const int64_t bytes = (int64_t)(prog.total_rows - prog.row0) * prog.n_iter * field_pitch(L, elem) * elem;

@@ -41,6 +41,9 @@ template <int L, int V> static void check(int eb) {
     } else if (H != W) {
         ok = false;
     }
+    // calls on few rows
+    const int Z = few_column_rows<L, V>(eb);
+    ok = ok && (Z == 0 || (Z < W && slots_ok<L, V>(eb, Z)));
     // the first pass over many wavelengths
     const int Q = poly_column_rows<L, V>(eb);
     ok = ok && slots_ok<L, V>(eb, Q) && Q >= W && (Q == W || (L <= kPolyColumnsMaxL && T * Q <= 512));

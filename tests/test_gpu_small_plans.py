@@ -112,3 +112,28 @@ def test_small_plans_vs_oracle(S, oracle, N, n, dtype):
         i64 = I[b].double().cpu().numpy()
         for k, r in enumerate((2.0, N / 12.0)):
             close(ext[b, k], oracle.smear(i64, r), dtype)
+
+
+@pytest.mark.parametrize("dtype", [torch.float32, torch.float64])
+@pytest.mark.parametrize("N", [64, 200, 256, 400])
+def test_a_screen_does_not_depend_on_its_batch(S, N, dtype):
+    # rows per workgroup follow the number of rows at 256 and 400: the same values in a batch and alone
+    z = 2 * np.pi * (N / 10.0) ** 2 / LAM
+    lams = [0.8 * LAM, LAM, 1.2 * LAM]
+    n = 21 if N == 400 else 5
+    phi = torch.tensor(inputs.phase_field(N, 3, sigma=1.5, n=n), dtype=dtype, device="cuda")
+    g = torch.tensor(inputs.phase_field(N, 4, n=n), dtype=dtype, device="cuda")
+
+    def outputs(p, w, r0, n):
+        If, field = S.fresnel_propagate_field(p, 1.0, LAM, z)
+        return (S.ps_generate(N, 1.0, 3.0, 11 / 3, 7, r0, n, dtype=dtype),
+                S.ps_screen_fresnel(N, 1.0, 3.0, 11 / 3, 7, LAM, z, first_realisation=r0, n_real=n, dtype=dtype),
+                S.fresnel_propagate(p, 1.0, LAM, z), If, field, S.fresnel_propagate_vjp(p, 1.0, LAM, z, w),
+                S.fresnel_propagate_vjp(p, 1.0, LAM, z, w, field=field),
+                S.illumination_polychromatic(p, 1.0, z, LAM, lams), S.fresnel_aperture(p, 1.0, LAM, N / LAM))
+
+    batch = outputs(phi, g, 20, n)
+    for b in (0, n - 1):
+        alone = outputs(phi[b:b + 1].contiguous(), g[b:b + 1].contiguous(), 20 + b, 1)
+        for x, y in zip(batch, alone):
+            assert torch.equal(x[b:b + 1], y)
