@@ -50,12 +50,11 @@ constexpr bool plan_ok(int L, int E, const int *R, int ns) {
 // ones 49, 44 and 43 us.  Fewer elements mean other radices, and a plan is
 // taken only if no call's FP32 results round worse than with the larger ones.
 // At 80 none of those tried does: {2,2,2,10} propagates at 0.93 of {4,20}'s
-// error but its aperture is at 1.08 ({10,2,2,2}: 1.08 and 1.03), so {4,20} stays
-// in FP32.  In FP64 the chirps set the error, which no plan moves by more than
-// 2e-4, and the smear's falls to 0.96: {2,2,2,10} there (f64_plan), 40 screens of
-// 80^2 32 us as {4,20}, 21 with it.
+// error but its aperture is at 1.08 ({10,2,2,2}: 1.08 and 1.03), so {4,20} stays.
 // At 200 {10,2,10} is below {20,10} in every call (0.84-0.995; {10,10,2} smears
-// at 1.01).
+// at 1.01).  FP64 has orders of its own there (f64_plan), whose errors against
+// 64-bit transforms of another library are 0.97-1.01 of {4,20}'s and 0.99-1.01 of
+// {20,10}'s (smear 1.03); {2,2,2,10} 1.00-1.13, {10,2,10} 1.00-1.04.
 // powers of two
 SCINT_PLAN(16, 16, 16)
 SCINT_PLAN(32, 8, 8, 4)
@@ -102,7 +101,8 @@ SCINT_PLAN_V(16000, 1, 20, 20, 20, 20, 2)
 SCINT_PLAN_V(20000, 1, 20, 20, 20, 10, 5)
 
 // FP64's own (f64_plan)
-SCINT_PLAN_V(80, 1, 10, 2, 2, 2, 10)
+SCINT_PLAN_V(80, 1, 10, 10, 2, 2, 2)
+SCINT_PLAN_V(200, 1, 10, 10, 10, 2)
 
 #undef SCINT_PLAN_EXPAND
 #undef SCINT_PLAN
@@ -121,8 +121,8 @@ constexpr int plan_variants(int L) {
 
 // The plan that FP64 takes as its plan 0 at length L, and X(L, V) for those that
 // are not FP32's
-constexpr int f64_plan(int L) { return L == 80 ? 1 : 0; }
-#define SCINT_VARIANTS_F64(X) X(80, 1)
+constexpr int f64_plan(int L) { return L == 80 || L == 200 ? 1 : 0; }
+#define SCINT_VARIANTS_F64(X) X(80, 1) X(200, 1)
 
 // Sizes in ascending order, per precision (FP64 stops at 8192 because a
 // 10000-point complex128 row does not fit in the 160 KB of LDS; FP32 stops at
